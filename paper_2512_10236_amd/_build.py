@@ -10,7 +10,7 @@ LIB = os.path.join(HERE, "libficco.so")
 SOURCES = ["ficco_gemm.hip", "ficco_reduce.hip", "ficco_plan.hip", "ficco_engines.hip", "ficco_api.hip", "ficco_static.hip"]
 HEADERS = ["ficco_internal.h", "ficco_plan.h", os.path.join("..", "..", "include", "ficco.h")]
 
-# packed fp32 instructions are switched off for all device code (they have misbehaved on the test machines)
+# packed fp32 instructions are switched off for all device code (some of their forms have given wrong results on this hardware)
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function",
@@ -32,11 +32,8 @@ def build(force: bool = True, verbose: bool = False) -> str:
 
 
 def build_variant(out: str, defines: list[str], verbose: bool = False) -> str:
-    """A measuring build with extra -D switches (the timing-only ablations FICCO_ABL_* and the in-kernel clock
-    probes FICCO_PROBE of ficco_gemm.hip), linked to `out`; load it with FICCO_LIBRARY=<out>. The in-tree
-    library is not touched. Example:
-        python -c "from paper_2512_10236_amd import _build; _build.build_variant('/tmp/libficco_nobar.so', ['FICCO_ABL_NOBAR'])"
-    """
+    """The library built with extra -D switches and linked to `out`; load it with FICCO_LIBRARY=<out>. The in-tree
+    library is not touched."""
     import tempfile
     with tempfile.TemporaryDirectory() as objdir:
         return _compile(os.path.abspath(out), objdir, ["-D" + d for d in defines], verbose)
