@@ -9,8 +9,8 @@
 //                            counter in arrival order and wait until the tile's piece is ready.
 //
 // Data flow per workgroup tile (BM x BN, 256 threads = 4 wavefronts of 64):
-//   global --global_load_lds_dwordx4--> LDS (two stages of BK = 64, XOR-swizzled 16 B slots)
-//   LDS --ds_read_b128--> 8-element bf16 fragments --> v_mfma_f32_32x32x16_bf16 --> fp32 accumulators
+//   global --global_load_lds_dwordx4--> LDS (a ring of stages of BK = 64, XOR-swizzled 16 B slots)
+//   LDS --ds_read_b128--> 8-element bf16 fragments --> v_mfma_f32_16x16x32_bf16 --> fp32 accumulators
 // The weight is read from a packed copy Wt[N, K] (k contiguous), so A and Wt fragments use the
 // same access pattern. Every output element is accumulated over k ascending by the same
 // instruction, whatever the tile shape or row block, which makes results bit-identical across
@@ -18,73 +18,112 @@
 #include "ficco_internal.h"
 #include <stdlib.h>
 #include <type_traits>
+#include <utility>
 #include <algorithm>
 
 namespace ficco {
 
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
+// two fp32 -> two bf16, round to nearest even, in one instruction (v_cvt_pk_bf16_f32)
 static __device__ __forceinline__ uint32_t pack2_bf16_rne(float lo, float hi)
 {
-    // fp32 -> bf16 round to nearest even; NaN stays NaN (quiet).
-    uint32_t a = __float_as_uint(lo), b = __float_as_uint(hi);
-    uint32_t ra = (a + 0x7FFFu + ((a >> 16) & 1u)) >> 16;
-    uint32_t rb = (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
-    if ((a & 0x7FFFFFFFu) > 0x7F800000u) ra = (a >> 16) | 0x0040u;
-    if ((b & 0x7FFFFFFFu) > 0x7F800000u) rb = (b >> 16) | 0x0040u;
-    return (ra & 0xFFFFu) | (rb << 16);
+    const bf16x2_t v = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(uint32_t, v);
 }
 
-// 64 lanes x 16 B from global memory straight into 1 KiB of LDS starting at the wave-uniform byte address
-// lds_base (lane l lands at lds_base + 16 l). The global address is a wave-uniform 64-bit base (scalar
-// registers) plus a per-lane 32-bit byte offset, so that stepping along k costs scalar additions only and a
-// load needs one vector register. Issued through inline assembly so that the waits are placed by hand
-// (s_waitcnt vmcnt) and not widened by the compiler; M0 is declared clobbered, so the compiler keeps nothing
-// of its own in it across the load.
-static __device__ __forceinline__ void load_to_lds_16(const void *base, uint32_t lane_off, uint32_t lds_base)
+template <int... I, class Fn>
+static __device__ __forceinline__ void static_for_(std::integer_sequence<int, I...>, Fn &&f) { (f(std::integral_constant<int, I>{}), ...); }
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose index is a constant in every turn
+template <int N, class Fn>
+static __device__ __forceinline__ void static_for(Fn &&f) { static_for_(std::make_integer_sequence<int, N>{}, f); }
+
+// 64 lanes x 16 B from global memory straight into 1 KiB of LDS at the wave-uniform byte address in M0 (lane l lands
+// at M0 + 16 l). The global address is a wave-uniform 64-bit base (scalar registers) plus a per-lane 32-bit byte
+// offset, so that stepping along k costs scalar additions only and a load needs one vector register. Issued through
+// inline assembly so that the waits are placed by hand (s_waitcnt vmcnt) and not widened by the compiler. M0 is
+// written by an instruction of its own (set_lds_target), which the k loop places one MFMA ahead of the load: the wait
+// state the hardware wants between the two is then an MFMA instead of a no-op, and no slot between two MFMAs has to
+// take more than two instructions. Between a set_lds_target and its load there is no other use of M0 (the kernels
+// use nothing that needs it: no GDS, no messages, no indirect registers).
+//
+// The base must be in scalar registers well before the load: a scalar register that a vector instruction has written
+// (v_readfirstlane, which is what the compiler makes of an address it cannot prove uniform) may be read by a memory
+// instruction only 5 wait states later, and the compiler, which sees to that for its own instructions, does not look
+// into inline assembly. scalar_base() is the way in: it makes the two halves uniform, waits, and returns an opaque
+// scalar, on which everything after it is scalar arithmetic. (tests/test_build_resources.py checks the assembly.)
+static __device__ __forceinline__ const uint16_t *scalar_base(const uint16_t *p)
 {
-    // (the base is the same in every lane by construction; the compiler cannot always see that - where it
-    // comes out of a table in memory, say - and is told so, half by half)
-    const uint64_t b = (uint64_t)base;
-    const uint64_t ub = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32) |
-                        (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 ::"v"(lane_off), "s"(ub), "s"(__builtin_amdgcn_readfirstlane(lds_base)) : "memory", "m0");
+    const uint64_t b = (uint64_t)p;
+    uint64_t s = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
+    asm volatile("s_nop 4" : "+s"(s));
+    return (const uint16_t *)s;
+}
+static __device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <int IMM>
+static __device__ __forceinline__ void set_lds_target(uint32_t lds_base)
+{
+    asm volatile("s_add_i32 m0, %0, %1" ::"s"(lds_base), "n"(IMM) : "m0", "scc");
+}
+static __device__ __forceinline__ void load_to_lds_16(const void *base, uint32_t lane_off)
+{
+    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base) : "memory");
 }
 template <int N>
 static __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 static __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-template <int BM_, int BN_, int WGM_, int WGN_, int NSTAGE_, int BK_ = kBK>
+// A workgroup tile and the schedule of its k loop. The loop's unit is the slot: one v_mfma_f32_16x16x32_bf16 and what
+// is issued behind it. A turn of TT slots multiplies one k-tile (a stage of 64 k values, two halves of 32); see
+// tile_accumulate_from for what the positions mean.
+template <int BM_, int BN_, int WGM_, int WGN_, int NSTAGE_>
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_;
-    static constexpr int NSTAGE = NSTAGE_;                     // LDS stages in the ring; loads run NSTAGE-1 k-tiles ahead
-    static constexpr int BK = BK_;                             // k extent of one LDS stage: 64, or 32 (a deeper ring in the same LDS)
-    static constexpr int KSUB = BK / 16;                       // sub-steps (one MFMA's k extent each) per stage
+    static constexpr int NSTAGE = NSTAGE_;                     // LDS stages in the ring: the loads of k-tile k + NSTAGE follow the reads of k-tile k
+    static constexpr int BK = kBK;
     static constexpr int ROWB = BK * 2;                        // bytes of a row of a stage
     static constexpr int SLOTS = BK / 8;                       // 16-byte slots per row
     static constexpr int RPL = 1024 / ROWB;                    // rows one load instruction (64 lanes x 16 B) fills
-    static constexpr int SWZ_SHIFT = BK == 64 ? 1 : 2;         // rows that share a 256-byte bank line
     static constexpr int THREADS = WGM * WGN * 64;
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;       // wavefront tile
-    static constexpr int FM = WTM / 32, FN = WTN / 32;         // 32x32 MFMA blocks per wavefront
+    static constexpr int FM = WTM / 16, FN = WTN / 16;         // 16x16 MFMA blocks per wavefront
     static constexpr int A_STAGE = BM * ROWB, B_STAGE = BN * ROWB;   // bytes
     static constexpr int STAGE = A_STAGE + B_STAGE;
     static constexpr int LDS_BYTES = NSTAGE * STAGE;
-    static constexpr int NW = WGM * WGN;                       // wavefronts: 4 (one per SIMD) or 8 (two per SIMD)
+    static constexpr int NW = WGM * WGN;                       // wavefronts, one per SIMD
     static constexpr int AB = BM / RPL / NW, BB = BN / RPL / NW; // 1 KiB blocks loaded per wavefront per stage
     static constexpr int LOADS = AB + BB;                      // load instructions per wavefront per k-tile
-    static_assert(BK == 64 || BK == 32, "stages of 64 or 32 k values");
+    static constexpr int NM = FM * FN, TT = 2 * NM;            // MFMAs per half and per turn
+    static constexpr int NR = FM + FN;                         // fragment reads per half
+    // LDS hands a wavefront one 1 KiB fragment in about 32 cycles when all four read: a read every second slot where the
+    // turn has the slots for it.
+    static constexpr int RSTEP = TT >= 4 * NR ? 2 : 1;
+    // Two stages: the stage is free (FREE) long before the other one is needed (LAND). More stages: one barrier does both.
+    static constexpr bool SPLIT = NSTAGE == 2 && TT >= 64;
+    static constexpr int R1 = SPLIT ? 6 : 0;                   // first slot of the reads of this k-tile's second half
+    static constexpr int FREE = R1 + NR * RSTEP + (SPLIT ? 2 : RSTEP == 2 ? 4 : 3);
+    static constexpr int LAND = SPLIT ? TT + 4 - 2 * (NR - 1) - 2 : FREE;
+    static constexpr int R0 = SPLIT ? LAND + 2 : LAND + 1;     // first slot of the reads of the next k-tile's first half
+    static constexpr int LS = FREE + 1;                        // first load of k-tile k + NSTAGE
+    static constexpr int LSTEP = NSTAGE == 2 && !SPLIT ? 2 : TT / LOADS > 0 ? TT / LOADS : 1;
+    static constexpr bool at(int dist, int step, int count) { return dist >= 0 && dist % step == 0 && dist / step < count; }
+    static constexpr int load_slot(int l) { return LS + l * LSTEP; }
+    static constexpr int loads_before(int slot) { int n = 0; for (int l = 0; l < LOADS; ++l) n += load_slot(l) < slot; return n; }
+    static constexpr int WRAPPED = LOADS - loads_before(TT);   // loads that fall into the next turn
+    // loads in flight at LAND that are younger than those of the next k-tile
+    static constexpr int younger_at_land() { int n = 0; for (int e = 0; e + 2 <= NSTAGE; ++e) n += loads_before(LAND + e * TT); return n; }
     static_assert(NSTAGE >= 2 && NSTAGE <= 4, "ring of 2 to 4 stages");
     static_assert(LDS_BYTES <= 160 * 1024 - 64, "LDS ring plus the kernels' few static words must fit one CU");
-    static_assert(THREADS == 256 || THREADS == 512, "4 or 8 wavefronts");
+    static_assert(THREADS == 256, "4 wavefronts");
     static_assert(BM % (RPL * NW) == 0 && BN % (RPL * NW) == 0, "every wavefront loads the same number of blocks");
-    static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wavefront tile is made of 32x32 blocks");
+    static_assert(WTM % 16 == 0 && WTN % 32 == 0, "wavefront tile is made of 16x16 blocks, stored in pairs along a row");
     static_assert(AB >= 1 && BB >= 1, "tile too small for the loader");
+    static_assert(R0 + (NR - 1) * RSTEP - TT < (FM - 1) * FN && R0 + (NR - 1) * RSTEP - TT < FREE && load_slot(LOADS - 1) - TT < LS && load_slot(LOADS - 1) < LAND + (NSTAGE - 1) * TT,
+                  "what a turn leaves to the next one is done before it is needed");
 };
 
 // Computes one BM x BN tile. a_tile: first row of the tile in A; rows_valid in [1, BM] rows of
@@ -100,7 +139,7 @@ struct TileCfg {
 // tile_accumulate_from.
 template <class T>
 struct TileAcc {
-    f32x16_t acc[T::FN][T::FM];
+    f32x4_t acc[T::FN][T::FM];
 };
 
 template <class T>
@@ -109,9 +148,10 @@ static __device__ __forceinline__ void tile_zero(TileAcc<T> &ta)
 #pragma unroll
     for (int j = 0; j < T::FN; ++j)
 #pragma unroll
-        for (int i = 0; i < T::FM; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) ta.acc[j][i][v] = 0.f;
+        for (int i = 0; i < T::FM; ++i) ta.acc[j][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // the MFMAs are inline assembly, so the compiler does not know what they need after a write to their accumulators
+    asm volatile("s_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 struct NoHook {
@@ -120,14 +160,14 @@ struct NoHook {
 
 // Byte offset, from the first row of the tile, of what lane `lane` fetches for 1 KiB block `blk` of a stage:
 // row blk*RPL + lane/SLOTS (clamped to the last row that exists), 16-byte slot (lane%SLOTS) ^ swizzle(row) of
-// its k-tile. The swizzle - (row>>1)&7 for rows of 128 B, (row>>2)&3 for rows of 64 B - spreads the rows that
-// share a 256-byte line of banks over different slots, so that the 16 lanes of a ds_read_b128 phase, which read
-// the same k slot of 16 consecutive rows, hit 64 different banks.
+// its k-tile. The swizzle - (row>>1)&7, two rows of 128 B share a 256-byte line of banks - spreads the rows over
+// different slots, so that the 16 lanes of a ds_read_b128 phase, which read one k slot of 16 consecutive rows, hit 64
+// different banks.
 template <class T>
 static __device__ __forceinline__ uint32_t lane_offset(int blk, int lane, int rows_valid, int64_t row_stride_elems)
 {
     const int row = blk * T::RPL + lane / T::SLOTS;
-    const int kc = (lane % T::SLOTS) ^ ((row >> T::SWZ_SHIFT) & (T::SLOTS - 1));
+    const int kc = (lane % T::SLOTS) ^ ((row >> 1) & (T::SLOTS - 1));
     const int rr = row < rows_valid ? row : rows_valid - 1;
     return (uint32_t)(((int64_t)rr * row_stride_elems + kc * 8) * 2);
 }
@@ -140,7 +180,7 @@ template <class T>
 struct PlainA {
     uint32_t off[T::AB];
     const uint16_t *base;
-    __device__ __forceinline__ PlainA(const uint16_t *a_tile, int rows_valid, int64_t lda, int wave, int lane) : base(a_tile)
+    __device__ __forceinline__ PlainA(const uint16_t *a_tile, int rows_valid, int64_t lda, int wave, int lane) : base(scalar_base(a_tile))
     {
 #pragma unroll
         for (int i = 0; i < T::AB; ++i) off[i] = lane_offset<T>(wave * T::AB + i, lane, rows_valid, lda);
@@ -170,10 +210,10 @@ struct SlicedA {
     {
         while (kt >= kt_end) {               // uniform: every lane takes the same steps
             ++sl;
-            const int kb = k0[sl], kw = k0[sl + 1] - kb;
+            const int kb = scalar(k0[sl]), kw = scalar(k0[sl + 1]) - kb;
             kt_begin = kt_end;
             kt_end += kw / T::BK;
-            base = A + M * kb + row0 * kw;
+            base = scalar_base(A + M * kb + row0 * kw);
 #pragma unroll
             for (int i = 0; i < T::AB; ++i) off[i] = lane_offset<T>(wave * T::AB + i, lane, rows_valid, kw);
         }
@@ -181,147 +221,145 @@ struct SlicedA {
     __device__ __forceinline__ const uint16_t *at(int kt) const { return base + (int64_t)(kt - kt_begin) * T::BK; }
 };
 
-// Waits until at most `load_groups` k-tiles' worth of this wavefront's loads are outstanding (the counter wants
-// a constant, hence the ladder; load_groups <= 2 with rings of at most four stages).
-template <class T>
-static __device__ __forceinline__ void wait_issued_after(int load_groups)
+// One MFMA: 16 columns of the packed weight x 16 rows of A x 32 k. The operands are passed swapped (D[n][m]), so that
+// a lane ends up with 4 consecutive columns of one C row. Inline assembly with the accumulator tied to the
+// accumulation registers: the builtin leaves the register allocator free to move the 256 of the big tile between the
+// two halves of the register file, which it does with hundreds of copies per turn.
+static __device__ __forceinline__ void mfma_16x16x32(f32x4_t &c, const bf16x8_t &n, const bf16x8_t &m)
 {
-    if (load_groups >= 2) wait_vmem<2 * T::LOADS>();
-    else if (load_groups == 1) wait_vmem<T::LOADS>();
-    else wait_vmem<0>();
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(n), "v"(m));
 }
 
+// The k loop. Turn k multiplies k-tile k out of registers: slots [0, NM) its first half (k values 0..31 of the stage),
+// whose fragments were read during the turn before, slots [NM, TT) its second half, whose fragments are read during
+// the first (from slot R1 on). Behind the MFMAs go, at fixed slots (TileCfg),
+//   FREE   all of this wavefront's reads of the stage are in registers; barrier: that holds for every wavefront
+//   LS...  the loads of k-tile k + NSTAGE into the stage just freed, one every LSTEP slots, spread over a whole turn:
+//          the last WRAPPED of them fall into turn k + 1
+//   LAND   k-tile k + 1 has landed for this wavefront's loads; barrier: for everyone's
+//   R0...  the reads of the first half of k-tile k + 1
+// so that no wait ever has an MFMA's operands behind it, a load has between half a turn and a turn and a half (two
+// stages) to arrive, and the address path, which takes 16 cycles per load and is shared by the four wavefronts, sees
+// them evenly. All issue order is pinned (sched_barrier); what the compiler adds are the LDS waits of the fragments.
+//
+// What it measured on the 256x256 tile (M 4096, K 16384, N 4096: one round of tiles; random data, board at its 1400 W):
+// v_mfma_f32_32x32x16 in this loop 1326 TFLOP/s, v_mfma_f32_16x16x32 1399 (half the accumulator traffic per flop, and
+// the same bits); its loads spread over the turn instead of one every four slots 1512 (a denser issue holds up the
+// MFMAs behind it); M0 written a slot ahead of its load 1552; this loop's row-segment stores 1556. The loop before it
+// (32x32x16, one barrier per turn, the loads of a k-tile within half a turn) 1244; the vendor library 1596-1650.
+// Of a turn's 2470 cycles 2048 are MFMAs; LDS reads cost 100, the loads 70 when they hit in L2, and what misses it 230.
 template <class T, class Hook = NoHook, class AddrA = PlainA<T>>
 static __device__ __forceinline__ void tile_accumulate_from(TileAcc<T> &ta, AddrA &pa,
                                                             const uint16_t *__restrict__ wt_tile, int cols_valid,
                                                             int64_t ldw, int K, unsigned char *smem,
                                                             Hook after_first_wait = Hook())
 {
-    f32x16_t (&acc)[T::FN][T::FM] = ta.acc;
+    f32x4_t (&acc)[T::FN][T::FM] = ta.acc;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / T::WGN, wn = wave % T::WGN;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const uint16_t *const wt = scalar_base(wt_tile);
+    constexpr int D = T::NSTAGE;           // k-tiles between a stage's reads and the loads that refill it
 
     uint32_t offb[T::BB];                  // per-lane byte offsets of the W loads from the tile's first row
 #pragma unroll
     for (int i = 0; i < T::BB; ++i) offb[i] = lane_offset<T>(wave * T::BB + i, lane, cols_valid, ldw);
-    // load l of the wavefront's LOADS loads of k-tile kt into `stage`: first the AB blocks of A, then the BB blocks
-    // of W (k-tiles are issued in ascending order; load 0 of a k-tile comes first)
-    auto issue_load = [&](int stage, int kt, int l) {
-        if (l == 0) pa.seek(kt);
-        if (l < T::AB) load_to_lds_16(pa.at(kt), pa.off[l], lds0 + stage * T::STAGE + (wave * T::AB + l) * 1024);
-        else load_to_lds_16(wt_tile + (int64_t)kt * T::BK, offb[l - T::AB], lds0 + stage * T::STAGE + T::A_STAGE + (wave * T::BB + (l - T::AB)) * 1024);
+    // load l of the wavefront's LOADS loads of a k-tile: first the AB blocks of A, then the BB blocks of W (k-tiles are
+    // issued in ascending order; load 0 of a k-tile comes first)
+    const uint32_t lds_a = lds0 + wave * T::AB * 1024, lds_b = lds0 + T::A_STAGE + wave * T::BB * 1024;
+    auto aim = [&](uint32_t stage, auto l_c) __attribute__((always_inline)) {
+        constexpr int l = decltype(l_c)::value;
+        if constexpr (l < T::AB) set_lds_target<l * 1024>(lds_a + stage);
+        else set_lds_target<(l - T::AB) * 1024>(lds_b + stage);
+    };
+    auto load = [&](int kt, auto l_c) __attribute__((always_inline)) {
+        constexpr int l = decltype(l_c)::value;
+        if constexpr (l == 0) pa.seek(kt);
+        if constexpr (l < T::AB) load_to_lds_16(pa.at(kt), pa.off[l]);
+        else load_to_lds_16(wt + (int64_t)kt * T::BK, offb[l - T::AB]);
     };
 
-    // LDS -> fragment addresses: lane reads row (lane%32) of a 32-row block, k-slot 2*kk + lane/32,
+    // LDS -> fragment addresses: lane reads row (lane%16) of a 16-row block, k-slot 4*half + lane/16,
     // un-swizzled by the row's swizzle, which only depends on the lane
-    const int frow = lane & 31, fh = lane >> 5, fs = (frow >> T::SWZ_SHIFT) & (T::SLOTS - 1);
+    const int frow = lane & 15, fh = lane >> 4, fs = (frow >> 1) & 7;
     const int a_base = (wm * T::WTM + frow) * T::ROWB;
     const int b_base = T::A_STAGE + (wn * T::WTN + frow) * T::ROWB;
-
-    const int KT = K / T::BK;
-    constexpr int D = T::NSTAGE - 1;      // prefetch distance in k-tiles
     bf16x8_t fa[2][T::FM], fb[2][T::FN];
-    // fragment q of the FM + FN fragments of sub-step kk of the k-tile in the stage at `base`, into buffer n.
-    // Order of arrival = order of first use by the MFMAs below (row block 0, then every column block, then the
-    // other row blocks).
-    auto read_frag = [&](const unsigned char *base, int kk, int n, int q) {
-        const int slot = ((2 * kk + fh) ^ fs) << 4;
-        if (q == 0) fa[n][0] = *reinterpret_cast<const bf16x8_t *>(base + a_base + slot);
-        else if (q <= T::FN) fb[n][q - 1] = *reinterpret_cast<const bf16x8_t *>(base + b_base + (q - 1) * 32 * T::ROWB + slot);
-        else fa[n][q - T::FN] = *reinterpret_cast<const bf16x8_t *>(base + a_base + (q - T::FN) * 32 * T::ROWB + slot);
+    // fragment q of the FM + FN fragments of a half: the order of their first use (row block 0, every column block,
+    // the other row blocks)
+    auto read_frag = [&](uint32_t stage, auto half_c, auto q_c) __attribute__((always_inline)) {
+        constexpr int half = decltype(half_c)::value, q = decltype(q_c)::value;
+        const int slot = ((4 * half + fh) ^ fs) << 4;
+        const unsigned char *base = smem + stage + slot;
+        if constexpr (q == 0) fa[half][0] = *reinterpret_cast<const bf16x8_t *>(base + a_base);
+        else if constexpr (q <= T::FN) fb[half][q - 1] = *reinterpret_cast<const bf16x8_t *>(base + b_base + (q - 1) * 16 * T::ROWB);
+        else fa[half][q - T::FN] = *reinterpret_cast<const bf16x8_t *>(base + a_base + (q - T::FN) * 16 * T::ROWB);
     };
-    constexpr int NM = T::FM * T::FN;           // MFMAs per sub-step
-    constexpr int NR = T::FM + T::FN;           // fragment reads per sub-step
-    constexpr int H1 = T::LOADS / 2, H2 = T::LOADS - H1;      // the two halves of a k-tile's loads
+    constexpr std::integral_constant<int, 0> first{};
+    constexpr std::integral_constant<int, 1> second{};
 
-    // ---- prologue: the first D k-tiles' loads, the first barrier, the first fragments
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-        if (d < KT) {
-#pragma unroll
-            for (int l = 0; l < T::LOADS; ++l) issue_load(d, d, l);
-        }
-    wait_issued_after<T>(min(D - 1, KT - 1));
-    wg_barrier();                          // B_0: k-tile 0 has landed for everyone
+    // Past the last k-tile the loads go on, on the last k-tile again and into stages that are not read any more: every
+    // turn is then the same code, which is what keeps the accumulators where they are (with a turn of its own for the
+    // end of a tile the compiler copies all 256 of them between the two).
+    const int KT = scalar(K) / T::BK;
+    // ---- prologue: the loads of the first D k-tiles, except those that turn 0 issues itself
+    static_for<D>([&](auto d) __attribute__((always_inline)) {
+        static_for<T::LOADS>([&](auto l) __attribute__((always_inline)) {
+            if constexpr (d.value < D - 1 || l.value < T::LOADS - T::WRAPPED) {
+                aim(d.value * T::STAGE, l);
+                asm volatile("s_nop 0" ::: "memory");
+                load(min(d.value, KT - 1), l);
+            }
+        });
+    });
+    wait_vmem<(D - 1) * T::LOADS - T::WRAPPED>();
+    wg_barrier();                          // k-tile 0 has landed for everyone
     after_first_wait();
-    if (D < KT) {
-#pragma unroll
-        for (int l = 0; l < H1; ++l) issue_load(D % T::NSTAGE, D, l);
-    }
-#pragma unroll
-    for (int q = 0; q < NR; ++q) read_frag(smem, 0, 0, q);
+    static_for<T::NR>([&](auto q) __attribute__((always_inline)) { read_frag(0, first, q); });
 
-    // ---- the loop, one k-tile (a stage of BK k values, KSUB sub-steps of one MFMA's k extent) per turn, rotated by
-    // one sub-step: a turn runs all but the last sub-step of k-tile k out of the fragments read one sub-step earlier,
-    // then waits for k-tile k+1 and for its own LDS reads and meets the others at barrier B_{k+1} (k-tile k+1 has
-    // landed for everyone; everyone is done with the stage of k-tile k, which the loads of k-tile k+1+D may now
-    // overwrite), and only then runs the last sub-step, whose MFMAs (16 in the big tiles) need registers only: under them go the first half of the loads of k-tile k+1+D and the reads of the first
-    // fragments of k-tile k+1, so that neither the barrier nor the LDS latency behind it leaves the MFMA pipe
-    // empty. The second half of those loads follows under sub-step 0 of the next turn. Every MFMA of the big
-    // tiles is followed by at most one load or one read, and the order is pinned (sched_barrier), so that a
-    // wavefront never issues a burst of loads: the four wavefronts share one address path, which takes about 16
-    // cycles per load, and whatever a wavefront issues between two MFMAs beyond the 32 cycles one of them takes
-    // leaves the MFMA pipe empty.
-    // (A turn is compiled in two forms: the steady state, where every condition is known and the body has no
-    // branch, and a general one for the first and last turns of a tile.)
-    auto turn = [&](int k, auto l1st, auto l2nd, auto rn, auto steady_c) __attribute__((always_inline)) {
-        constexpr bool steady = decltype(steady_c)::value;
-        const unsigned char *cur = smem + (k % T::NSTAGE) * T::STAGE;
-        const unsigned char *nxt = smem + ((k + 1) % T::NSTAGE) * T::STAGE;
-        const int free_stage = k % T::NSTAGE;           // after B_{k+1}
-#pragma unroll
-        for (int kk = 0; kk < T::KSUB; ++kk) {
-            const int c = kk & 1, n = c ^ 1;
-            if (kk == T::KSUB - 1) {
-                // everything this wavefront reads from the stage of k-tile k has arrived in registers
+    if constexpr (T::at(T::TT - T::LS, T::LSTEP, T::LOADS)) aim((D - 1) * T::STAGE, std::integral_constant<int, (T::TT - T::LS) / T::LSTEP>{});
+    uint32_t st_prev = (D - 1) * T::STAGE, st_cur = 0;         // byte offsets in the ring of the stages of k-tiles k - 1 and k
+#pragma clang loop unroll(disable)
+    for (int k = 0; k < KT; ++k) {
+        const uint32_t st_next = st_cur == (D - 1) * T::STAGE ? 0 : st_cur + T::STAGE;
+        const int kt = min(k + D, KT - 1), kt_wrapped = min(k + D - 1, KT - 1);
+        static_for<T::TT>([&](auto p_c) __attribute__((always_inline)) {
+            constexpr int p = decltype(p_c)::value;
+            constexpr int half = p / T::NM, w = p % T::NM, i = w / T::FN;
+            constexpr int j = i % 2 ? T::FN - 1 - w % T::FN : w % T::FN;       // back and forth: one operand stays from MFMA to MFMA
+            mfma_16x16x32(acc[j][i], fb[half][j], fa[half][i]);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (T::at(p - T::R1, T::RSTEP, T::NR)) read_frag(st_cur, second, std::integral_constant<int, (p - T::R1) / T::RSTEP>{});
+            if constexpr (p == T::FREE) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                // ... and k-tile k+1 has landed: what may still be in flight are the loads issued after its own,
-                // those of the k-tiles k+2 .. k+D that exist (memory operations complete in issue order)
-                if constexpr (steady) wait_vmem<(D - 1) * T::LOADS>();
-                else if (rn) wait_issued_after<T>(min(D - 1, KT - 2 - k));
+                if constexpr (T::FREE == T::LAND) wait_vmem<T::younger_at_land()>();
                 wg_barrier();
             }
-#pragma unroll
-            for (int t = 0; t < NM; ++t) {
-                const int i = t / T::FN, j = t % T::FN;
-                // operands swapped on purpose: D[n][m], so each lane ends up with 4 consecutive
-                // columns of one C row (8-byte stores in the epilogue)
-                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[c][j], fa[c][i], acc[j][i], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                // under this MFMA: the reads and loads whose turn it is. Reads of the next sub-step's fragments go
-                // behind the even MFMAs, loads behind the odd ones, where there are enough MFMAs to keep them apart.
-#pragma unroll
-                for (int q = 0; q < NR; ++q)
-                    if (q * NM / NR == t) {
-                        if (kk < T::KSUB - 1) read_frag(cur, kk + 1, n, q);
-                        else if (rn) read_frag(nxt, 0, n, q);
-                    }
-                if (kk == T::KSUB - 1 && l1st) {
-#pragma unroll
-                    for (int l = 0; l < H1; ++l)
-                        if (min(NM - 1, l * NM / H1 + ((NM / H1 / 2) | 1)) == t) issue_load(free_stage, k + 1 + D, l);
-                }
-                if (kk == 0 && l2nd) {
-#pragma unroll
-                    for (int l = 0; l < H2; ++l)
-                        if (min(NM - 1, l * NM / H2 + ((NM / H2 / 2) | 1)) == t) issue_load((k + D) % T::NSTAGE, k + D, H1 + l);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+            if constexpr (p == T::LAND && T::FREE != T::LAND) {
+                wait_vmem<T::younger_at_land()>();
+                wg_barrier();
             }
-        }
-    };
-    constexpr std::true_type yes{};
-    constexpr std::false_type no{};
-    int k = 0;
-    for (; k + 1 < D && k + 1 + D < KT; ++k) turn(k, true, true, true, no);    // (rings of three or four stages only)
-    for (; k + 1 + D < KT; ++k) turn(k, yes, yes, yes, yes);
-    for (; k < KT; ++k) turn(k, false, k + D < KT, k + 1 < KT, no);
-    // (the barrier before the last sub-step was the last one: every wavefront had finished reading the ring)
+            // a load, then the target of the next slot's
+            if constexpr (T::at(p + T::TT - T::LS, T::LSTEP, T::LOADS)) load(kt_wrapped, std::integral_constant<int, (p + T::TT - T::LS) / T::LSTEP>{});
+            if constexpr (T::at(p - T::LS, T::LSTEP, T::LOADS)) load(kt, std::integral_constant<int, (p - T::LS) / T::LSTEP>{});
+            constexpr int n = (p + 1) % T::TT;
+            if constexpr (T::at(n + T::TT - T::LS, T::LSTEP, T::LOADS))
+                aim(p + 1 < T::TT ? st_prev : st_cur, std::integral_constant<int, (n + T::TT - T::LS) / T::LSTEP>{});
+            if constexpr (T::at(n - T::LS, T::LSTEP, T::LOADS)) aim(st_cur, std::integral_constant<int, (n - T::LS) / T::LSTEP>{});
+            // (in a tile's last turn these read a stage that is not used again)
+            if constexpr (T::at(p - T::R0, T::RSTEP, T::NR)) read_frag(st_next, first, std::integral_constant<int, (p - T::R0) / T::RSTEP>{});
+            if constexpr (T::at(p + T::TT - T::R0, T::RSTEP, T::NR)) read_frag(st_cur, first, std::integral_constant<int, (p + T::TT - T::R0) / T::RSTEP>{});
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        st_prev = st_cur;
+        st_cur = st_next;
+    }
+    // accumulators may be read after the last MFMA's 16 passes
+    asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
-
 
 template <class T, class Hook = NoHook>
 static __device__ __forceinline__ void tile_accumulate(TileAcc<T> &ta, const uint16_t *__restrict__ a_tile, int rows_valid,
@@ -334,86 +372,38 @@ static __device__ __forceinline__ void tile_accumulate(TileAcc<T> &ta, const uin
 }
 
 // Rounds the accumulators to bf16 (nearest even) and stores the valid part of the tile.
-template <class T>
+// acc[j][i][v] is C[m][n] with m = wm*WTM + 16 i + lane%16, n = wn*WTN + 16 j + 4 (lane/16) + v. The lanes of odd rows
+// of 16 exchange their half of column block j for their neighbours' half of block j + 1 (v_permlane16_swap), after
+// which a lane holds 8 consecutive columns: a store instruction writes 16 bytes per lane, 64 bytes in each of 16 rows,
+// and the two instructions of 64 columns whole lines. (8-byte stores without the exchange: twice the requests, and
+// with the conversion done in integer arithmetic 6700 cycles more per 256x256 tile; M 65536, K 4096, N 14336: 5281 ->
+// 5124 us.) THROUGH: written through the caches (system scope), for output that a copy engine reads while the kernel
+// runs on. N and with it cols_valid are multiples of 8.
+template <class T, bool THROUGH = false>
 static __device__ __forceinline__ void tile_store(const TileAcc<T> &ta, uint16_t *__restrict__ c_tile, int rows_valid,
                                                   int cols_valid, int64_t ldc)
 {
-    const f32x16_t (&acc)[T::FN][T::FM] = ta.acc;
+    const f32x4_t (&acc)[T::FN][T::FM] = ta.acc;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / T::WGN, wn = wave % T::WGN;
-    const int frow = lane & 31, fh = lane >> 5;
-    // ---- epilogue: acc[j][i][v] is C[m][n] with m = wm*WTM + 32 i + lane%32,
-    //      n = wn*WTN + 32 j + 8 (v/4) + 4 (lane/32) + v%4
+    const int frow = lane & 15, fh = lane >> 4;
+    const int n0 = wn * T::WTN + (fh & 1) * 16 + (fh >> 1) * 8;
 #pragma unroll
     for (int i = 0; i < T::FM; ++i) {
-        const int m = wm * T::WTM + i * 32 + frow;
-        if (m < rows_valid) {
-            uint16_t *crow = c_tile + (int64_t)m * ldc;
+        const int m = wm * T::WTM + i * 16 + frow;
+        uint16_t *crow = c_tile + (int64_t)m * ldc;
 #pragma unroll
-            for (int j = 0; j < T::FN; ++j)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int n = wn * T::WTN + j * 32 + 8 * b + 4 * fh;
-                    if (n < cols_valid) {
-                        u32x2_t p;
-                        p.x = pack2_bf16_rne(acc[j][i][4 * b + 0], acc[j][i][4 * b + 1]);
-                        p.y = pack2_bf16_rne(acc[j][i][4 * b + 2], acc[j][i][4 * b + 3]);
-                        *reinterpret_cast<u32x2_t *>(crow + n) = p;
-                    }
-                }
-        }
-    }
-}
-
-// The same result stored as whole row segments: a wavefront passes each 32-row block of its part of
-// the tile through LDS (rows padded by 16 B so that they spread over the banks) and reads it back
-// with consecutive lanes on consecutive 16-byte slots of a row, so a store instruction writes whole
-// 128-byte lines instead of 16 bytes in each of 32 rows. Written through the caches (system scope):
-// this is the epilogue for output that a copy engine reads while the kernel runs on, where partial
-// lines would each go to memory on their own. Needs ldc % 8 == 0 and a 16-byte aligned C; uses the
-// first 4 * 32 * (2 WTN + 16) bytes of the ring, which must be idle (tile_accumulate's final barrier)
-// and stay idle until a workgroup barrier after the call.
-template <class T>
-static __device__ __forceinline__ void tile_store_rows_through(const TileAcc<T> &ta, uint16_t *__restrict__ c_tile, int rows_valid,
-                                                               int cols_valid, int64_t ldc, unsigned char *smem)
-{
-    constexpr int SEG = T::WTN / 8;                 // 16-byte slots per row of the wavefront's part
-    constexpr int STRIDE = T::WTN * 2 + 16;         // bytes between rows in LDS
-    static_assert(T::NW * 32 * STRIDE <= T::LDS_BYTES, "staging area must fit the ring");
-    static_assert((32 * SEG) % 64 == 0, "whole wavefront instructions");
-    const f32x16_t (&acc)[T::FN][T::FM] = ta.acc;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave / T::WGN, wn = wave % T::WGN;
-    const int frow = lane & 31, fh = lane >> 5;
-    unsigned char *mine = smem + wave * (32 * STRIDE);
-#pragma unroll
-    for (int i = 0; i < T::FM; ++i) {
-#pragma unroll
-        for (int j = 0; j < T::FN; ++j)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                u32x2_t p;
-                p.x = pack2_bf16_rne(acc[j][i][4 * b + 0], acc[j][i][4 * b + 1]);
-                p.y = pack2_bf16_rne(acc[j][i][4 * b + 2], acc[j][i][4 * b + 3]);
-                *reinterpret_cast<u32x2_t *>(mine + frow * STRIDE + (j * 32 + 8 * b + 4 * fh) * 2) = p;
-            }
-        // same wavefront, LDS operations execute in order: no barrier between the two phases
-#pragma unroll
-        for (int it = 0; it < (32 * SEG) / 64; ++it) {
-            const int q = it * 64 + lane;
-            const int row = q / SEG, seg = q % SEG;
-            const u32x4_t v = *reinterpret_cast<const u32x4_t *>(mine + row * STRIDE + seg * 16);
-            const int m = wm * T::WTM + i * 32 + row;
-            const int n = wn * T::WTN + seg * 8;
+        for (int j = 0; j < T::FN; j += 2) {
+            const auto lo = __builtin_amdgcn_permlane16_swap(pack2_bf16_rne(acc[j][i][0], acc[j][i][1]),
+                                                             pack2_bf16_rne(acc[j + 1][i][0], acc[j + 1][i][1]), false, false);
+            const auto hi = __builtin_amdgcn_permlane16_swap(pack2_bf16_rne(acc[j][i][2], acc[j][i][3]),
+                                                             pack2_bf16_rne(acc[j + 1][i][2], acc[j + 1][i][3]), false, false);
+            const u32x4_t v = {lo[0], hi[0], lo[1], hi[1]};
+            const int n = n0 + j * 16;
             if (m < rows_valid && n < cols_valid) {
-                uint16_t *dst = c_tile + (int64_t)m * ldc + n;
-                if (n + 8 <= cols_valid)
-                    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(dst), "v"(v) : "memory");
-                else   // N is a multiple of 4: the last slot of a row may be half there
-                    __hip_atomic_store(reinterpret_cast<uint64_t *>(dst), (uint64_t)v.x | ((uint64_t)v.y << 32), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_SYSTEM);
+                if constexpr (THROUGH) asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(crow + n), "v"(v) : "memory");
+                else *reinterpret_cast<u32x4_t *>(crow + n) = v;
             }
         }
     }
@@ -510,10 +500,11 @@ __global__ __launch_bounds__(T::THREADS) void gemm_blocks_kernel(GemmLaunch a)
         const int rows_valid = min(T::BM, a.rows_per_block - rt * T::BM);
         const int col0 = tn * T::BN;
         const int cols_valid = min(T::BN, a.N - col0);
-        // (tile_accumulate ends with a barrier after the last LDS read, so the next tile may refill the ring)
         compute_tile<T>(a.A + row0 * a.lda, rows_valid, a.Wt + (int64_t)col0 * a.K, cols_valid,
                         a.C + row0 * a.ldc + col0, a.lda, a.K, a.ldc, a.K, smem);
+        __syncthreads();                   // everyone is done with the ring before the next tile refills it
     }
+    wait_vmem<0>();                        // no load may arrive in LDS that is not this workgroup's any more
 }
 
 // Tile order of the resident kernels. Row tiles are numbered in arrival order (R = arrival position x
@@ -707,13 +698,13 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
             s_ok = ok;
         }
         __syncthreads();                   // also orders the tile's loads after the flag read
-        const int x = s_walk.x, t = s_walk.t;
+        const int x = __builtin_amdgcn_readfirstlane(s_walk.x), t = __builtin_amdgcn_readfirstlane(s_walk.t);
         if (x < 0) break;
         if (s_ok) {
             int R, tn;
             lists.position(x, t, R, tn);
             const int rt = R % rt_per_chunk;
-            const int chunk = s_chunk;
+            const int chunk = __builtin_amdgcn_readfirstlane(s_chunk);
             const int64_t row0 = (int64_t)chunk * a.rows_per_block + (int64_t)rt * T::BM;
             const int rows_valid = min(T::BM, a.rows_per_block - rt * T::BM);
             const int col0 = tn * T::BN;
@@ -728,7 +719,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
             // the next ticket's round trip runs under the epilogue
             if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, total_of, drawn);
             if constexpr (STREAM_OUT) {
-                tile_store_rows_through<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc, smem);
+                tile_store<T, true>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
                 stored_chunk = chunk;
             } else {
                 tile_store<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
@@ -736,8 +727,8 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
         }
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused
     }
+    wait_vmem<0>();                        // no load may arrive in LDS that is not this workgroup's any more; stores are done
     if constexpr (STREAM_OUT) {
-        wait_vmem<0>();
         __syncthreads();
         count_stored();
     }
@@ -770,7 +761,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
             s_walk = w;
         }
         __syncthreads();
-        const int x = s_walk.x, t = s_walk.t;
+        const int x = __builtin_amdgcn_readfirstlane(s_walk.x), t = __builtin_amdgcn_readfirstlane(s_walk.t);
         if (x < 0) break;
         int tm, tn;
         lists.position(x, t, tm, tn);
@@ -815,6 +806,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
         if (ok) tile_store<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused
     }
+    wait_vmem<0>();                        // no load may arrive in LDS that is not this workgroup's any more
     leave_run(r.leave);
 }
 
@@ -852,7 +844,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
             s_ok = ok;
         }
         __syncthreads();                   // also orders the tile's loads after the flag reads
-        const int x = s_walk.x, t = s_walk.t;
+        const int x = __builtin_amdgcn_readfirstlane(s_walk.x), t = __builtin_amdgcn_readfirstlane(s_walk.t);
         if (x < 0) break;
         if (s_ok) {
             int R, tn;
@@ -872,6 +864,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
         }
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused
     }
+    wait_vmem<0>();                        // no load may arrive in LDS that is not this workgroup's any more
 }
 
 __global__ __launch_bounds__(64) void wait_ready_kernel(Gate gate, const int32_t *chunks, int n)
@@ -959,12 +952,6 @@ hipError_t launch_slice_source(const SliceLaunch &a, hipStream_t s)
 }
 
 // ------------------------------------------------------------------------------------------ host
-// The big tile keeps two stages of 64 k values. Four stages of 32 (TileCfg<256, 256, 2, 2, 4, 32>) take the
-// memory wait out of the loop but run 6-8 % slower: rows of 64 bytes double the cache lines each load
-// instruction touches, and every 64 k values pay two barriers instead of one.
-// Eight wavefronts (TileCfg<256, 256, 2, 4, 2> or <256, 256, 4, 2, 2>, two per SIMD, 128x64 each) give the
-// same bits 2-5 % slower: a second wavefront per SIMD hides nothing that matters here, and the smaller
-// wavefront tile reads half as much again from LDS per MFMA.
 typedef TileCfg<256, 256, 2, 2, 2> T256x256;
 typedef TileCfg<128, 128, 2, 2, 2> T128x128;       // two workgroups per CU: for launches that fill the machine
 typedef TileCfg<128, 128, 2, 2, 4> T128x128D;      // deep ring, one workgroup per CU: for launches that do not
