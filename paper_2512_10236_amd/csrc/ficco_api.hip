@@ -222,21 +222,13 @@ int ficco_run(ficco_plan_t *p, const void *A_src, void *A_dev, const void *W_dev
                 r.arrival = p->d_arrival;
                 r.n_chunks = n;
                 r.g.gate = gate;
-                r.ticket = p->d_ticket;
-                r.grid = grid;
                 const ListGeometry lg = resident_lists(p);
                 if (!lg.col_lists) return FICCO_ERR_ARG;
-                r.group = lg.group;
-                r.col_lists = lg.col_lists;
                 if (!dependent) { r.local_chunk_begin = 0; r.local_chunk_end = n; }
                 else if (p->local_shard >= 0) { r.local_chunk_begin = p->local_shard * c; r.local_chunk_end = (p->local_shard + 1) * c; }
                 else { r.local_chunk_begin = 0; r.local_chunk_end = 0; }
                 TileShape ts = tile_shape(p->tile);
-                for (int x = 0; x < kTicketLists; ++x) {
-                    r.ticket_base[x] = p->ticket_total[x];
-                    p->ticket_total[x] += resident_list_draws(resident_list_tiles((int64_t)n * ((p->m + ts.bm - 1) / ts.bm),
-                                                                                  (p->N + ts.bn - 1) / ts.bn, x, r.col_lists), r.grid, x);
-                }
+                book_tickets(p, r, lg, (int64_t)n * ((p->m + ts.bm - 1) / ts.bm), (p->N + ts.bn - 1) / ts.bn, grid);
                 HIP_TRY(launch_resident(p->tile, r, cs));
             }
             ++n_launches;

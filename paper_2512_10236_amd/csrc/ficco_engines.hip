@@ -304,21 +304,14 @@ int run_grouped(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, hi
         r.g.gate = gate;
         r.row_tiles = p->d_row_tiles;
         r.n_row_tiles = p->n_row_tiles;
-        r.ticket = p->d_ticket;
-        r.grid = p->resident_grid;
         r.gated = (dependent && do_copy) ? 1 : 0;
         TileShape ts = tile_shape(p->tile);
         const int64_t tn = (p->N + ts.bn - 1) / ts.bn;
         // ragged steps: a step brings about 1/c of the row tiles
-        const ListGeometry lg = pick_lists(p, ts, tn, p->n_row_tiles, std::max<int64_t>(1, p->n_row_tiles / std::max(p->c, 1)), r.grid / kTicketLists,
+        const ListGeometry lg = pick_lists(p, ts, tn, p->n_row_tiles, std::max<int64_t>(1, p->n_row_tiles / std::max(p->c, 1)), p->resident_grid / kTicketLists,
                                            p->M * p->K * 2, (int64_t)p->E * p->N * p->K * 2);
         if (!lg.col_lists) return FICCO_ERR_ARG;
-        r.group = lg.group;
-        r.col_lists = lg.col_lists;
-        for (int x = 0; x < kTicketLists; ++x) {
-            r.ticket_base[x] = p->ticket_total[x];
-            p->ticket_total[x] += resident_list_draws(resident_list_tiles(p->n_row_tiles, tn, x, r.col_lists), r.grid, x);
-        }
+        book_tickets(p, r, lg, p->n_row_tiles, tn, p->resident_grid);
         HIP_TRY(launch_grouped(p->tile, r, cs));
         ++n_launches;
     }
@@ -680,20 +673,12 @@ int run_engines(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, vo
                 r.arrival = p->d_arrival;
                 r.n_chunks = n;
                 r.g.gate = gate;
-                r.ticket = p->d_ticket;
-                r.grid = p->resident_grid;
                 const ListGeometry lg = resident_lists(p);
                 if (!lg.col_lists) return FICCO_ERR_ARG;
-                r.group = lg.group;
-                r.col_lists = lg.col_lists;
                 if (!dependent) { r.local_chunk_begin = 0; r.local_chunk_end = n; }
                 else if (p->local_shard >= 0) { r.local_chunk_begin = p->local_shard * c; r.local_chunk_end = (p->local_shard + 1) * c; }
                 TileShape ts = tile_shape(p->tile);
-                for (int x = 0; x < kTicketLists; ++x) {
-                    r.ticket_base[x] = p->ticket_total[x];
-                    p->ticket_total[x] += resident_list_draws(resident_list_tiles((int64_t)n * ((p->m + ts.bm - 1) / ts.bm),
-                                                                                  (p->N + ts.bn - 1) / ts.bn, x, r.col_lists), r.grid, x);
-                }
+                book_tickets(p, r, lg, (int64_t)n * ((p->m + ts.bm - 1) / ts.bm), (p->N + ts.bn - 1) / ts.bn, p->resident_grid);
                 if (timing) HIP_TRY(hipEventRecord(p->ev_gemm_b[0], cs));
                 HIP_TRY(launch_resident(p->tile, r, cs));
                 if (release_in_kernel) p->exit_total += (uint32_t)p->resident_grid;
@@ -749,22 +734,15 @@ int run_engines(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, vo
             r.arrival = p->d_arrival;
             r.n_chunks = n;
             r.g.gate = gate;
-            r.ticket = p->d_ticket;
-            r.grid = p->resident_grid;
             const ListGeometry lg = resident_lists(p);
             if (!lg.col_lists) return FICCO_ERR_ARG;
-            r.group = lg.group;
-            r.col_lists = lg.col_lists;
             r.local_chunk_begin = 0; r.local_chunk_end = n;                   // A is resident: nothing to wait for
             TileShape ts = tile_shape(p->tile);
             const int64_t rt = (p->m + ts.bm - 1) / ts.bm, tn = (p->N + ts.bn - 1) / ts.bn;
             r.done_count = p->d_done_count;
             r.done_sig = p->d_done_value;
             r.tiles_per_chunk = (int32_t)(rt * tn);
-            for (int x = 0; x < kTicketLists; ++x) {
-                r.ticket_base[x] = p->ticket_total[x];
-                p->ticket_total[x] += resident_list_draws(resident_list_tiles((int64_t)n * rt, tn, x, r.col_lists), r.grid, x);
-            }
+            book_tickets(p, r, lg, (int64_t)n * rt, tn, p->resident_grid);
             HIP_TRY(launch_resident(p->tile, r, cs));
             ++n_launches;
         }

@@ -519,16 +519,15 @@ __global__ __launch_bounds__(T::THREADS) void gemm_blocks_kernel(GemmLaunch a)
 // splits the lists by column block as well (ResidentLaunch::col_lists), so that an XCD works on
 // several row tiles of the step times a run of columns, as a launch over the step's pieces would.
 //
-// TileWalk hands a workgroup its next (list, tile) pair. The first tile of the first list is the
-// workgroup's rank among the workgroups that start there (no memory access); later tiles are drawn
-// from the list's counter. Before it turns to the other lists it reads their counters once, all
-// loads in flight together: on a list that is already used up it only leaves its one
-// past-the-end draw (an atomic whose result nobody waits for), and a list that the ranks of its own
-// workgroups cover completely is never drawn from at all. Counter traffic is what a short launch
-// pays at its start and end, since a draw goes to memory shared by all XCDs.
+// TileWalk hands a workgroup its next (list, tile) pair. The first `rounds` tiles of its home list are the workgroup's
+// by its rank among the workgroups that start there (no memory access; often that is all of them, see static_rounds);
+// later tiles are drawn from the list's counter. Before it turns to the other lists it reads their counters once, all
+// loads in flight together: on a list that is already used up it only leaves its one past-the-end draw (an atomic
+// whose result nobody waits for), and a list that the ranks of its own workgroups cover completely is never drawn from
+// at all. Counter traffic is what a launch pays at its end, since a draw goes to memory shared by all XCDs.
 struct TileWalk {
     int turn;        // lists visited so far; the current list is (home + turn) % kTicketLists
-    int first;       // the rank tile of the home list has not been handed out yet
+    int taken;       // tiles of the home list taken by rank so far
     int looked;      // the other lists' counters have been read
     int spent;       // bit k: list (home + k) % kTicketLists was already used up at that look
     int x, t;        // the result: list and tile in the list, x < 0 when there is nothing left
@@ -538,19 +537,19 @@ struct TileWalk {
 // start with one) and returns 1 with the raw counter value in `drawn`; the caller puts this before
 // work whose duration then hides the draw's round trip. Returns 0 when the next step is not a plain draw.
 template <class TotalFn>
-static __device__ __forceinline__ int tile_walk_predraw(const TileWalk &w, uint32_t *ticket, int grid, TotalFn total_of,
+static __device__ __forceinline__ int tile_walk_predraw(const TileWalk &w, uint32_t *ticket, int grid, int rounds, TotalFn total_of,
                                                         uint32_t &drawn)
 {
-    if (w.turn >= kTicketLists || w.first) return 0;
+    if (w.turn >= kTicketLists || (w.turn == 0 && w.taken < rounds)) return 0;
     const int y = (blockIdx.x + w.turn) % kTicketLists;
-    if (total_of(y) <= resident_list_homes(grid, y)) return 0;
+    if (total_of(y) <= rounds * resident_list_homes(grid, y)) return 0;
     if (w.turn > 0 && (!w.looked || ((w.spent >> w.turn) & 1))) return 0;
     drawn = __hip_atomic_fetch_add(ticket + y * kFlagStrideWords, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return 1;
 }
 
 template <class TotalFn>
-static __device__ __forceinline__ void tile_walk_next(TileWalk &w, uint32_t *ticket, const uint32_t *base, int grid,
+static __device__ __forceinline__ void tile_walk_next(TileWalk &w, uint32_t *ticket, const uint32_t *base, int grid, int rounds,
                                                       TotalFn total_of, int have_drawn = 0, uint32_t drawn = 0)
 {
     const int home = blockIdx.x % kTicketLists, rank = blockIdx.x / kTicketLists;
@@ -559,12 +558,15 @@ static __device__ __forceinline__ void tile_walk_next(TileWalk &w, uint32_t *tic
         const int y = (home + w.turn) % kTicketLists;
         const int total = total_of(y), homes = resident_list_homes(grid, y);
         uint32_t *ctr = ticket + y * kFlagStrideWords;
-        if (total <= homes) {
+        if (w.turn == 0 && w.taken < rounds) {
+            const int cand = rank + w.taken * homes;
+            ++w.taken;
+            if (cand < total) { w.x = y; w.t = cand; return; }
+            w.taken = rounds;                      // and none further on
+        }
+        if (total <= rounds * homes) {
             // the ranks of the workgroups that start on this list cover it: nobody draws from its counter
-            const bool mine = w.first && rank < total;
-            w.first = 0;
             ++w.turn;
-            if (mine) { w.x = y; w.t = rank; return; }
             continue;
         }
         if (w.turn > 0 && !w.looked) {
@@ -577,8 +579,8 @@ static __device__ __forceinline__ void tile_walk_next(TileWalk &w, uint32_t *tic
 #pragma unroll
             for (int k = 1; k < kTicketLists; ++k) {
                 const int yk = (home + k) % kTicketLists;
-                const int homes_k = resident_list_homes(grid, yk), total_k = total_of(yk);
-                if (total_k > homes_k && (int)(seen[k] - base[yk]) + homes_k >= total_k) spent |= 1 << k;
+                const int by_rank = rounds * resident_list_homes(grid, yk), total_k = total_of(yk);
+                if (total_k > by_rank && (int)(seen[k] - base[yk]) + by_rank >= total_k) spent |= 1 << k;
             }
             w.spent = spent;
             w.looked = 1;
@@ -588,16 +590,9 @@ static __device__ __forceinline__ void tile_walk_next(TileWalk &w, uint32_t *tic
             ++w.turn;
             continue;
         }
-        int cand;
-        if (w.first) {
-            w.first = 0;
-            if (rank >= total) continue;          // no tile at this rank: go on to the draws
-            cand = rank;
-        } else {
-            const uint32_t raw = have_drawn ? drawn : __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            have_drawn = 0;
-            cand = (int)(raw - base[y]) + homes;
-        }
+        const uint32_t raw = have_drawn ? drawn : __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        have_drawn = 0;
+        const int cand = (int)(raw - base[y]) + rounds * homes;
         if (cand < total) { w.x = y; w.t = cand; return; }
         ++w.turn;                                  // that was this workgroup's one draw past the end of list y
     }
@@ -662,7 +657,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
     const ListGrid lists(row_tiles, tiles_n, r.col_lists, r.group);
     auto total_of = [&](int x) { return lists.total(x); };
 
-    if (threadIdx.x == 0) s_walk = TileWalk{0, 1, 0, 0, -1, 0};
+    if (threadIdx.x == 0) s_walk = TileWalk{0, 0, 0, 0, -1, 0};
     int have_drawn = 0;
     uint32_t drawn = 0;
     // Output streaming: a copy engine reads a piece of C while the kernel runs on, so
@@ -684,7 +679,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
     for (;;) {
         if (threadIdx.x == 0) {
             TileWalk w = s_walk;
-            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, total_of, have_drawn, drawn);
+            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.rounds, total_of, have_drawn, drawn);
             have_drawn = 0;
             int ok = 1;
             if (w.x >= 0) {
@@ -717,7 +712,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
             else
                 tile_accumulate<T>(ta, a.A + row0 * a.lda, rows_valid, a.Wt + (int64_t)col0 * a.K, cols_valid, a.lda, a.K, a.K, smem);
             // the next ticket's round trip runs under the epilogue
-            if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, total_of, drawn);
+            if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.rounds, total_of, drawn);
             if constexpr (STREAM_OUT) {
                 tile_store<T, true>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
                 stored_chunk = chunk;
@@ -750,13 +745,13 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
     const ListGrid lists(row_tiles, tiles_n, r.col_lists, r.group);
     auto total_of = [&](int x) { return lists.total(x); };
 
-    if (threadIdx.x == 0) s_walk = TileWalk{0, 1, 0, 0, -1, 0};
+    if (threadIdx.x == 0) s_walk = TileWalk{0, 0, 0, 0, -1, 0};
     int have_drawn = 0;
     uint32_t drawn = 0;
     for (;;) {
         if (threadIdx.x == 0) {
             TileWalk w = s_walk;
-            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, total_of, have_drawn, drawn);
+            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.rounds, total_of, have_drawn, drawn);
             have_drawn = 0;
             s_walk = w;
         }
@@ -802,7 +797,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
                 sl = run_end;
             }
         }
-        if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, total_of, drawn);
+        if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.rounds, total_of, drawn);
         if (ok) tile_store<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused
     }
@@ -825,13 +820,13 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
     const ListGrid lists(r.n_row_tiles, tiles_n, r.col_lists, r.group);
     auto total_of = [&](int x) { return lists.total(x); };
 
-    if (threadIdx.x == 0) s_walk = TileWalk{0, 1, 0, 0, -1, 0};
+    if (threadIdx.x == 0) s_walk = TileWalk{0, 0, 0, 0, -1, 0};
     int have_drawn = 0;
     uint32_t drawn = 0;
     for (;;) {
         if (threadIdx.x == 0) {
             TileWalk w = s_walk;
-            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, total_of, have_drawn, drawn);
+            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.rounds, total_of, have_drawn, drawn);
             have_drawn = 0;
             int ok = 1;
             if (w.x >= 0 && r.gated) {
@@ -859,7 +854,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
             tile_zero(ta);
             tile_accumulate<T>(ta, a.A + row0 * a.lda, rows_valid, a.Wt + (expert * a.N + col0) * (int64_t)a.K, cols_valid,
                                a.lda, a.K, a.K, smem);
-            if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, total_of, drawn);
+            if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.rounds, total_of, drawn);
             tile_store<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
         }
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused

@@ -79,15 +79,35 @@ __host__ inline double tile_order_cost(int bm, int bn, int64_t tn, int64_t row_t
 // Workgroups of a resident launch whose first list is x (workgroup b starts on list b % kTicketLists).
 __host__ __device__ inline int resident_list_homes(int grid, int x) { return grid > x ? (grid - x + kTicketLists - 1) / kTicketLists : 0; }
 
-// Atomic draws one resident launch makes on list x's counter: a workgroup's first tile of its first list
-// is its rank there and needs no draw; if that covers the whole list nobody draws from it at all;
-// otherwise every later tile is drawn and every workgroup draws exactly one ticket past the end of the
-// list. The host advances its copy of each counter by this much per launch, so counters are never
-// reset.
-__host__ __device__ inline uint32_t resident_list_draws(int64_t list_tiles, int grid, int x)
+// A workgroup takes the first `rounds` of its home list's tiles by its rank there (rank, rank + homes, rank + 2 homes, ...)
+// without touching memory; later tiles are drawn from the list's counter, and when the home list is used up from the
+// other lists' (tile_walk_next). A draw is a round trip of 3-4 us to memory that all XCDs share, and a launch that
+// needs draws pays two or three of them at its end (two rounds of 32x256 tiles by rank instead of by draws: M 2048, K 1024,
+// N 4096 45.7 -> 34.6 us, M 9600, K 512, N 256 17.0 -> 13.7 us; nothing on launches of 200 us and more), so everything goes by rank where that is as good: the lists are even enough that no workgroup takes more tiles
+// than sharing all of them out evenly would ask for, and the launch is short enough that workgroups do not drift apart.
+// Long launches draw their last quarter, uneven ones everything after the first round.
+constexpr int kStaticRounds = 8;
+__host__ inline int static_rounds(int64_t row_tiles, int64_t tiles_n, int col_lists, int grid)
 {
-    const int64_t homes = resident_list_homes(grid, x);
-    return list_tiles > homes ? (uint32_t)(list_tiles - homes + grid) : 0u;
+    int64_t most = 1, total = 0;
+    for (int x = 0; x < kTicketLists; ++x) {
+        const int64_t t = resident_list_tiles(row_tiles, tiles_n, x, col_lists), h = resident_list_homes(grid, x);
+        total += t;
+        if (t > 0 && h == 0) return 1;                      // a list nobody starts on
+        if (h > 0 && (t + h - 1) / h > most) most = (t + h - 1) / h;
+    }
+    const int64_t even = (total + grid - 1) / grid;
+    if (most > even) return 1;
+    return (int)(even <= kStaticRounds ? even : even * 3 / 4);
+}
+
+// Atomic draws one resident launch makes on list x's counter: none if the ranks of its own workgroups cover the list;
+// otherwise every later tile is drawn and every workgroup draws exactly one ticket past the end of the list. The host
+// advances its copy of each counter by this much per launch, so counters are never reset.
+__host__ __device__ inline uint32_t resident_list_draws(int64_t list_tiles, int grid, int x, int rounds)
+{
+    const int64_t by_rank = (int64_t)rounds * resident_list_homes(grid, x);
+    return list_tiles > by_rank ? (uint32_t)(list_tiles - by_rank + grid) : 0u;
 }
 
 // How a kernel learns that piece `chunk` has landed:
@@ -142,7 +162,7 @@ struct ResidentLaunch {
     int32_t n_chunks;
     uint32_t *ticket;             // device, kTicketLists counters kFlagStrideWords apart, monotonically increasing across runs
     uint32_t ticket_base[8];      // value of each counter when this run starts
-    int32_t grid;
+    int32_t grid, rounds;         // workgroups; tiles each takes by rank (static_rounds)
     int32_t group;                // row tiles per group of a list's tile order (1..8)
     int32_t col_lists;            // column blocks the lists are split into (1, 2, 4 or 8; see resident_list_tiles)
     int32_t local_chunk_begin, local_chunk_end;   // chunk ids that need no flag (already resident), or empty
@@ -165,7 +185,7 @@ struct Resident2DLaunch {
     const int32_t *k0;            // device, slices + 1 entries: first column of each slice, then K (multiples of the k-tile)
     uint32_t *ticket;
     uint32_t ticket_base[8];
-    int32_t grid;
+    int32_t grid, rounds;
     int32_t gated;                // 0: operands resident, no waiting
     int32_t group, col_lists;     // tile order, as in ResidentLaunch
     RunExit leave;
@@ -197,7 +217,7 @@ struct GroupedLaunch {
     int32_t n_row_tiles;
     uint32_t *ticket;
     uint32_t ticket_base[8];
-    int32_t grid;
+    int32_t grid, rounds;
     int32_t gated;
     int32_t group, col_lists;     // tile order, as in ResidentLaunch
 };

@@ -193,6 +193,20 @@ GemmLaunch make_launch(const ficco_plan_t *p, const Group &g, const void *A_dev,
 ListGeometry pick_lists(const ficco_plan_t *p, const TileShape &ts, int64_t tn, int64_t row_tiles, int64_t S, int64_t slots,
                         int64_t a_bytes, int64_t w_bytes);
 ListGeometry resident_lists(const ficco_plan_t *p);
+// Fills the tile order and ticket fields of a resident launch over row_tiles x tn tiles and books its draws.
+template <class Launch>
+inline void book_tickets(ficco_plan_t *p, Launch &r, const ListGeometry &lg, int64_t row_tiles, int64_t tn, int grid)
+{
+    r.ticket = p->d_ticket;
+    r.grid = grid;
+    r.group = lg.group;
+    r.col_lists = lg.col_lists;
+    r.rounds = static_rounds(row_tiles, tn, lg.col_lists, grid);
+    for (int x = 0; x < kTicketLists; ++x) {
+        r.ticket_base[x] = p->ticket_total[x];
+        p->ticket_total[x] += resident_list_draws(resident_list_tiles(row_tiles, tn, x, lg.col_lists), grid, x, r.rounds);
+    }
+}
 int launch_2d(ficco_plan_t *p, const Gate &gate, bool gated, int grid, const void *A_dev, void *C_dev, hipStream_t cs,
               uint64_t release_addr = 0);
 

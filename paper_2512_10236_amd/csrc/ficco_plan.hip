@@ -420,20 +420,13 @@ int launch_2d(ficco_plan_t *p, const Gate &gate, bool gated, int grid, const voi
     r.shards = p->G;
     r.rows_per_shard = (int32_t)(p->M / p->G);
     r.k0 = p->d_slice_k0;
-    r.ticket = p->d_ticket;
-    r.grid = grid;
     r.gated = gated ? 1 : 0;
     TileShape ts = tile_shape(p->tile);
     const int64_t row_tiles = (p->M + ts.bm - 1) / ts.bm, tn = (p->N + ts.bn - 1) / ts.bn;
     // column pieces: every tile can start with the first step, so any group height goes
     const ListGeometry lg = pick_lists(p, ts, tn, row_tiles, row_tiles, grid / kTicketLists, p->M * p->K * 2, p->N * p->K * 2);
     if (!lg.col_lists) return FICCO_ERR_ARG;
-    r.group = lg.group;
-    r.col_lists = lg.col_lists;
-    for (int x = 0; x < kTicketLists; ++x) {
-        r.ticket_base[x] = p->ticket_total[x];
-        p->ticket_total[x] += resident_list_draws(resident_list_tiles(row_tiles, tn, x, r.col_lists), grid, x);
-    }
+    book_tickets(p, r, lg, row_tiles, tn, grid);
     HIP_TRY(launch_resident2d(p->tile, r, cs));
     if (release_addr) p->exit_total += (uint32_t)grid;      // counted only once the workgroups are on their way
     return FICCO_OK;
