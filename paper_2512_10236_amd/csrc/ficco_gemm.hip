@@ -16,66 +16,11 @@
 // instruction, whatever the tile shape or row block, which makes results bit-identical across
 // schedules.
 #include "ficco_internal.h"
+#include "ficco_mfma.h"
 #include <stdlib.h>
-#include <type_traits>
-#include <utility>
 #include <algorithm>
 
 namespace ficco {
-
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-// two fp32 -> two bf16, round to nearest even, in one instruction (v_cvt_pk_bf16_f32)
-static __device__ __forceinline__ uint32_t pack2_bf16_rne(float lo, float hi)
-{
-    const bf16x2_t v = {(__bf16)lo, (__bf16)hi};
-    return __builtin_bit_cast(uint32_t, v);
-}
-
-template <int... I, class Fn>
-static __device__ __forceinline__ void static_for_(std::integer_sequence<int, I...>, Fn &&f) { (f(std::integral_constant<int, I>{}), ...); }
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose index is a constant in every turn
-template <int N, class Fn>
-static __device__ __forceinline__ void static_for(Fn &&f) { static_for_(std::make_integer_sequence<int, N>{}, f); }
-
-// 64 lanes x 16 B from global memory straight into 1 KiB of LDS at the wave-uniform byte address in M0 (lane l lands
-// at M0 + 16 l). The global address is a wave-uniform 64-bit base (scalar registers) plus a per-lane 32-bit byte
-// offset, so that stepping along k costs scalar additions only and a load needs one vector register. Issued through
-// inline assembly so that the waits are placed by hand (s_waitcnt vmcnt) and not widened by the compiler. M0 is
-// written by an instruction of its own (set_lds_target), which the k loop places one MFMA ahead of the load: the wait
-// state the hardware wants between the two is then an MFMA instead of a no-op, and no slot between two MFMAs has to
-// take more than two instructions. Between a set_lds_target and its load there is no other use of M0 (the kernels
-// use nothing that needs it: no GDS, no messages, no indirect registers).
-//
-// The base must be in scalar registers well before the load: a scalar register that a vector instruction has written
-// (v_readfirstlane, which is what the compiler makes of an address it cannot prove uniform) may be read by a memory
-// instruction only 5 wait states later, and the compiler, which sees to that for its own instructions, does not look
-// into inline assembly. scalar_base() is the way in: it makes the two halves uniform, waits, and returns an opaque
-// scalar, on which everything after it is scalar arithmetic. (tests/test_build_resources.py checks the assembly.)
-static __device__ __forceinline__ const uint16_t *scalar_base(const uint16_t *p)
-{
-    const uint64_t b = (uint64_t)p;
-    uint64_t s = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
-    asm volatile("s_nop 4" : "+s"(s));
-    return (const uint16_t *)s;
-}
-static __device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }
-template <int IMM>
-static __device__ __forceinline__ void set_lds_target(uint32_t lds_base)
-{
-    asm volatile("s_add_i32 m0, %0, %1" ::"s"(lds_base), "n"(IMM) : "m0", "scc");
-}
-static __device__ __forceinline__ void load_to_lds_16(const void *base, uint32_t lane_off)
-{
-    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base) : "memory");
-}
-template <int N>
-static __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-static __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // A workgroup tile and the schedule of its k loop. The loop's unit is the slot: one v_mfma_f32_16x16x32_bf16 and what
 // is issued behind it. A turn of TT slots multiplies one k-tile (a stage of 64 k values, two halves of 32); see
@@ -877,10 +822,38 @@ __global__ __launch_bounds__(64) void release_signal_kernel(int64_t *value)
     if (threadIdx.x == 0) __hip_atomic_store(value, (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// W[K,N] -> Wt[N,K] through a 64x64 LDS tile (padded), 256 threads.
+// W[K,N] -> Wt[N,K], one wavefront per 64x64 tile, for a 16-byte aligned W, K % 64 == 0 and N % 8 == 0. A lane turns an
+// 8x8 block in its registers (eight 16-byte loads, 32 byte permutes, eight 16-byte stores); lane l has k group l % 8 and
+// column group l / 8, so that a load instruction reads, and a store instruction writes, whole 128-byte lines.
+// Streaming work, bound by memory. The first workgroup also clears `clear_words` words at `clear` for the caller.
 __global__ __launch_bounds__(256) void pack_weight_kernel(const uint16_t *__restrict__ W, uint16_t *__restrict__ Wt,
-                                                          int64_t K, int64_t N)
+                                                          int64_t K, int64_t N, uint32_t *clear, int clear_words)
 {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && (int)threadIdx.x < clear_words) clear[threadIdx.x] = 0u;
+    const int lane = threadIdx.x & 63;
+    const int64_t k0 = ((int64_t)blockIdx.y * 4 + (threadIdx.x >> 6)) * 64 + (lane & 7) * 8, n0 = (int64_t)blockIdx.x * 64 + (lane >> 3) * 8;
+    if (k0 >= K || n0 >= N) return;
+    u32x4_t r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = *reinterpret_cast<const u32x4_t *>(W + (k0 + i) * N + n0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        u32x4_t even, odd;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            even[i] = __builtin_amdgcn_perm(r[2 * i + 1][c], r[2 * i][c], 0x05040100u);
+            odd[i] = __builtin_amdgcn_perm(r[2 * i + 1][c], r[2 * i][c], 0x07060302u);
+        }
+        *reinterpret_cast<u32x4_t *>(Wt + (n0 + 2 * c) * K + k0) = even;
+        *reinterpret_cast<u32x4_t *>(Wt + (n0 + 2 * c + 1) * K + k0) = odd;
+    }
+}
+
+// The same for any W, 2 bytes at a time through a 64x64 LDS tile (padded), 256 threads.
+__global__ __launch_bounds__(256) void pack_weight_unaligned_kernel(const uint16_t *__restrict__ W, uint16_t *__restrict__ Wt,
+                                                                    int64_t K, int64_t N, uint32_t *clear, int clear_words)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0 && (int)threadIdx.x < clear_words) clear[threadIdx.x] = 0u;
     __shared__ uint16_t t[64][66];
     const int64_t k0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
     for (int e = threadIdx.x; e < 64 * 64; e += 256) {
@@ -1156,10 +1129,14 @@ hipError_t launch_release_signal(uint64_t value_addr, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_pack_weight(const uint16_t *W, uint16_t *Wt, int64_t K, int64_t N, hipStream_t s)
+hipError_t launch_pack_weight(const uint16_t *W, uint16_t *Wt, int64_t K, int64_t N, hipStream_t s, uint32_t *clear, int clear_words)
 {
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((K + 63) / 64));
-    hipLaunchKernelGGL(pack_weight_kernel, grid, dim3(256), 0, s, W, Wt, K, N);
+    if (clear_words < 0 || clear_words > 256) return hipErrorInvalidValue;
+    const unsigned tn = (unsigned)((N + 63) / 64);
+    if ((uintptr_t)W % 16 == 0 && (uintptr_t)Wt % 16 == 0 && K % 64 == 0 && N % 8 == 0)
+        hipLaunchKernelGGL(pack_weight_kernel, dim3(tn, (unsigned)((K + 255) / 256)), dim3(256), 0, s, W, Wt, K, N, clear, clear_words);
+    else
+        hipLaunchKernelGGL(pack_weight_unaligned_kernel, dim3(tn, (unsigned)((K + 63) / 64)), dim3(256), 0, s, W, Wt, K, N, clear, clear_words);
     return hipGetLastError();
 }
 

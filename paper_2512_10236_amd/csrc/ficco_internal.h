@@ -252,7 +252,17 @@ struct SliceLaunch {
     const uint64_t *done_sig;     // device, per piece id: address of the signal's value word
 };
 hipError_t launch_slice_source(const SliceLaunch &a, hipStream_t s);
-hipError_t launch_pack_weight(const uint16_t *W, uint16_t *Wt, int64_t K, int64_t N, hipStream_t s);
+// C = A * W with W row-major, in one launch of tiles of 16 * row_blocks (1, 2 or 4) rows x 64 columns. W 16-byte aligned,
+// C must not overlap W (it is read until the end).
+struct DirectLaunch {
+    const uint16_t *A, *W;
+    uint16_t *C;
+    int32_t M, N, K;
+    int32_t tiles_m, tiles_n;     // set by the launcher
+};
+hipError_t launch_direct(int row_blocks, const DirectLaunch &a, hipStream_t s);
+// W[K,N] -> Wt[N,K]; also clears up to 256 words at `clear`
+hipError_t launch_pack_weight(const uint16_t *W, uint16_t *Wt, int64_t K, int64_t N, hipStream_t s, uint32_t *clear = nullptr, int clear_words = 0);
 int resident_grid_size(int tile, int device);
 
 }  // namespace ficco

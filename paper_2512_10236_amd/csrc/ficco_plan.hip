@@ -120,7 +120,7 @@ LaunchShape launch_shape(const ficco_plan_t *p, const Group &g)
 // tiles re-fitted to multi-round resident launches after the tile order changed: 128x256 and 256x128
 // run at 0.87-0.95 of the 256x256 tile's throughput there, 128x128 at 0.84-0.88); padded (masked)
 // rows and columns are paid in full.
-int choose_tile(const ficco_plan_t *p, int cus)
+int choose_tile(const ficco_plan_t *p, int cus, double *step_us)
 {
     static const struct { int id; double base, slope; int occ; } cand[] = {
         {TILE_256x256, 1.40, 0.45, 1}, {TILE_128x256, 0.80, 0.25, 1}, {TILE_256x128, 0.80, 0.27, 1},
@@ -154,6 +154,7 @@ int choose_tile(const ficco_plan_t *p, int cus)
         }
         if (total < best * 0.999) { best = total; best_id = cd.id; }
     }
+    if (step_us) *step_us = best;
     return best_id;
 }
 

@@ -1,5 +1,5 @@
-// ficco_gemm_static: the resident GEMM over operands that are already in place, for callers that
-// cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses that
+// ficco_gemm_static: the GEMM over operands that are already in place (small products straight from the row-major
+// weight, others by the resident kernel), for callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses that
 // forbid hipMalloc). Everything the resident kernel needs beyond its inputs and outputs - the ticket
 // counters of its tile lists, the status word of its bounded waits, the one-entry arrival table and
 // the packed copy of the weight - lives in one file-scope device array instead of plan-owned
@@ -35,11 +35,28 @@ int scratch_of(int dev, unsigned char **out)
     return FICCO_OK;
 }
 
-// The array keeps the last call's contents: counters, status and the arrival entry start every call from
-// zero. A kernel rather than a memset, so that a caller may capture the call into a graph.
-__global__ __launch_bounds__(256) void static_clear_kernel(uint32_t *head)
+// Which way a call goes: 0 = pack the weight, then the resident GEMM; else one launch of the direct kernel on tiles of
+// 16 * row_blocks rows x 64 columns. The direct kernel needs no packed weight but fetches every operand row once per
+// narrow tile, so it wins where a launch is a round or two of its tiles and loses where the resident kernel's big tiles
+// fill the chip. Estimates in us, from timings over M 1-8192, K 64-8192, N 8-4096: a stage of 128 k values takes 0.25 /
+// 0.31 / 0.55 us with 1 / 2 / 4 row blocks (a CU draws about 80 GB/s from L2 and beyond), a round starts in 1.5 us; the
+// packed way takes choose_tile's steps and 8 us for the packing launch. Measured on either side, direct against packed:
+// M 64, K 4096, N 768 9.7 : 37.6; M 512, K 4096, N 1024 12.7 : 33.8; M 1024, K 2048, N 2048 (two rounds) 20.0 : 24.9;
+// M 2048, K 4096, N 1024 41.7 : 37.2; M 4096, K 1024, N 1024 26.7 : 20.6. A weight that is not 16-byte aligned, or that
+// the result overwrites, is always packed first.
+int direct_row_blocks(int64_t M, int64_t K, int64_t N, const void *W, const void *C, int cus, double packed_step_us)
 {
-    if (threadIdx.x < kHeadWordsCleared) head[threadIdx.x] = 0u;
+    const uintptr_t w0 = (uintptr_t)W, c0 = (uintptr_t)C;
+    if (w0 % 16 || (c0 < w0 + (uintptr_t)(2 * K * N) && w0 < c0 + (uintptr_t)(2 * M * N))) return 0;
+    static const struct { int row_blocks; double stage; } cand[] = {{1, 0.25}, {2, 0.31}, {4, 0.55}};
+    double best = 0.95 * (8.0 + packed_step_us * (double)(K / kBK));
+    int best_id = 0;
+    for (auto &cd : cand) {
+        const int64_t tiles = ((M + 16 * cd.row_blocks - 1) / (16 * cd.row_blocks)) * ((N + 63) / 64);
+        const double t = (double)((tiles + cus - 1) / cus) * (1.5 + cd.stage * (double)((K + 127) / 128)) + 2.0;
+        if (t < best) { best = t; best_id = cd.row_blocks; }
+    }
+    return best_id;
 }
 
 }  // namespace
@@ -65,7 +82,6 @@ extern "C" int ficco_gemm_static(int64_t M, int64_t K, int64_t N, const void *A_
     uint32_t *head = reinterpret_cast<uint32_t *>(base);
     uint16_t *wt = reinterpret_cast<uint16_t *>(base + kHeadBytes);
     hipStream_t s = (hipStream_t)stream;
-
     // the shape as a one-piece resident plan (host-side bookkeeping only): same tile choice and tile order
     // as ficco_run gives such a plan, hence the same kernel
     ficco_plan_t shape;
@@ -75,7 +91,18 @@ extern "C" int ficco_gemm_static(int64_t M, int64_t K, int64_t N, const void *A_
     if ((rc = build_lists(&shape))) return rc;
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    shape.tile = choose_tile(&shape, cus);
+    double step_us = 0;
+    shape.tile = choose_tile(&shape, cus, &step_us);
+    const int row_blocks = direct_row_blocks(M, K, N, W_dev, C_dev, cus, step_us);
+    if (row_blocks) {
+        DirectLaunch d{};
+        d.A = (const uint16_t *)A_dev;
+        d.W = (const uint16_t *)W_dev;
+        d.C = (uint16_t *)C_dev;
+        d.M = (int32_t)M; d.N = (int32_t)N; d.K = (int32_t)K;
+        HIP_TRY(launch_direct(row_blocks, d, s));
+        return FICCO_OK;
+    }
     const TileShape ts = tile_shape(shape.tile);
     if (ts.bm == 0) return FICCO_ERR_ARG;
     const int64_t row_tiles = (M + ts.bm - 1) / ts.bm, tn = (N + ts.bn - 1) / ts.bn;
@@ -88,9 +115,9 @@ extern "C" int ficco_gemm_static(int64_t M, int64_t K, int64_t N, const void *A_
     int khz = 100000;
     (void)hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev);
 
-    hipLaunchKernelGGL(static_clear_kernel, dim3(1), dim3(256), 0, s, head);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(launch_pack_weight((const uint16_t *)W_dev, wt, K, N, s));
+    // The array keeps the last call's contents: counters, status and the arrival entry start every call from zero, which
+    // the packing kernel sees to (no memset, so that a caller may capture the call into a graph).
+    HIP_TRY(launch_pack_weight((const uint16_t *)W_dev, wt, K, N, s, head, kHeadWordsCleared));
 
     ResidentLaunch r{};
     r.g.A = (const uint16_t *)A_dev;
