@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libficco.so")
 SOURCES = ["ficco_gemm.hip", "ficco_reduce.hip", "ficco_plan.hip", "ficco_engines.hip", "ficco_api.hip", "ficco_static.hip", "ficco_direct.hip"]
-HEADERS = ["ficco_internal.h", "ficco_mfma.h", "ficco_plan.h", os.path.join("..", "..", "include", "ficco.h")]
+HEADERS = ["ficco_internal.h", "ficco_gate.h", "ficco_mfma.h", "ficco_plan.h", os.path.join("..", "..", "include", "ficco.h")]
 
 # packed fp32 instructions are switched off for all device code (some of their forms have given wrong results on this hardware)
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",

@@ -1,0 +1,72 @@
+// Device side of a Gate (ficco_internal.h): how kernels wait for pieces. Not installed.
+#pragma once
+#include "ficco_internal.h"
+
+namespace ficco {
+
+// Bounded wait of one thread until a piece is ready (see Gate). Reads at system scope (past the
+// caches): the writer is a copy engine. Returns 0 when the limit expires or another workgroup has
+// already given up; the caller then skips its work, so every wave still reaches its exit.
+static __device__ __forceinline__ int wait_ready(const Gate &g, int chunk)
+{
+    const uint64_t t0 = wall_clock64();
+    const uint32_t *f = g.flags + (size_t)chunk * kFlagStrideWords;
+    const int64_t *sv = g.sig_value ? reinterpret_cast<const int64_t *>(g.sig_value[chunk]) : nullptr;
+    for (;;) {
+        if (sv) {
+            if (__hip_atomic_load(sv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) <= 0) return 1;
+        } else {
+            if (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == g.epoch) return 1;
+        }
+        if (__hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) return 0;
+        if (wall_clock64() - t0 > g.spin_limit_ticks) {
+            __hip_atomic_store(g.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(g.status_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            return 0;
+        }
+        __builtin_amdgcn_s_sleep(8);
+    }
+}
+
+// One look at a piece, without waiting: has it landed?
+static __device__ __forceinline__ int peek_ready(const Gate &g, int chunk)
+{
+    if (g.sig_value) return __hip_atomic_load(reinterpret_cast<const int64_t *>(g.sig_value[chunk]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) <= 0;
+    return __hip_atomic_load(g.flags + (size_t)chunk * kFlagStrideWords, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == g.epoch;
+}
+
+// The same for several pieces, piece_of(0) ... piece_of(n - 1), by one whole wavefront: lane l watches pieces l, l + 64,
+// ... A look at a signal is a round trip to host memory of 1-2 us, and a wave that looked at its pieces one after the
+// other paid one for each of them, landed or not; this way it pays one for 64. The limit counts from the last time
+// that a piece was seen to land. Returns the same value in every lane.
+template <class PieceFn>
+static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, PieceFn piece_of)
+{
+    const int lane = threadIdx.x & 63;
+    uint64_t t0 = wall_clock64();
+    for (int base = 0; base < n; base += 64) {
+        int waiting = base + lane < n;
+        const int piece = piece_of(waiting ? base + lane : base);
+        for (;;) {
+            const int landed = waiting && peek_ready(g, piece);
+            if (landed) waiting = 0;
+            if (!__any(waiting)) break;
+            if (__any(landed)) t0 = wall_clock64();
+            int give_up = 0;
+            if (lane == 0) {
+                if (__hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) {
+                    give_up = 1;
+                } else if (wall_clock64() - t0 > g.spin_limit_ticks) {
+                    __hip_atomic_store(g.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    __hip_atomic_store(g.status_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    give_up = 1;
+                }
+            }
+            if (__any(give_up)) return 0;
+            __builtin_amdgcn_s_sleep(8);
+        }
+    }
+    return 1;
+}
+
+}  // namespace ficco

@@ -16,6 +16,7 @@
 // instruction, whatever the tile shape or row block, which makes results bit-identical across
 // schedules.
 #include "ficco_internal.h"
+#include "ficco_gate.h"
 #include "ficco_mfma.h"
 #include <stdlib.h>
 #include <algorithm>
@@ -366,37 +367,6 @@ static __device__ __forceinline__ void compute_tile(const uint16_t *__restrict__
     tile_store<T>(ta, c_tile, rows_valid, cols_valid, ldc);
 }
 
-// Bounded wait of one thread until a piece is ready (see Gate). Reads at system scope (past the
-// caches): the writer is a copy engine. Returns 0 when the limit expires or another workgroup has
-// already given up; the caller then skips its work, so every wave still reaches its exit.
-static __device__ __forceinline__ int wait_ready(const Gate &g, int chunk)
-{
-    const uint64_t t0 = wall_clock64();
-    const uint32_t *f = g.flags + (size_t)chunk * kFlagStrideWords;
-    const int64_t *sv = g.sig_value ? reinterpret_cast<const int64_t *>(g.sig_value[chunk]) : nullptr;
-    for (;;) {
-        if (sv) {
-            if (__hip_atomic_load(sv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) <= 0) return 1;
-        } else {
-            if (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == g.epoch) return 1;
-        }
-        if (__hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) return 0;
-        if (wall_clock64() - t0 > g.spin_limit_ticks) {
-            __hip_atomic_store(g.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            __hip_atomic_store(g.status_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            return 0;
-        }
-        __builtin_amdgcn_s_sleep(8);
-    }
-}
-
-// One look at a piece, without waiting: has it landed?
-static __device__ __forceinline__ int peek_ready(const Gate &g, int chunk)
-{
-    if (g.sig_value) return __hip_atomic_load(reinterpret_cast<const int64_t *>(g.sig_value[chunk]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) <= 0;
-    return __hip_atomic_load(g.flags + (size_t)chunk * kFlagStrideWords, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == g.epoch;
-}
-
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2). The tiles are cut
 // into 8 runs of consecutive logical ids, one per XCD, and the tile grid is walked in groups of
 // group_m row tiles, so that one XCD works on few A row tiles and W column tiles at a time. A launch
@@ -417,10 +387,9 @@ __global__ __launch_bounds__(T::THREADS) void gemm_blocks_kernel(GemmLaunch a)
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     if (a.n_wait > 0) {
         __shared__ int s_go;
-        if (threadIdx.x == 0) {
-            int ok = 1;
-            for (int i = 0; i < a.n_wait && ok; ++i) ok = wait_ready(a.gate, a.wait_chunks[i]);
-            s_go = ok;
+        if (threadIdx.x < 64) {
+            const int ok = wait_ready_all(a.gate, a.n_wait, [&](int i) { return a.wait_chunks[i]; });
+            if (threadIdx.x == 0) s_go = ok;
         }
         __syncthreads();                   // also orders the tile's loads after the flag reads
         if (!s_go) return;
@@ -719,16 +688,15 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
         for (int sl = 0; sl < r.slices && ok;) {
             int run_end = r.slices;
             if (r.gated) {
-                if (threadIdx.x == 0) {
-                    int o = 1;
-                    for (int j = j0; j <= j1 && o; ++j) o = wait_ready(a.gate, sl * r.shards + j);
-                    int e = sl + 1;
-                    for (; o && e < r.slices; ++e) {
-                        int landed = 1;
-                        for (int j = j0; j <= j1 && landed; ++j) landed = peek_ready(a.gate, e * r.shards + j);
-                        if (!landed) break;
-                    }
-                    s_ok = o ? e : 0;      // 0: gave up; else the slice after the run
+                if (threadIdx.x < 64) {
+                    const int o = wait_ready_all(a.gate, j1 - j0 + 1, [&](int i) { return sl * r.shards + j0 + i; });
+                    // one look at up to 64 following slices, a lane each
+                    const int mine = sl + 1 + (int)threadIdx.x;
+                    int landed = o && mine < r.slices;
+                    for (int j = j0; j <= j1; ++j) landed = landed && peek_ready(a.gate, mine * r.shards + j);
+                    const uint64_t not_landed = ~__ballot(landed);
+                    const int run = not_landed ? __builtin_ctzll(not_landed) : 64;
+                    if (threadIdx.x == 0) s_ok = o ? sl + 1 + run : 0;      // 0: gave up; else the slice after the run
                 }
                 __syncthreads();           // also orders the run's loads after the flag reads
                 run_end = s_ok;
@@ -769,19 +737,24 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
     int have_drawn = 0;
     uint32_t drawn = 0;
     for (;;) {
-        if (threadIdx.x == 0) {
-            TileWalk w = s_walk;
-            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.rounds, total_of, have_drawn, drawn);
-            have_drawn = 0;
-            int ok = 1;
-            if (w.x >= 0 && r.gated) {
-                int R, tn;
-                lists.position(w.x, w.t, R, tn);
-                const int32_t *rt = r.row_tiles + (size_t)R * kRowTileWords;
-                for (int pc = rt[3]; pc <= rt[4] && ok; ++pc) ok = wait_ready(a.gate, pc);
+        if (threadIdx.x < 64) {
+            TileWalk w{};
+            if (threadIdx.x == 0) {
+                w = s_walk;
+                tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.rounds, total_of, have_drawn, drawn);
+                have_drawn = 0;
+                s_walk = w;
             }
-            s_walk = w;
-            s_ok = ok;
+            const int wx = __builtin_amdgcn_readfirstlane(w.x), wt = __builtin_amdgcn_readfirstlane(w.t);
+            int ok = 1;
+            if (wx >= 0 && r.gated) {
+                int R, tn;
+                lists.position(wx, wt, R, tn);
+                const int32_t *rt = r.row_tiles + (size_t)R * kRowTileWords;
+                const int first = rt[3];
+                ok = wait_ready_all(a.gate, rt[4] - first + 1, [&](int i) { return first + i; });
+            }
+            if (threadIdx.x == 0) s_ok = ok;
         }
         __syncthreads();                   // also orders the tile's loads after the flag reads
         const int x = __builtin_amdgcn_readfirstlane(s_walk.x), t = __builtin_amdgcn_readfirstlane(s_walk.t);
@@ -809,9 +782,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
 
 __global__ __launch_bounds__(64) void wait_ready_kernel(Gate gate, const int32_t *chunks, int n)
 {
-    if (threadIdx.x == 0)
-        for (int i = 0; i < n; ++i)
-            if (!wait_ready(gate, chunks[i])) break;
+    (void)wait_ready_all(gate, n, [&](int i) { return chunks[i]; });
 }
 
 // Nothing is published through the signal: what it orders is that the kernels before this one on the

@@ -10,7 +10,7 @@
 // kernel is built for HBM: 16-byte coalesced loads, every peer's vector in flight before the first
 // add, four vectors per thread, workgroups striding over tiles so that the whole machine stays busy
 // on whichever pieces have arrived.
-#include "ficco_internal.h"
+#include "ficco_gate.h"
 
 namespace ficco {
 
@@ -24,28 +24,6 @@ static __device__ __forceinline__ uint32_t pack2_rne(float lo, float hi)
     if ((a & 0x7FFFFFFFu) > 0x7F800000u) ra = (a >> 16) | 0x0040u;
     if ((b & 0x7FFFFFFFu) > 0x7F800000u) rb = (b >> 16) | 0x0040u;
     return (ra & 0xFFFFu) | (rb << 16);
-}
-
-// same bounded wait as the GEMM kernels use (one thread; see Gate)
-static __device__ __forceinline__ int piece_ready(const Gate &g, int chunk)
-{
-    const uint64_t t0 = wall_clock64();
-    const uint32_t *f = g.flags + (size_t)chunk * kFlagStrideWords;
-    const int64_t *sv = g.sig_value ? reinterpret_cast<const int64_t *>(g.sig_value[chunk]) : nullptr;
-    for (;;) {
-        if (sv) {
-            if (__hip_atomic_load(sv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) <= 0) return 1;
-        } else {
-            if (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == g.epoch) return 1;
-        }
-        if (__hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) return 0;
-        if (wall_clock64() - t0 > g.spin_limit_ticks) {
-            __hip_atomic_store(g.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            __hip_atomic_store(g.status_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            return 0;
-        }
-        __builtin_amdgcn_s_sleep(8);
-    }
 }
 
 constexpr int kVecPerThread = 4;                       // 16-byte vectors per thread and tile
@@ -65,7 +43,7 @@ __global__ __launch_bounds__(256) void rs_reduce_kernel(ReduceLaunch r)
     for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
         const int s = t / tiles_per_piece, tt = t % tiles_per_piece;
         if (r.gated) {
-            if (threadIdx.x == 0) {
+            if (threadIdx.x < 64) {
                 // The first tile of a piece watches the G-1 transfers (their signals live in host memory:
                 // thousands of workgroups polling them would swamp the host link). It then raises the
                 // piece's word in device memory - the flag slot of the receiver's own piece, which no
@@ -78,19 +56,22 @@ __global__ __launch_bounds__(256) void rs_reduce_kernel(ReduceLaunch r)
                 uint32_t *word = const_cast<uint32_t *>(r.gate.flags) + (size_t)mine * kFlagStrideWords;
                 int ok = 1, watch = tt == 0;
                 if (!watch) {
-                    const uint64_t t0 = wall_clock64();
-                    while (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != r.gate.epoch) {
-                        if (__hip_atomic_load(r.gate.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) { ok = 0; break; }
-                        if (wall_clock64() - t0 > r.gate.spin_limit_ticks / 4) { watch = 1; break; }
-                        __builtin_amdgcn_s_sleep(8);
+                    if (threadIdx.x == 0) {
+                        const uint64_t t0 = wall_clock64();
+                        while (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != r.gate.epoch) {
+                            if (__hip_atomic_load(r.gate.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) { ok = 0; break; }
+                            if (wall_clock64() - t0 > r.gate.spin_limit_ticks / 4) { watch = 1; break; }
+                            __builtin_amdgcn_s_sleep(8);
+                        }
                     }
+                    ok = __builtin_amdgcn_readfirstlane(ok);
+                    watch = __builtin_amdgcn_readfirstlane(watch);
                 }
                 if (watch && ok) {
-                    for (int p = 0; p < r.G && ok; ++p)
-                        if (p != r.block) ok = piece_ready(r.gate, p * r.pieces + s);
-                    if (ok) __hip_atomic_store(word, r.gate.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+                    ok = wait_ready_all(r.gate, r.G - 1, [&](int i) { return (i < r.block ? i : i + 1) * r.pieces + s; });
+                    if (ok && threadIdx.x == 0) __hip_atomic_store(word, r.gate.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
                 }
-                s_ok = ok;
+                if (threadIdx.x == 0) s_ok = ok;
             }
             __syncthreads();               // also orders the tile's loads after the flag reads
             const int ok = s_ok;
