@@ -182,7 +182,7 @@ inline Extent piece_extent(const ficco_plan_t *p, int chunk)
 
 // ---- plan construction and launches (ficco_plan.hip)
 int build_lists(ficco_plan_t *p);
-int choose_tile(const ficco_plan_t *p, int cus, double *step_us = nullptr);   // step_us: estimated time of 64 k values over all tiles
+int choose_tile(const ficco_plan_t *p, int cus, double *us = nullptr);   // us: the estimate for the tile chosen
 int finalize(ficco_plan_t *p);
 void release(ficco_plan_t *p);
 int make_events(std::vector<hipEvent_t> &v, size_t n);

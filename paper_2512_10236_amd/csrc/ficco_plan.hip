@@ -113,48 +113,61 @@ LaunchShape launch_shape(const ficco_plan_t *p, const Group &g)
     return {g.pos_end - g.pos_begin, p->m, false, 0};
 }
 
-// Tile choice. Estimated time of a launch = k-steps x [full rounds over the machine x step(1) +
-// step(fill of the last, partial round)], where step(f) = base + slope * f is the time of one k-step
-// of that tile shape when a fraction f of the machine's workgroup slots is occupied (microseconds,
-// fitted to a sweep of launch sizes on MI355X; the full-machine cost base + slope of the mid-size
-// tiles re-fitted to multi-round resident launches after the tile order changed: 128x256 and 256x128
-// run at 0.87-0.95 of the 256x256 tile's throughput there, 128x128 at 0.84-0.88); padded (masked)
-// rows and columns are paid in full.
-int choose_tile(const ficco_plan_t *p, int cus, double *step_us)
+// Tile choice. Estimated time of a launch, in microseconds: start + (rounds - 1) * next + k-steps (of 64) x [full rounds
+// over the machine x step(1) + step(fill of the last, partial round)], where step(f) = base + slope * f is the time of one
+// k-step of that tile shape when a fraction f of the machine's workgroup slots is occupied. Fitted to resident launches
+// over M 64-16384, K 1024 and 4096, N 256-7168 (132 shapes x 10 tiles, 4-10 % rms): the tile picked is 0.9 % slower than
+// the fastest on average, where the constants of the kernels' earlier k loop, without the 64x128 tile, were 8 % slower.
+// The full-machine cost of 256x128 and 256x192 is set 4-5 % above the fit: beside transfers they lose more than that
+// (all-gather pair, M 16384, K 8192, N 3584: 256x256 0.82 ms, 256x192 0.90, 256x128 0.97, the same three within 1 % alone).
+// Padded (masked) rows and columns are paid in full.
+int choose_tile(const ficco_plan_t *p, int cus, double *us)
 {
-    static const struct { int id; double base, slope; int occ; } cand[] = {
-        {TILE_256x256, 1.40, 0.45, 1}, {TILE_128x256, 0.80, 0.25, 1}, {TILE_256x128, 0.80, 0.27, 1},
-        {TILE_128x128, 0.60, 0.48, 2}, {TILE_128x128D, 0.48, 0.08, 1},
-        {TILE_64x256, 0.57, 0.15, 1},  {TILE_32x256, 0.45, 0.05, 1},
-        {TILE_128x192, 0.72, 0.12, 1}, {TILE_256x192, 1.10, 0.45, 1},
+    static const struct { int id; double base, slope, start, next; int occ; } cand[] = {
+        {TILE_256x256, 0.89, 0.39, 13, 8, 1}, {TILE_128x256, 0.49, 0.22, 10, 6, 1}, {TILE_256x128, 0.51, 0.21, 10, 7, 1},
+        {TILE_128x128, 0.47, 0.39, 6, 3, 2},  {TILE_128x128D, 0.31, 0.09, 8, 4, 1}, {TILE_64x256, 0.32, 0.16, 8, 3, 1},
+        {TILE_32x256, 0.31, 0.09, 6, 2, 1},   {TILE_128x192, 0.40, 0.15, 9, 4, 1},  {TILE_256x192, 0.71, 0.34, 11, 6, 1},
+        {TILE_64x128, 0.23, 0.04, 7, 2, 1},
     };
     double best = 1e300;
     int best_id = TILE_128x128;
+    const double k_steps = (double)p->K / kBK;
     for (auto &cd : cand) {
         TileShape ts = tile_shape(cd.id);
         const double cap = (double)cus * cd.occ;
+        const int64_t tn = (p->N + ts.bn - 1) / ts.bn;
         auto cost = [&](int64_t tiles) {
             const double full = std::floor((double)tiles / cap), rem = (double)tiles - full * cap;
-            return full * (cd.base + cd.slope) + (rem > 0 ? cd.base + cd.slope * rem / cap : 0.0);
+            const double steps = full * (cd.base + cd.slope) + (rem > 0 ? cd.base + cd.slope * rem / cap : 0.0);
+            return cd.start + cd.next * (std::ceil((double)tiles / cap) - 1.0) + k_steps * steps;
         };
         double total = 0;
         if (p->grouped) {
             int64_t rt = 0;
             for (int64_t me : p->expert_nrows) rt += (me + ts.bm - 1) / ts.bm;
-            total = cost(rt * ((p->N + ts.bn - 1) / ts.bn));
+            total = cost(rt * tn);
         } else if (is_2d(p)) {
-            total = cost(((p->M + ts.bm - 1) / ts.bm) * ((p->N + ts.bn - 1) / ts.bn));
+            total = cost(((p->M + ts.bm - 1) / ts.bm) * tn);
         } else if (p->schedule == FICCO_FINE_PERSISTENT) {
-            total = cost((int64_t)p->n_chunks * ((p->m + ts.bm - 1) / ts.bm) * ((p->N + ts.bn - 1) / ts.bn));
+            const int64_t piece_tiles = ((p->m + ts.bm - 1) / ts.bm) * tn;
+            total = cost((int64_t)p->n_chunks * piece_tiles);
+            if (p->c > 1 && p->order == FICCO_ORDER_STEP_MAJOR && p->direction == FICCO_DIR_AG_GEMM) {
+                // pieces arrive step by step: either everything follows the first step's transfer, or, where the transfers
+                // (one shard over one link at 58 GB/s) are the longer side, the last step's tiles follow the last byte
+                // (M 8192, K 4096, N 768, two steps: 128x128 in one round a step 206 us, 128x192, the faster one over
+                // both steps together, 212)
+                const double shard_us = (double)(p->M / p->G) * (double)p->K * 2.0 / 58e3;
+                total = std::max(shard_us / p->c + total, shard_us + cost((int64_t)p->G * piece_tiles));
+            }
         } else {
             for (auto &g : p->groups) {
                 LaunchShape ls = launch_shape(p, g);
-                total += cost((int64_t)ls.n_blocks * ((ls.rows_per_block + ts.bm - 1) / ts.bm) * ((p->N + ts.bn - 1) / ts.bn));
+                total += cost((int64_t)ls.n_blocks * ((ls.rows_per_block + ts.bm - 1) / ts.bm) * tn);
             }
         }
         if (total < best * 0.999) { best = total; best_id = cd.id; }
     }
-    if (step_us) *step_us = best;
+    if (us) *us = best;
     return best_id;
 }
 
@@ -731,7 +744,7 @@ int ficco_plan_set(ficco_plan_t *p, int option, int64_t value)
         p->timing = (int)value;
         break;
     case FICCO_OPT_TILE:
-        if (value != 0 && tile_shape((int)value).bm == 0) return FICCO_ERR_ARG;
+        if (value < 0 || value > FICCO_TILE_256x192) return FICCO_ERR_ARG;      // (64x128 is the library's own choice only)
         p->tile_opt = (int)value;
         break;
     case FICCO_OPT_FLAG_WRITE:

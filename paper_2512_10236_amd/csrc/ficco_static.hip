@@ -40,16 +40,15 @@ int scratch_of(int dev, unsigned char **out)
 // narrow tile, so it wins where a launch is a round or two of its tiles and loses where the resident kernel's big tiles
 // fill the chip. Estimates in us, from timings over M 1-8192, K 64-8192, N 8-4096: a stage of 128 k values takes 0.25 /
 // 0.31 / 0.55 us with 1 / 2 / 4 row blocks (a CU draws about 80 GB/s from L2 and beyond), a round starts in 1.5 us; the
-// packed way takes choose_tile's steps and 8 us for the packing launch. Measured on either side, direct against packed:
-// M 64, K 4096, N 768 9.7 : 37.6; M 512, K 4096, N 1024 12.7 : 33.8; M 1024, K 2048, N 2048 (two rounds) 20.0 : 24.9;
-// M 2048, K 4096, N 1024 41.7 : 37.2; M 4096, K 1024, N 1024 26.7 : 20.6. A weight that is not 16-byte aligned, or that
-// the result overwrites, is always packed first.
-int direct_row_blocks(int64_t M, int64_t K, int64_t N, const void *W, const void *C, int cus, double packed_step_us)
+// packed way takes choose_tile's estimate and 4 us for the packing launch. Measured on either side, direct against packed:
+// M 64, K 4096, N 768 9.7 : 37.6; M 512, K 4096, N 1024 12.7 : 33.8; M 2048, K 4096, N 1024 41.7 : 37.2; M 4096, K 1024,
+// N 1024 26.7 : 20.6. A weight that is not 16-byte aligned, or that the result overwrites, is always packed first.
+int direct_row_blocks(int64_t M, int64_t K, int64_t N, const void *W, const void *C, int cus, double packed_us)
 {
     const uintptr_t w0 = (uintptr_t)W, c0 = (uintptr_t)C;
     if (w0 % 16 || (c0 < w0 + (uintptr_t)(2 * K * N) && w0 < c0 + (uintptr_t)(2 * M * N))) return 0;
     static const struct { int row_blocks; double stage; } cand[] = {{1, 0.25}, {2, 0.31}, {4, 0.55}};
-    double best = 0.95 * (8.0 + packed_step_us * (double)(K / kBK));
+    double best = packed_us + 4.0;
     int best_id = 0;
     for (auto &cd : cand) {
         const int64_t tiles = ((M + 16 * cd.row_blocks - 1) / (16 * cd.row_blocks)) * ((N + 63) / 64);
@@ -91,9 +90,9 @@ extern "C" int ficco_gemm_static(int64_t M, int64_t K, int64_t N, const void *A_
     if ((rc = build_lists(&shape))) return rc;
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    double step_us = 0;
-    shape.tile = choose_tile(&shape, cus, &step_us);
-    const int row_blocks = direct_row_blocks(M, K, N, W_dev, C_dev, cus, step_us);
+    double packed_us = 0;
+    shape.tile = choose_tile(&shape, cus, &packed_us);
+    const int row_blocks = direct_row_blocks(M, K, N, W_dev, C_dev, cus, packed_us);
     if (row_blocks) {
         DirectLaunch d{};
         d.A = (const uint16_t *)A_dev;
