@@ -647,11 +647,11 @@ int run_engines(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, vo
             }
         }
     } else if (!rs) {
-        // ---- The kernels wait on flags or signals inside, so the order of the two sides is free. Short runs
-        // enqueue the GEMM side first so that it is resident before data lands; long ones (a MiB or more per
-        // link) start the engines first and enqueue the launches while the first pieces are on their way,
-        // which takes the launch latency off the critical path.
-        const bool copies_first = do_copy && do_gemm && (size_t)p->M * row_bytes_a / (size_t)std::max(links, 1) >= ((size_t)1 << 20);
+        // ---- The kernels wait on flags or signals inside, so the order of the two sides is free. The engines start
+        // first and the launches are enqueued while the first pieces are on their way, which takes the launch latency off
+        // the critical path (with the launch in front: M 512, K 512, N 256 over two shards 39.1 us a run instead of
+        // 36.4, M 512, K 1024, N 1024 over four 42.6 instead of 39.7, the same from 1 MiB per link on).
+        const bool copies_first = do_copy && do_gemm;
         if (copies_first)
             for (int q = 0; q < n; ++q)
                 if ((rc = submit(q))) return rc;

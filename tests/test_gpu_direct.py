@@ -1,7 +1,7 @@
 """The GEMM straight from a row-major weight (small products of ficco_gemm_static) and the weight packing kernels, bit for
 bit against the plan path: the same MFMAs in the same k order. Sizes: one row and one column block, remainders of rows,
-columns and of the 128-value stage, fewer stages than the ring holds (7 of 128 values for 16-row tiles), as many and more,
-every tile height on both sides of where the rule changes it, and what the direct kernel does not take."""
+columns and of the 128-value stage, fewer stages than the ring holds (7, 6 and 4 of 128 values for 1, 2 and 4 row blocks),
+as many and more, every tile on both sides of where the rule changes it, and what the direct kernel does not take."""
 import os
 import sys
 
@@ -34,7 +34,7 @@ def _by_plan(gpu, A, W, M, K, N):
     return C.view(torch.int16)
 
 
-SHAPES = [(1, 64, 8), (16, 128, 64), (17, 192, 72), (5, 768, 136), (48, 896, 1160), (64, 1024, 56), (130, 2880, 1448),
+SHAPES = [(1, 64, 8), (16, 128, 64), (17, 192, 72), (5, 768, 136), (48, 896, 1160), (64, 1024, 56), (20, 896, 96), (16, 1024, 40), (64, 4096, 768), (130, 2880, 1448),
           (256, 512, 1024), (257, 512, 1024), (512, 576, 1000), (513, 576, 1032), (1024, 512, 1024), (1025, 640, 1032), (4096, 128, 64)]
 
 
