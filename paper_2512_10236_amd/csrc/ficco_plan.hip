@@ -151,7 +151,7 @@ int choose_tile(const ficco_plan_t *p, int cus, double *us)
         } else if (p->schedule == FICCO_FINE_PERSISTENT) {
             const int64_t piece_tiles = ((p->m + ts.bm - 1) / ts.bm) * tn;
             total = cost((int64_t)p->n_chunks * piece_tiles);
-            if (p->c > 1 && p->order == FICCO_ORDER_STEP_MAJOR && p->direction == FICCO_DIR_AG_GEMM) {
+            if (p->c > 1 && p->order == FICCO_ORDER_STEP_MAJOR && p->direction == FICCO_DIR_AG_GEMM && p->mode == FICCO_MODE_PAIR) {
                 // pieces arrive step by step: either everything follows the first step's transfer, or, where the transfers
                 // (one shard over one link at 58 GB/s) are the longer side, the last step's tiles follow the last byte
                 // (M 8192, K 4096, N 768, two steps: 128x128 in one round a step 206 us, 128x192, the faster one over
