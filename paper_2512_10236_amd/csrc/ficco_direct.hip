@@ -7,9 +7,13 @@
 // at once, and keeps a ring of S - 1 stages of 128 k values (20-32 KiB each, over 100 KiB a CU) in flight, which
 // covers the latency of memory. The weight's fragments need 8 consecutive k of one column, which a row-major tile does
 // not hold next to each other: ds_read_b64_tr_b16 transposes on the way out of LDS (16 lanes read 4 rows x 16
-// columns, lane i gets column i). A stage takes 0.25 us with FM = 1: a CU draws about 80 GB/s (35 bytes a cycle) however
-// many of them take part, and M 64, K 4096, N 768 takes 9.7 us, where packing the weight and running the resident kernel
-// on it took 43. With the stage's reads behind its loads instead of in front of them 11.7 us.
+// columns, lane i gets column i).
+//
+// With FM = 1 a stage takes 0.16-0.25 us and M 64, K 4096, N 768 9.7 us, where packing the weight 2 bytes at a time and
+// running the resident kernel on it took 43. With the
+// stage's reads behind its loads instead of in front of them 11.7 us. Neither fewer bytes a stage (16 x 32 tiles, twice the
+// CUs, 9.7), nor reads a stage ahead in a second register buffer (11.1), nor wavefronts of their own for the loads (10.2)
+// made it faster; the last took 64-row tiles from 18.2 to 15.4 us (M 1024, K 4096, N 768).
 #include "ficco_internal.h"
 #include "ficco_mfma.h"
 

@@ -39,10 +39,11 @@ int scratch_of(int dev, unsigned char **out)
 // 16 * row_blocks rows x 64 columns. The direct kernel needs no packed weight but fetches every operand row once per
 // narrow tile, so it wins where a launch is a round or two of its tiles and loses where the resident kernel's big tiles
 // fill the chip. Estimates in us, from timings over M 1-8192, K 64-8192, N 8-4096: a stage of 128 k values takes 0.25 /
-// 0.31 / 0.55 us with 1 / 2 / 4 row blocks (a CU draws about 80 GB/s from L2 and beyond), a round starts in 1.5 us; the
-// packed way takes choose_tile's estimate and 4 us for the packing launch. Measured on either side, direct against packed:
-// M 64, K 4096, N 768 9.7 : 37.6; M 512, K 4096, N 1024 12.7 : 33.8; M 2048, K 4096, N 1024 41.7 : 37.2; M 4096, K 1024,
-// N 1024 26.7 : 20.6. A weight that is not 16-byte aligned, or that the result overwrites, is always packed first.
+// 0.31 / 0.55 us with 1 / 2 / 4 row blocks, a round starts in 1.5 us; the packed way takes choose_tile's
+// estimate and 4 us for the packing launch. Measured on either side, direct against packed: M 64, K 4096, N 768 9.7 : 37.6
+// and M 512, K 4096, N 1024 12.7 : 33.8 (packed without the 64x128 tile); M 1024, K 2048, N 2048 20.0 : 22.9 (packed by
+// the estimate); M 2048, K 4096, N 1024 41.7 : 30.1; M 4096, K 1024, N 1024 26.7 : 19.6. A weight that is not 16-byte
+// aligned, or that the result overwrites, is always packed first.
 int direct_row_blocks(int64_t M, int64_t K, int64_t N, const void *W, const void *C, int cus, double packed_us)
 {
     const uintptr_t w0 = (uintptr_t)W, c0 = (uintptr_t)C;
