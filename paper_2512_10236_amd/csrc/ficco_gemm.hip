@@ -348,7 +348,7 @@ static __device__ __forceinline__ void tile_store(const TileAcc<T> &ta, uint16_t
             const u32x4_t v = {lo[0], hi[0], lo[1], hi[1]};
             const int n = n0 + j * 16;
             if (m < rows_valid && n < cols_valid) {
-                if constexpr (THROUGH) asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(crow + n), "v"(v) : "memory");
+                if constexpr (THROUGH) store_through_16(crow + n, v);
                 else *reinterpret_cast<u32x4_t *>(crow + n) = v;
             }
         }
@@ -867,7 +867,7 @@ __global__ __launch_bounds__(256) void slice_source_kernel(SliceLaunch a)
             for (int u = 0; u < 4; ++u) {
                 const int ee = e + u * 256;
                 // written through the caches: the reader is a copy engine
-                if (ee < total) asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(dst + ee), "v"(v[u]) : "memory");
+                if (ee < total) store_through_16(dst + ee, v[u]);
             }
         }
         // every store of the block has been performed (not just issued) before the block is counted

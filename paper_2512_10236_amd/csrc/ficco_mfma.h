@@ -56,6 +56,14 @@ static __device__ __forceinline__ void load_to_lds_16(const void *base, uint32_t
 {
     asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base) : "memory");
 }
+// 16 bytes per lane written through the caches (system scope), for data that a copy engine reads while the kernel runs on.
+// The hardware reads the data of a store of more than 64 bits up to two wait states after its issue; the compiler keeps
+// its vector instructions off the registers that long behind its own stores only, hence the no-op (without it up to 26
+// stores of a tile's epilogue had their registers overwritten one state later; tests/test_asm_hazards.py checks it).
+static __device__ __forceinline__ void store_through_16(void *dst, u32x4_t v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(dst), "v"(v) : "memory");
+}
 template <int N>
 static __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 static __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
