@@ -520,6 +520,9 @@ double ficco_ideal_overlap_us(double t_comm_us, double t_gemm_us, int n);
  * one fixed array in the library's device image, of FICCO_STATIC_MAX_WEIGHT_BYTES + 4096 bytes, which every GPU the
  * library runs on holds until the process ends; the packing kernel clears what must start at zero (no memset node is
  * recorded if the stream is being captured). The call returns without waiting.
+ * C_dev may overlap W_dev (the weight is read to its end first). It may also be A_dev itself where K == N <= 256 (the row
+ * of the result takes the place of the row it came from), or overlap A_dev anyhow where M <= 32 and N <= 256; any other
+ * overlap of C_dev and A_dev is undefined.
  * Shape rules: M, K, N >= 1, K % 64 == 0, N % 8 == 0, M and N below 2^31, K at most 2^22, and K*N*2 bytes at most
  * FICCO_STATIC_MAX_WEIGHT_BYTES (FICCO_ERR_SHAPE otherwise; e.g. K = 4096 with N up to 1024).
  * All calls on one GPU share that GPU's array: two calls whose kernels overlap on one GPU (different

@@ -182,7 +182,13 @@ inline Extent piece_extent(const ficco_plan_t *p, int chunk)
 
 // ---- plan construction and launches (ficco_plan.hip)
 int build_lists(ficco_plan_t *p);
-int choose_tile(const ficco_plan_t *p, int cus, double *us = nullptr);   // us: the estimate for the tile chosen
+// whole_rows: only tiles as wide as the output, where one is (N <= 256), so that a workgroup has read all it will read of
+// its rows of A before it stores them; us: the estimate for the tile chosen
+int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows = false, double *us = nullptr);
+inline bool overlap(const void *a, int64_t a_bytes, const void *b, int64_t b_bytes)
+{
+    return (uintptr_t)a < (uintptr_t)b + (uintptr_t)b_bytes && (uintptr_t)b < (uintptr_t)a + (uintptr_t)a_bytes;
+}
 int finalize(ficco_plan_t *p);
 void release(ficco_plan_t *p);
 int make_events(std::vector<hipEvent_t> &v, size_t n);

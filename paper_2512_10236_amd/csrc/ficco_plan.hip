@@ -121,7 +121,7 @@ LaunchShape launch_shape(const ficco_plan_t *p, const Group &g)
 // The full-machine cost of 256x128 and 256x192 is set 4-5 % above the fit: beside transfers they lose more than that
 // (all-gather pair, M 16384, K 8192, N 3584: 256x256 0.82 ms, 256x192 0.90, 256x128 0.97, the same three within 1 % alone).
 // Padded (masked) rows and columns are paid in full.
-int choose_tile(const ficco_plan_t *p, int cus, double *us)
+int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
 {
     static const struct { int id; double base, slope, start, next; int occ; } cand[] = {
         {TILE_256x256, 0.89, 0.39, 13, 8, 1}, {TILE_128x256, 0.49, 0.22, 10, 6, 1}, {TILE_256x128, 0.51, 0.21, 10, 7, 1},
@@ -134,6 +134,7 @@ int choose_tile(const ficco_plan_t *p, int cus, double *us)
     const double k_steps = (double)p->K / kBK;
     for (auto &cd : cand) {
         TileShape ts = tile_shape(cd.id);
+        if (whole_rows && p->N <= 256 && ts.bn < p->N) continue;
         const double cap = (double)cus * cd.occ;
         const int64_t tn = (p->N + ts.bn - 1) / ts.bn;
         auto cost = [&](int64_t tiles) {

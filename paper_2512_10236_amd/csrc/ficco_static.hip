@@ -42,12 +42,9 @@ int scratch_of(int dev, unsigned char **out)
 // 0.31 / 0.55 us with 1 / 2 / 4 row blocks, a round starts in 1.5 us; the packed way takes choose_tile's
 // estimate and 4 us for the packing launch. Measured on either side, direct against packed: M 64, K 4096, N 768 9.7 : 37.6
 // and M 512, K 4096, N 1024 12.7 : 33.8 (packed without the 64x128 tile); M 1024, K 2048, N 2048 20.0 : 22.9 (packed by
-// the estimate); M 2048, K 4096, N 1024 41.7 : 30.1; M 4096, K 1024, N 1024 26.7 : 19.6. A weight that is not 16-byte
-// aligned, or that the result overwrites, is always packed first.
-int direct_row_blocks(int64_t M, int64_t K, int64_t N, const void *W, const void *C, int cus, double packed_us)
+// the estimate); M 2048, K 4096, N 1024 41.7 : 30.1; M 4096, K 1024, N 1024 26.7 : 19.6.
+int direct_row_blocks(int64_t M, int64_t K, int64_t N, int cus, double packed_us)
 {
-    const uintptr_t w0 = (uintptr_t)W, c0 = (uintptr_t)C;
-    if (w0 % 16 || (c0 < w0 + (uintptr_t)(2 * K * N) && w0 < c0 + (uintptr_t)(2 * M * N))) return 0;
     static const struct { int row_blocks; double stage; } cand[] = {{1, 0.25}, {2, 0.31}, {4, 0.55}};
     double best = packed_us + 4.0;
     int best_id = 0;
@@ -92,8 +89,13 @@ extern "C" int ficco_gemm_static(int64_t M, int64_t K, int64_t N, const void *A_
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     double packed_us = 0;
-    shape.tile = choose_tile(&shape, cus, &packed_us);
-    const int row_blocks = direct_row_blocks(M, K, N, W_dev, C_dev, cus, packed_us);
+    // A weight that is not 16-byte aligned, or that the result overwrites, is packed first. A result over the activation
+    // needs it too: the direct kernel's tiles are narrower than most outputs, and while one stores, another still reads
+    // the same rows of A. The packed way then takes a tile as wide as the output.
+    const bool over_a = overlap(C_dev, 2 * M * N, A_dev, 2 * M * K);
+    shape.tile = choose_tile(&shape, cus, over_a, &packed_us);
+    const bool packed_only = over_a || (uintptr_t)W_dev % 16 || overlap(C_dev, 2 * M * N, W_dev, 2 * K * N);
+    const int row_blocks = packed_only ? 0 : direct_row_blocks(M, K, N, cus, packed_us);
     if (row_blocks) {
         DirectLaunch d{};
         d.A = (const uint16_t *)A_dev;
