@@ -34,6 +34,7 @@ int ficco_run(ficco_plan_t *p, const void *A_src, void *A_dev, const void *W_dev
     }
     int rc = finalize(p);
     if (rc) return rc;
+    if ((rc = select_tile(p))) return rc;
     if (p->tile_col_lists > 1 && (is_resident(p) || p->grouped)) {     // refuse before anything is enqueued
         const TileShape ts = tile_shape(p->tile);
         if (p->tile_col_lists > (p->N + ts.bn - 1) / ts.bn) return FICCO_ERR_ARG;
@@ -602,6 +603,7 @@ int ficco_profile_losses(ficco_plan_t *p, const void *A_src, void *A_dev, const 
     whole->links_opt = p->links_opt;
     whole->spin_limit_us = p->spin_limit_us;
     const int saved_mode = p->mode, saved_timing = p->timing;
+    p->losses_of = saved_mode;           // the losses of the launches that the plan's own mode makes
 
     // mean span of one mode over `iters` runs after `warmup`; `repeat` > 1 (GEMM alone): every run enqueues the
     // plan's launches that many times back to back inside its bracket of events and the span is divided by it
@@ -653,6 +655,7 @@ int ficco_profile_losses(ficco_plan_t *p, const void *A_src, void *A_dev, const 
         if ((rc = measure(p, FICCO_MODE_INDEPENDENT, 0, 1, &L.t_gemm_pieces_cont_us, &L.t_copy_pieces_cont_us, nullptr))) break;
     } while (0);
     ficco_destroy(whole);
+    p->losses_of = -1;
     p->mode = saved_mode;
     p->timing = saved_timing;
     p->repeat = saved_repeat;

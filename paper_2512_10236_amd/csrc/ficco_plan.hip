@@ -113,6 +113,9 @@ LaunchShape launch_shape(const ficco_plan_t *p, const Group &g)
     return {g.pos_end - g.pos_begin, p->m, false, 0};
 }
 
+// Is the tile to be one for a GEMM that follows its transfers?
+static bool runs_pair(const ficco_plan_t *p) { return (p->losses_of >= 0 ? p->losses_of : p->mode) == FICCO_MODE_PAIR; }
+
 // Tile choice. Estimated time of a launch, in microseconds: start + (rounds - 1) * next + k-steps (of 64) x [full rounds
 // over the machine x step(1) + step(fill of the last, partial round)], where step(f) = base + slope * f is the time of one
 // k-step of that tile shape when a fraction f of the machine's workgroup slots is occupied. Fitted to resident launches
@@ -152,7 +155,7 @@ int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
         } else if (p->schedule == FICCO_FINE_PERSISTENT) {
             const int64_t piece_tiles = ((p->m + ts.bm - 1) / ts.bm) * tn;
             total = cost((int64_t)p->n_chunks * piece_tiles);
-            if (p->c > 1 && p->order == FICCO_ORDER_STEP_MAJOR && p->direction == FICCO_DIR_AG_GEMM && p->mode == FICCO_MODE_PAIR) {
+            if (p->c > 1 && p->order == FICCO_ORDER_STEP_MAJOR && p->direction == FICCO_DIR_AG_GEMM && runs_pair(p)) {
                 // pieces arrive step by step: either everything follows the first step's transfer, or, where the transfers
                 // (one shard over one link at 58 GB/s) are the longer side, the last step's tiles follow the last byte
                 // (M 8192, K 4096, N 768, two steps: 128x128 in one round a step 206 us, 128x192, the faster one over
@@ -226,6 +229,33 @@ int make_events(std::vector<hipEvent_t> &v, size_t n)
     return FICCO_OK;
 }
 
+// The tile and the resident grid of the run at hand. The mode may change from run to run and the rule with it: the order
+// in which a plan's modes are used must not decide which tile they get (M 8192, K 4096, N 768, two steps: the pair's tile
+// takes 59 us in a run of the GEMM alone, whose own takes 48, and that one costs the pair 6 us). Nothing on the device
+// depends on the tile but an expert-parallel plan's table of row tiles, and there the rule does not ask for the mode.
+int select_tile(ficco_plan_t *p)
+{
+    const bool pair = runs_pair(p);
+    if (p->tile && (p->grouped || pair == p->tile_for_pair)) return FICCO_OK;
+    int cus = 0;
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+    const int tile = p->tile_opt ? p->tile_opt : choose_tile(p, cus);
+    const TileShape ts = tile_shape(tile);
+    if (ts.bm == 0) return FICCO_ERR_ARG;
+    int grid = 0;
+    if (is_resident(p) && !p->grouped) {         // (an expert-parallel plan's grid comes with its table)
+        grid = is_2d(p) ? resident2d_grid_size(tile, p->device) : resident_grid_size(tile, p->device);
+        if (grid <= 0) return FICCO_ERR_HIP;
+        const int64_t tiles = (is_2d(p) ? (p->M + ts.bm - 1) / ts.bm : (int64_t)p->n_chunks * ((p->m + ts.bm - 1) / ts.bm)) *
+                              ((p->N + ts.bn - 1) / ts.bn);
+        if (tiles < grid) grid = (int)tiles;
+    }
+    p->tile = tile;
+    p->resident_grid = grid;
+    p->tile_for_pair = pair;
+    return FICCO_OK;
+}
+
 int finalize(ficco_plan_t *p)
 {
     if (p->finalized) return FICCO_OK;
@@ -236,10 +266,8 @@ int finalize(ficco_plan_t *p)
     p->device = dev;
     int rc = build_lists(p);
     if (rc) return rc;
-    int cus = 0;
-    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    p->tile = p->tile_opt ? p->tile_opt : choose_tile(p, cus);
-    if (tile_shape(p->tile).bm == 0) return FICCO_ERR_ARG;
+    p->tile = 0;                                  // (options may have changed since an attempt that failed)
+    if ((rc = select_tile(p))) return rc;
     int khz = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0) p->wall_clock_khz = khz;
 
@@ -323,13 +351,6 @@ int finalize(ficco_plan_t *p)
         if (p->resident_grid <= 0) return FICCO_ERR_HIP;
         const int64_t tiles = (int64_t)p->n_row_tiles * ((p->N + ts.bn - 1) / ts.bn);
         if (tiles < p->resident_grid) p->resident_grid = (int)std::max<int64_t>(tiles, 1);
-    } else if (is_resident(p)) {
-        p->resident_grid = is_2d(p) ? resident2d_grid_size(p->tile, dev) : resident_grid_size(p->tile, dev);
-        if (p->resident_grid <= 0) return FICCO_ERR_HIP;
-        TileShape ts = tile_shape(p->tile);
-        int64_t tiles = is_2d(p) ? ((p->M + ts.bm - 1) / ts.bm) * ((p->N + ts.bn - 1) / ts.bn)
-                                 : (int64_t)n * ((p->m + ts.bm - 1) / ts.bm) * ((p->N + ts.bn - 1) / ts.bn);
-        if (tiles < p->resident_grid) p->resident_grid = (int)tiles;
     }
     p->finalized = true;
     return FICCO_OK;

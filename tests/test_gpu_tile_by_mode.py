@@ -1,0 +1,71 @@
+"""The tile of a run follows from the plan and the run's mode, whatever ran before: each mode on a fresh plan, then on one
+plan in both orders and behind the loss profiler, at a shape whose pair and whose GEMM alone get different tiles, with the
+same result bit for bit (the counters of the tile lists go on from run to run)."""
+import pytest
+
+import paper_2512_10236_amd as ficco
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+M, K, N, G, C = 8192, 1024, 768, 8, 2
+PAIR, ALONE, BOTH = ficco.FICCO_MODE_PAIR, ficco.FICCO_MODE_GEMM_ONLY, ficco.FICCO_MODE_INDEPENDENT
+
+
+@pytest.fixture(scope="module")
+def operands(gpu):
+    g = torch.Generator(device=gpu["dev"]).manual_seed(5)
+    A = torch.randn((M, K), generator=g, device=gpu["dev"]).bfloat16()
+    W = torch.randn((K, N), generator=g, device=gpu["dev"]).bfloat16()
+    torch.cuda.synchronize()
+    return A, W, A.clone(), torch.empty((M, N), dtype=torch.bfloat16, device=gpu["dev"])
+
+
+def _run(gpu, plan, mode, ops):
+    A, W, A_dev, out = ops
+    print(f"mode {mode}", flush=True)
+    ficco.ficco_plan_set(plan, ficco.FICCO_OPT_MODE, mode)
+    out.fill_(7.0)
+    torch.cuda.synchronize()
+    ficco.ficco_run(plan, None if mode == ALONE else A, A_dev, W, out, None, gpu["cs"], gpu["xs"])
+    ficco.ficco_query_stats(plan)
+    info = ficco.ficco_plan_info(plan)
+    return (info.tile_m, info.tile_n, info.resident_grid), out.view(torch.int16).clone()
+
+
+def _fresh(gpu, mode, ops):
+    plan = ficco.ficco_plan(M, K, N, G, C, ficco.FICCO_FINE_PERSISTENT)
+    try:
+        return _run(gpu, plan, mode, ops)
+    finally:
+        ficco.ficco_destroy(plan)
+
+
+def test_tile_does_not_depend_on_what_ran_before(gpu, operands):
+    tile, bits = {}, {}
+    for mode in (PAIR, ALONE, BOTH):
+        tile[mode], bits[mode] = _fresh(gpu, mode, operands)
+        assert torch.equal(bits[mode], bits[PAIR])
+    assert tile[PAIR] != tile[ALONE], "the shape no longer tells the two apart: take another one"
+    for order in ((PAIR, ALONE, PAIR, BOTH, PAIR), (ALONE, PAIR, ALONE), (BOTH, PAIR)):
+        plan = ficco.ficco_plan(M, K, N, G, C, ficco.FICCO_FINE_PERSISTENT)
+        try:
+            for mode in order:
+                got, out = _run(gpu, plan, mode, operands)
+                assert got == tile[mode], (order, mode)
+                assert torch.equal(out, bits[PAIR]), (order, mode)
+        finally:
+            ficco.ficco_destroy(plan)
+
+
+def test_loss_profile_leaves_the_pair_its_tile(gpu, operands):
+    A, W, A_dev, out = operands
+    pair = _fresh(gpu, PAIR, operands)[0]
+    plan = ficco.ficco_plan(M, K, N, G, C, ficco.FICCO_FINE_PERSISTENT)
+    try:
+        ficco.ficco_profile_losses(plan, A, A_dev, W, out, gpu["cs"], gpu["xs"], 1, 2)
+        info = ficco.ficco_plan_info(plan)
+        assert (info.tile_m, info.tile_n, info.resident_grid) == pair, "the losses are those of the pair's launches"
+        assert _run(gpu, plan, PAIR, operands)[0] == pair
+    finally:
+        ficco.ficco_destroy(plan)
