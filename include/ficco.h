@@ -381,7 +381,9 @@ int ficco_pack_weight(ficco_plan_t *plan, const void *W_dev, void *stream);
  *                      piece i is copied to the same rows of A_dev on copy_stream (may be NULL in
  *                      FICCO_MODE_GEMM_ONLY).
  *             A_dev  - [M,K] device; written by the transfers, read by the GEMM.
- *             C_dev  - [M,N] device; written by the GEMM.
+ *             C_dev  - [M,N] device; written by the GEMM. It may be A_dev itself where K == N <= 256 and the
+ *                      tile is left to the library (the row of the result takes the place of the row it
+ *                      came from; not with FICCO_FINE_2D); any other overlap of the two is undefined.
  *             peer_out must be NULL.
  *             FICCO_FINE_2D: A_dev is K-sliced: slice s holds its columns of every row as an
  *             [M][width_s] row-major block, block after block ([chunks][M][K/chunks] when K/64 is a

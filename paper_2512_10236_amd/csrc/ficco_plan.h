@@ -99,7 +99,7 @@ struct ficco_plan_s {
     bool finalized = false;
     int tile = 0;                        // of the latest run (select_tile); 0: none chosen yet
     int resident_grid = 0;
-    bool tile_for_pair = false;          // what `tile` was chosen for
+    bool tile_for_pair = false, tile_whole_rows = false;   // what `tile` was chosen for
     int losses_of = -1;                  // ficco_profile_losses: the mode whose tile the runs of the other modes take, too
     uint32_t *d_words = nullptr;         // flags | status | scratch: fine-grained device memory, polled while engines write it
     uint32_t *d_ticket_mem = nullptr;    // ticket counter: ordinary device memory (device-scope atomics)
@@ -192,7 +192,7 @@ inline bool overlap(const void *a, int64_t a_bytes, const void *b, int64_t b_byt
     return (uintptr_t)a < (uintptr_t)b + (uintptr_t)b_bytes && (uintptr_t)b < (uintptr_t)a + (uintptr_t)a_bytes;
 }
 int finalize(ficco_plan_t *p);
-int select_tile(ficco_plan_t *p);
+int select_tile(ficco_plan_t *p, bool in_place);
 void release(ficco_plan_t *p);
 int make_events(std::vector<hipEvent_t> &v, size_t n);
 int pack_weight(ficco_plan_t *p, const void *W_dev, hipStream_t s);

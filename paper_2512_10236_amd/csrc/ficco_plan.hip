@@ -231,15 +231,17 @@ int make_events(std::vector<hipEvent_t> &v, size_t n)
 
 // The tile and the resident grid of the run at hand. The mode may change from run to run and the rule with it: the order
 // in which a plan's modes are used must not decide which tile they get (M 8192, K 4096, N 768, two steps: the pair's tile
-// takes 59 us in a run of the GEMM alone, whose own takes 48, and that one costs the pair 6 us). Nothing on the device
-// depends on the tile but an expert-parallel plan's table of row tiles, and there the rule does not ask for the mode.
-int select_tile(ficco_plan_t *p)
+// takes 59 us in a run of the GEMM alone, whose own takes 48, and that one costs the pair 6 us). So may the buffers: a
+// result over the activation (in_place) needs tiles that hold whole rows, or one stores what another still reads. Nothing
+// on the device depends on the tile but an expert-parallel plan's table of row tiles: there the rule does not ask for the
+// mode, and a weight that could be used in place gets such tiles from the start.
+int select_tile(ficco_plan_t *p, bool in_place)
 {
-    const bool pair = runs_pair(p);
-    if (p->tile && (p->grouped || pair == p->tile_for_pair)) return FICCO_OK;
+    const bool pair = runs_pair(p), whole_rows = p->grouped ? p->K == p->N : in_place;
+    if (p->tile && (p->grouped || (pair == p->tile_for_pair && whole_rows == p->tile_whole_rows))) return FICCO_OK;
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-    const int tile = p->tile_opt ? p->tile_opt : choose_tile(p, cus);
+    const int tile = p->tile_opt ? p->tile_opt : choose_tile(p, cus, whole_rows);
     const TileShape ts = tile_shape(tile);
     if (ts.bm == 0) return FICCO_ERR_ARG;
     int grid = 0;
@@ -253,6 +255,7 @@ int select_tile(ficco_plan_t *p)
     p->tile = tile;
     p->resident_grid = grid;
     p->tile_for_pair = pair;
+    p->tile_whole_rows = whole_rows;
     return FICCO_OK;
 }
 
@@ -267,7 +270,7 @@ int finalize(ficco_plan_t *p)
     int rc = build_lists(p);
     if (rc) return rc;
     p->tile = 0;                                  // (options may have changed since an attempt that failed)
-    if ((rc = select_tile(p))) return rc;
+    if ((rc = select_tile(p, false))) return rc;
     int khz = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0) p->wall_clock_khz = khz;
 

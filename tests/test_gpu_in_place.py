@@ -41,3 +41,48 @@ def test_static_result_over_a_part_of_the_activation(gpu, M, K, N, lead):
     ficco.ficco_gemm_static(M, K, N, A, W, C, gpu["cs"])
     torch.cuda.synchronize()
     assert torch.equal(C.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("schedule,G,c,mode", [
+    (ficco.FICCO_FINE_PERSISTENT, 1, 1, ficco.FICCO_MODE_GEMM_ONLY), (ficco.FICCO_SERIAL, 1, 1, ficco.FICCO_MODE_GEMM_ONLY),
+    (ficco.FICCO_FINE_PERSISTENT, 8, 2, ficco.FICCO_MODE_PAIR), (ficco.FICCO_FINE_FUSED, 8, 2, ficco.FICCO_MODE_PAIR)])
+@pytest.mark.parametrize("M,K", [(16 * 100, 256), (65536, 192), (65536, 256)])
+def test_run_in_place(gpu, schedule, G, c, mode, M, K):
+    """One plan, first with a result of its own, then in place, then with its own again."""
+    A, W = _operands(gpu["dev"], M, K, K)
+    own = [torch.empty_like(A) for _ in range(2)]
+    landing = A.clone()
+    plan = ficco.ficco_plan(M, K, K, G, c, schedule)
+    try:
+        ficco.ficco_plan_set(plan, ficco.FICCO_OPT_MODE, mode)
+        print(f"plan in place {M}x{K} schedule {schedule} {G}x{c}", flush=True)
+        for C in (own[0], landing, own[1]):
+            if mode == ficco.FICCO_MODE_GEMM_ONLY and C is not landing:
+                landing.copy_(A)
+            torch.cuda.synchronize()
+            ficco.ficco_run(plan, None if mode == ficco.FICCO_MODE_GEMM_ONLY else A, landing, W, C, None, gpu["cs"], gpu["xs"])
+            ficco.ficco_query_stats(plan)
+            if C is landing:
+                placed = landing.clone()
+    finally:
+        ficco.ficco_destroy(plan)
+    for got in (placed, own[1]):
+        assert torch.equal(got.view(torch.int16), own[0].view(torch.int16))
+
+
+def test_experts_in_place(gpu):
+    G, E, K, rows = 4, 2, 192, 8192
+    g = torch.Generator(device=gpu["dev"]).manual_seed(3)
+    A = torch.randn((G * E * rows, K), generator=g, device=gpu["dev"]).bfloat16()
+    W = (torch.randn((E * K, K), generator=g, device=gpu["dev"]) * K ** -0.5).bfloat16()
+    landing, own = torch.empty_like(A), torch.empty_like(A)
+    plan = ficco.ficco_plan_grouped(K, K, [[rows] * E] * G, 1, ficco.FICCO_FINE_PERSISTENT)
+    try:
+        print("experts in place", flush=True)
+        torch.cuda.synchronize()
+        for C in (own, landing):
+            ficco.ficco_run(plan, A, landing, W, C, None, gpu["cs"], gpu["xs"])
+            ficco.ficco_query_stats(plan)
+    finally:
+        ficco.ficco_destroy(plan)
+    assert torch.equal(landing.view(torch.int16), own.view(torch.int16))
