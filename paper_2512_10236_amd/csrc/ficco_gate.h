@@ -50,7 +50,10 @@ static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, Piece
         for (;;) {
             const int landed = waiting && peek_ready(g, piece);
             if (landed) waiting = 0;
-            if (!__any(waiting)) break;
+            if (!__any(waiting)) {
+                if (base + 64 < n) t0 = wall_clock64();      // the next 64 have the whole limit, as after any landing
+                break;
+            }
             if (__any(landed)) t0 = wall_clock64();
             int give_up = 0;
             if (lane == 0) {

@@ -1,6 +1,7 @@
 """Waits for more pieces than a wavefront has lanes, and for slices of which some have landed: the whole output of a
 launch over 80 shards (its wait list is 80 pieces), the join of a run whose 128 transfers no GEMM consumes, and column
-pieces that are more than 64 slices. Compared with the resident row-piece run, bit for bit."""
+pieces that are more than 64 slices. Compared with the resident row-piece run, bit for bit. And the limit of a wait for
+more than 64 pieces."""
 import pytest
 
 import paper_2512_10236_amd as ficco
@@ -46,3 +47,32 @@ def test_more_slices_than_lanes(gpu):
     C = _run(gpu, 256, 64 * 70, 256, 2, 70, ficco.FICCO_FINE_2D)[2]
     want = _run(gpu, 256, 64 * 70, 256, 2, 1, ficco.FICCO_FINE_PERSISTENT)[2]
     assert torch.equal(C, want)
+
+
+def test_limit_counts_from_the_last_landing_across_batches(gpu):
+    """One long transfer after the other, the 64th and the 65th of a wait: the wavefront watches 64 pieces at a time, and the
+    landing that ends the first batch starts the limit anew for the second. Each of the two takes half of what the run
+    takes (measured first), the limit is three quarters of it: no piece is late, two together would be."""
+    dev, K = gpu["dev"], 4096
+    rows = [[8]] * 63 + [[1 << 16]] * 2
+    M = sum(r[0] for r in rows)
+    A = torch.randint(-1000, 1000, (M, K), dtype=torch.int16, device=dev).view(torch.bfloat16)
+    A_dev = torch.zeros_like(A)
+    W = torch.zeros((K, 8), dtype=torch.bfloat16, device=dev)
+    C = torch.zeros((M, 8), dtype=torch.bfloat16, device=dev)
+    torch.cuda.synchronize()
+    plan = ficco.ficco_plan_grouped(K, 8, rows, 1, ficco.FICCO_SHARD)
+    try:
+        ficco.ficco_plan_set(plan, ficco.FICCO_OPT_MODE, ficco.FICCO_MODE_COPY_ONLY)
+        for _ in range(3):
+            ficco.ficco_run(plan, A, A_dev, W, C, None, gpu["cs"], gpu["xs"])
+            wall_us = ficco.ficco_query_stats(plan).wall_us
+        print(f"two pieces of {rows[-1][0] * K * 2 >> 20} MiB in {wall_us:.0f} us", flush=True)
+        assert wall_us > 4000
+        ficco.ficco_plan_set(plan, ficco.FICCO_OPT_SPIN_LIMIT_US, int(wall_us * 0.75))
+        for _ in range(2):
+            ficco.ficco_run(plan, A, A_dev, W, C, None, gpu["cs"], gpu["xs"])
+            ficco.ficco_query_stats(plan)                    # raises if a wait has given up
+    finally:
+        ficco.ficco_destroy(plan)
+    assert torch.equal(A_dev.view(torch.int16), A.view(torch.int16))
