@@ -99,7 +99,8 @@ struct ficco_plan_s {
     bool finalized = false;
     int tile = 0;                        // of the latest run (select_tile); 0: none chosen yet
     int resident_grid = 0;
-    bool tile_for_pair = false, tile_whole_rows = false;   // what `tile` was chosen for
+    bool tile_for_pair = false, tile_whole_rows = false;   // what `tile` was chosen for ...
+    int tile_for_lists = 0;                                // ... and tile_col_lists at the time
     int losses_of = -1;                  // ficco_profile_losses: the mode whose tile the runs of the other modes take, too
     uint32_t *d_words = nullptr;         // flags | status | scratch: fine-grained device memory, polled while engines write it
     uint32_t *d_ticket_mem = nullptr;    // ticket counter: ordinary device memory (device-scope atomics)

@@ -135,11 +135,14 @@ int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
     double best = 1e300;
     int best_id = TILE_128x128;
     const double k_steps = (double)p->K / kBK;
+    const int lists = (is_resident(p) || p->grouped) && !(whole_rows && p->N <= 256) ? p->tile_col_lists : 0;
     for (auto &cd : cand) {
         TileShape ts = tile_shape(cd.id);
         if (whole_rows && p->N <= 256 && ts.bn < p->N) continue;
         const double cap = (double)cus * cd.occ;
         const int64_t tn = (p->N + ts.bn - 1) / ts.bn;
+        // column lists that the caller asks for must not depend on how wide a tile this rule happens to like
+        if (lists > tn && lists <= (p->N + 127) / 128) continue;
         auto cost = [&](int64_t tiles) {
             const double full = std::floor((double)tiles / cap), rem = (double)tiles - full * cap;
             const double steps = full * (cd.base + cd.slope) + (rem > 0 ? cd.base + cd.slope * rem / cap : 0.0);
@@ -232,13 +235,14 @@ int make_events(std::vector<hipEvent_t> &v, size_t n)
 // The tile and the resident grid of the run at hand. The mode may change from run to run and the rule with it: the order
 // in which a plan's modes are used must not decide which tile they get (M 8192, K 4096, N 768, two steps: the pair's tile
 // takes 59 us in a run of the GEMM alone, whose own takes 48, and that one costs the pair 6 us). So may the buffers: a
-// result over the activation (in_place) needs tiles that hold whole rows, or one stores what another still reads. Nothing
-// on the device depends on the tile but an expert-parallel plan's table of row tiles: there the rule does not ask for the
-// mode, and a weight that could be used in place gets such tiles from the start.
+// result over the activation (in_place) needs tiles that hold whole rows, or one stores what another still reads. So may
+// the column lists, which need as many column tiles. Nothing on the device depends on the tile but an expert-parallel
+// plan's table of row tiles: there the rule does not ask for the mode, a weight that could be used in place gets tiles of
+// whole rows from the start, and lists count if they were asked for before the first run.
 int select_tile(ficco_plan_t *p, bool in_place)
 {
     const bool pair = runs_pair(p), whole_rows = p->grouped ? p->K == p->N : in_place;
-    if (p->tile && (p->grouped || (pair == p->tile_for_pair && whole_rows == p->tile_whole_rows))) return FICCO_OK;
+    if (p->tile && (p->grouped || (pair == p->tile_for_pair && whole_rows == p->tile_whole_rows && p->tile_col_lists == p->tile_for_lists))) return FICCO_OK;
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
     const int tile = p->tile_opt ? p->tile_opt : choose_tile(p, cus, whole_rows);
@@ -256,6 +260,7 @@ int select_tile(ficco_plan_t *p, bool in_place)
     p->resident_grid = grid;
     p->tile_for_pair = pair;
     p->tile_whole_rows = whole_rows;
+    p->tile_for_lists = p->tile_col_lists;
     return FICCO_OK;
 }
 

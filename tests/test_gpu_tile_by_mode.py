@@ -69,3 +69,30 @@ def test_loss_profile_leaves_the_pair_its_tile(gpu, operands):
         assert _run(gpu, plan, PAIR, operands)[0] == pair
     finally:
         ficco.ficco_destroy(plan)
+
+
+@pytest.mark.parametrize("m,k,n,c,lists", [(16384, 512, 256, 2, 2), (4096, 512, 1024, 4, 8), (8192, 512, 768, 4, 4)])
+def test_column_lists_are_taken_wherever_a_tile_fits_them(gpu, m, k, n, c, lists):
+    """Shapes whose own tile is too wide for the lists: they are taken all the same, before the first run and after it, and
+    more lists than columns of the narrowest tile are refused."""
+    g = torch.Generator(device=gpu["dev"]).manual_seed(7)
+    ops = (torch.randn((m, k), generator=g, device=gpu["dev"]).bfloat16(), torch.randn((k, n), generator=g, device=gpu["dev"]).bfloat16())
+    ops += (torch.empty_like(ops[0]), torch.empty((m, n), dtype=torch.bfloat16, device=gpu["dev"]))
+    plans = [ficco.ficco_plan(m, k, n, 8, c, ficco.FICCO_FINE_PERSISTENT) for _ in range(2)]
+    try:
+        own, want = _run(gpu, plans[0], PAIR, ops)
+        assert -(-n // own[1]) < lists, "the shape's own tile fits the lists: take another one"
+        for plan in plans:
+            ficco.ficco_plan_set(plan, ficco.FICCO_OPT_TILE_COLUMN_LISTS, lists)
+            tile, out = _run(gpu, plan, PAIR, ops)
+            assert -(-n // tile[1]) >= lists
+            assert torch.equal(out, want)
+        ficco.ficco_plan_set(plans[0], ficco.FICCO_OPT_TILE_COLUMN_LISTS, 0)
+        assert _run(gpu, plans[0], PAIR, ops)[0] == own
+        if n == 256:
+            ficco.ficco_plan_set(plans[0], ficco.FICCO_OPT_TILE_COLUMN_LISTS, 4)
+            with pytest.raises(ficco.FiccoError):
+                _run(gpu, plans[0], PAIR, ops)
+    finally:
+        for plan in plans:
+            ficco.ficco_destroy(plan)
