@@ -62,6 +62,24 @@ struct TileCfg {
     static constexpr int WRAPPED = LOADS - loads_before(TT);   // loads that fall into the next turn
     // loads in flight at LAND that are younger than those of the next k-tile
     static constexpr int younger_at_land() { int n = 0; for (int e = 0; e + 2 <= NSTAGE; ++e) n += loads_before(LAND + e * TT); return n; }
+    // First and last slot of a half whose MFMA uses fragment q (row block 0, the column blocks, the other row blocks; column
+    // blocks go back and forth from row block to row block).
+    static constexpr int first_use(int q) { return q == 0 ? 0 : q <= FN ? q - 1 : (q - FN) * FN; }
+    static constexpr int last_use(int q)
+    {
+        return q == 0 ? FN - 1 : q <= FN ? (FM - 1) * FN + (FM % 2 ? q - 1 : FN - q) : (q - FN) * FN + FN - 1;
+    }
+    // A half's fragments are replaced behind their last MFMA and there before their first. (256x128 and 128x256 begin to
+    // read the next k-tile's first half three MFMAs before this one's is done with.)
+    static constexpr bool fragments_hold()
+    {
+        for (int q = 0; q < NR; ++q) {
+            const int r0 = R0 + q * RSTEP, r1 = R1 + q * RSTEP;
+            if (r0 < last_use(q) || (r0 >= TT && r0 - TT >= first_use(q)) || r1 >= NM + first_use(q)) return false;
+        }
+        return true;
+    }
+    static_assert(fragments_hold(), "a fragment is read too early or too late");
     static_assert(NSTAGE >= 2 && NSTAGE <= 6 && (NSTAGE - 1) * LOADS < 64, "ring of 2 to 6 stages, vmcnt has 6 bits");
     static_assert(LDS_BYTES <= 160 * 1024 - 64, "LDS ring plus the kernels' few static words must fit one CU");
     static_assert(THREADS == 256, "4 wavefronts");
