@@ -188,6 +188,8 @@ int build_lists(ficco_plan_t *p);
 // whole_rows: only tiles as wide as the output, where one is (N <= 256), so that a workgroup has read all it will read of
 // its rows of A before it stores them; us: the estimate for the tile chosen
 int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows = false, double *us = nullptr);
+// ficco_gemm_static: row blocks (1, 2 or 4) of the direct kernel, 0 = pack the weight first, which takes packed_us
+int direct_row_blocks(int64_t M, int64_t K, int64_t N, int cus, double packed_us);
 inline bool overlap(const void *a, int64_t a_bytes, const void *b, int64_t b_bytes)
 {
     return (uintptr_t)a < (uintptr_t)b + (uintptr_t)b_bytes && (uintptr_t)b < (uintptr_t)a + (uintptr_t)a_bytes;

@@ -35,6 +35,8 @@ int scratch_of(int dev, unsigned char **out)
     return FICCO_OK;
 }
 
+}  // namespace
+
 // Which way a call goes: 0 = pack the weight, then the resident GEMM; else one launch of the direct kernel on tiles of
 // 16 * row_blocks rows x 64 columns. The direct kernel needs no packed weight but fetches every operand row once per
 // narrow tile, so it wins where a launch is a round or two of its tiles and loses where the resident kernel's big tiles
@@ -56,7 +58,6 @@ int direct_row_blocks(int64_t M, int64_t K, int64_t N, int cus, double packed_us
     return best_id;
 }
 
-}  // namespace
 }  // namespace ficco
 
 using namespace ficco;

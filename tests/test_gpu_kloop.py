@@ -1,5 +1,5 @@
-"""The k loop at its shortest: k extents of one k-tile up to more than every ring holds, for every tile shape, on a
-ragged product. Against an fp64 product rounded once, within one bf16 step of the result (the fp32 sums of at most 576
+"""The k loop at its shortest: k extents of one k-tile up to more than every ring holds, for every tile that can be asked for
+(the 64x128 one has tests of its own), on a ragged product. Against an fp64 product rounded once, within one bf16 step of the result (the fp32 sums of at most 576
 terms are off by less than 576 * 2^-24 of the sum of magnitudes, far below half a step, so only a rounding that falls the
 other way is left), and bit for bit between the tile shapes."""
 import pytest

@@ -1,12 +1,39 @@
-"""The 64x128 tile, which the library picks for launches that leave CUs idle with every larger one, on row pieces,
-column pieces and the expert-parallel kernel, at the edges of the tile (one row, one column block, remainders, more k-tiles
-than its ring of six stages and fewer): bit for bit what a forced 256x256 tile gives. And that it stays the library's own
-choice: the option refuses it as before."""
+"""The 64x128 tile, which the library picks for launches that leave CUs idle with every larger one, in each kernel that has
+it - row pieces, column pieces, one launch per step, output streaming and expert-parallel - at the edges of the tile (one
+row, one column block, remainders) and with fewer k-tiles than its ring of six stages, as many and more: bit for bit what
+a forced 256x256 tile gives. And that it stays the library's own choice: the option refuses it as before."""
+import os
+import sys
+
 import pytest
 
 import paper_2512_10236_amd as ficco
 
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import internal
+
 torch = pytest.importorskip("torch")
+
+CASES = [
+    ("rows", 512, 1024, 1024, 4, 1), ("rows", 8, 1024, 136, 8, 1), ("rows", 8 * 65, 1088, 264, 8, 1), ("rows", 2 * 64 * 4, 4096, 128, 2, 4),
+    ("rows", 1024, 1024, 2040, 8, 2), ("rows", 16384, 256, 64, 1, 1), ("rows", 624, 256, 3088, 1, 1), ("rows", 624, 320, 3088, 1, 1),
+    ("rows", 624, 384, 3088, 1, 1), ("rows", 624, 448, 3088, 1, 1),
+    ("columns", 512, 1024, 1024, 4, 3), ("columns", 130, 1088, 776, 2, 2), ("columns", 624, 320, 3088, 2, 5),
+    ("fused", 520, 1088, 1032, 4, 1), ("fused", 624, 320, 3088, 2, 1),
+    ("scatter", 520, 1088, 1032, 8, 1), ("scatter", 624, 256, 3088, 2, 1),
+    ("experts", 700, 1024, 520, 4, 2)]
+SCHEDULE = dict(rows=ficco.FICCO_FINE_PERSISTENT, columns=ficco.FICCO_FINE_2D, fused=ficco.FICCO_FINE_FUSED, scatter=ficco.FICCO_FINE_PERSISTENT)
+
+
+def _plan(kind, M, K, N, G, c):
+    if kind == "experts":
+        rows = [[M // (2 * G)] * 2 for _ in range(G)]
+        rows[0][1] += M - sum(map(sum, rows))
+        return ficco.ficco_plan_grouped(K, N, rows, c, ficco.FICCO_FINE_PERSISTENT)
+    plan = ficco.ficco_plan(M, K, N, G, c, SCHEDULE[kind])
+    if kind == "scatter":
+        ficco.ficco_plan_set(plan, ficco.FICCO_OPT_DIRECTION, ficco.FICCO_DIR_GEMM_RS)
+    return plan
 
 
 def test_option_refuses_the_tile():
@@ -19,42 +46,47 @@ def test_option_refuses_the_tile():
         ficco.ficco_destroy(plan)
 
 
-def _run(gpu, make, tile, A, W, M, N):
-    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=gpu["dev"])
-    A_dev = torch.full_like(A, float("nan"))
+@pytest.mark.parametrize("kind,M,K,N,G,c", CASES)
+def test_rule_picks_the_tile(kind, M, K, N, G, c):
+    plan = _plan(kind, M, K, N, G, c)
+    try:
+        assert internal.choose_tile(plan)[0] == (64, 128)
+    finally:
+        ficco.ficco_destroy(plan)
+
+
+def _run(gpu, case, tile, A, W):
+    kind, M, K, N, G, c = case
+    dev = gpu["dev"]
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=dev)
+    rs = kind == "scatter"
+    A_dev = A if rs else torch.full_like(A, float("nan"))
+    peers = [torch.full((M // G, N), float("nan"), dtype=torch.bfloat16, device=dev) for _ in range(G)] if rs else None
     torch.cuda.synchronize()
-    plan = make()
+    plan = _plan(*case)
     try:
         ficco.ficco_plan_set(plan, ficco.FICCO_OPT_TILE, tile)
         for _ in range(2):
-            ficco.ficco_run(plan, A, A_dev, W, C, None, gpu["cs"], gpu["xs"])
+            ficco.ficco_run(plan, None if rs else A, A_dev, W, C, peers, gpu["cs"], gpu["xs"])
             ficco.ficco_query_stats(plan)
         info = ficco.ficco_plan_info(plan)
     finally:
         ficco.ficco_destroy(plan)
+    if rs:
+        assert torch.equal(torch.cat(peers).view(torch.int16), C.view(torch.int16))
     return C, (info.tile_m, info.tile_n)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("kind,M,K,N,G,c", [
-    ("rows", 512, 1024, 1024, 4, 1), ("rows", 8, 1024, 136, 8, 1), ("rows", 8 * 65, 1088, 264, 8, 1), ("rows", 2 * 64 * 4, 4096, 128, 2, 4),
-    ("rows", 64, 384, 768, 1, 1), ("rows", 1024, 1024, 2040, 8, 2), ("columns", 512, 1024, 1024, 4, 3), ("columns", 130, 1088, 776, 2, 2),
-    ("experts", 700, 1024, 520, 4, 2)])
-def test_small_tile_has_the_bits_of_the_large_one(gpu, kind, M, K, N, G, c):
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-%dx%dx%d-%dx%d" % c)
+def test_small_tile_has_the_bits_of_the_large_one(gpu, case):
+    kind, M, K, N, G, c = case
     g = torch.Generator(device=gpu["dev"]).manual_seed(M + K + N)
     A = torch.randn((M, K), generator=g, device=gpu["dev"]).bfloat16()
     W = torch.randn((2 * K if kind == "experts" else K, N), generator=g, device=gpu["dev"]).bfloat16()
-    if kind == "experts":
-        rows = [[M // (2 * G)] * 2 for _ in range(G)]
-        rows[0][1] += M - sum(map(sum, rows))
-        make = lambda: ficco.ficco_plan_grouped(K, N, rows, c, ficco.FICCO_FINE_PERSISTENT)
-    else:
-        make = lambda: ficco.ficco_plan(M, K, N, G, c, ficco.FICCO_FINE_PERSISTENT if kind == "rows" else ficco.FICCO_FINE_2D)
     print(f"small tile {kind} {M}x{K}x{N} {G}x{c}", flush=True)
-    got, tile = _run(gpu, make, ficco.FICCO_TILE_AUTO, A, W, M, N)
-    want, _ = _run(gpu, make, ficco.FICCO_TILE_256x256, A, W, M, N)
+    got, tile = _run(gpu, case, ficco.FICCO_TILE_AUTO, A, W)
+    want, _ = _run(gpu, case, ficco.FICCO_TILE_256x256, A, W)
     assert not torch.isnan(want.float()).any()
     assert torch.equal(got, want)
-    assert tile[1] in (128, 256) and tile[0] <= 128, tile
-    if (M, K, N) == (512, 1024, 1024):
-        assert tile == (64, 128)
+    assert tile == (64, 128)
