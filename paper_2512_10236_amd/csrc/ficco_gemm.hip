@@ -452,8 +452,8 @@ __global__ __launch_bounds__(T::THREADS) void gemm_blocks_kernel(GemmLaunch a)
 // several row tiles of the step times a run of columns, as a launch over the step's pieces would.
 //
 // TileWalk hands a workgroup its next (list, tile) pair. The first `rounds` tiles of its home list are the workgroup's
-// by its rank among the workgroups that start there (no memory access; often that is all of them, see static_rounds);
-// later tiles are drawn from the list's counter. Before it turns to the other lists it reads their counters once, all
+// by its rank among the workgroups that start there (no memory access), and short launches have all their tiles that way
+// (hand_out); later tiles are drawn from the list's counter. Before it turns to the other lists it reads their counters once, all
 // loads in flight together: on a list that is already used up it only leaves its one past-the-end draw (an atomic
 // whose result nobody waits for), and a list that the ranks of its own workgroups cover completely is never drawn from
 // at all. Counter traffic is what a launch pays at its end, since a draw goes to memory shared by all XCDs.
@@ -469,10 +469,11 @@ struct TileWalk {
 // start with one) and returns 1 with the raw counter value in `drawn`; the caller puts this before
 // work whose duration then hides the draw's round trip. Returns 0 when the next step is not a plain draw.
 template <class TotalFn>
-static __device__ __forceinline__ int tile_walk_predraw(const TileWalk &w, uint32_t *ticket, int grid, int rounds, TotalFn total_of,
+static __device__ __forceinline__ int tile_walk_predraw(const TileWalk &w, uint32_t *ticket, int grid, HandOut out, TotalFn total_of,
                                                         uint32_t &drawn)
 {
-    if (w.turn >= kTicketLists || (w.turn == 0 && w.taken < rounds)) return 0;
+    const int rounds = out.rounds;
+    if (out.by_rank || w.turn >= kTicketLists || (w.turn == 0 && w.taken < rounds)) return 0;
     const int y = (blockIdx.x + w.turn) % kTicketLists;
     if (total_of(y) <= rounds * resident_list_homes(grid, y)) return 0;
     if (w.turn > 0 && (!w.looked || ((w.spent >> w.turn) & 1))) return 0;
@@ -481,11 +482,16 @@ static __device__ __forceinline__ int tile_walk_predraw(const TileWalk &w, uint3
 }
 
 template <class TotalFn>
-static __device__ __forceinline__ void tile_walk_next(TileWalk &w, uint32_t *ticket, const uint32_t *base, int grid, int rounds,
+static __device__ __forceinline__ void tile_walk_next(TileWalk &w, uint32_t *ticket, const uint32_t *base, int grid, HandOut out,
                                                       TotalFn total_of, int have_drawn = 0, uint32_t drawn = 0)
 {
-    const int home = blockIdx.x % kTicketLists, rank = blockIdx.x / kTicketLists;
+    const int home = blockIdx.x % kTicketLists, rank = blockIdx.x / kTicketLists, rounds = out.rounds;
     w.x = -1;
+    if (out.by_rank) {
+        if (w.taken < rounds && !tile_by_rank(home, rank, w.taken, grid, rounds, total_of, w.x, w.t)) w.taken = rounds;
+        ++w.taken;
+        return;
+    }
     while (w.turn < kTicketLists) {
         const int y = (home + w.turn) % kTicketLists;
         const int total = total_of(y), homes = resident_list_homes(grid, y);
@@ -611,7 +617,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
     for (;;) {
         if (threadIdx.x == 0) {
             TileWalk w = s_walk;
-            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.rounds, total_of, have_drawn, drawn);
+            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.out, total_of, have_drawn, drawn);
             have_drawn = 0;
             int ok = 1;
             if (w.x >= 0) {
@@ -644,7 +650,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
             else
                 tile_accumulate<T>(ta, a.A + row0 * a.lda, rows_valid, a.Wt + (int64_t)col0 * a.K, cols_valid, a.lda, a.K, a.K, smem);
             // the next ticket's round trip runs under the epilogue
-            if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.rounds, total_of, drawn);
+            if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.out, total_of, drawn);
             if constexpr (STREAM_OUT) {
                 tile_store<T, true>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
                 stored_chunk = chunk;
@@ -683,7 +689,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
     for (;;) {
         if (threadIdx.x == 0) {
             TileWalk w = s_walk;
-            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.rounds, total_of, have_drawn, drawn);
+            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.out, total_of, have_drawn, drawn);
             have_drawn = 0;
             s_walk = w;
         }
@@ -728,7 +734,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
                 sl = run_end;
             }
         }
-        if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.rounds, total_of, drawn);
+        if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.out, total_of, drawn);
         if (ok) tile_store<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused
     }
@@ -759,7 +765,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
             TileWalk w{};
             if (threadIdx.x == 0) {
                 w = s_walk;
-                tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.rounds, total_of, have_drawn, drawn);
+                tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.out, total_of, have_drawn, drawn);
                 have_drawn = 0;
                 s_walk = w;
             }
@@ -790,7 +796,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
             tile_zero(ta);
             tile_accumulate<T>(ta, a.A + row0 * a.lda, rows_valid, a.Wt + (expert * a.N + col0) * (int64_t)a.K, cols_valid,
                                a.lda, a.K, a.K, smem);
-            if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.rounds, total_of, drawn);
+            if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.out, total_of, drawn);
             tile_store<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
         }
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused

@@ -80,35 +80,62 @@ __host__ inline double tile_order_cost(int bm, int bn, int64_t tn, int64_t row_t
 // Workgroups of a resident launch whose first list is x (workgroup b starts on list b % kTicketLists).
 __host__ __device__ inline int resident_list_homes(int grid, int x) { return grid > x ? (grid - x + kTicketLists - 1) / kTicketLists : 0; }
 
-// A workgroup takes the first `rounds` of its home list's tiles by its rank there (rank, rank + homes, rank + 2 homes, ...)
-// without touching memory; later tiles are drawn from the list's counter, and when the home list is used up from the
-// other lists' (tile_walk_next). A draw is a round trip of 3-4 us to memory that all XCDs share, and a launch that
-// needs draws pays two or three of them at its end (two rounds of 32x256 tiles by rank instead of by draws: M 2048, K 1024,
-// N 4096 45.7 -> 34.6 us, M 9600, K 512, N 256 17.0 -> 13.7 us; nothing on launches of 200 us and more), so everything goes by rank where that is as good: the lists are even enough that no workgroup takes more tiles
-// than sharing all of them out evenly would ask for, and the launch is short enough that workgroups do not drift apart.
-// Long launches draw their last quarter, uneven ones everything after the first round.
-constexpr int kStaticRounds = 8;
-__host__ inline int static_rounds(int64_t row_tiles, int64_t tiles_n, int col_lists, int grid)
+// How a resident launch hands out its tiles. A draw from a list's counter is a round trip of 3-4 us to memory that all
+// XCDs share, and at the end of a launch every workgroup makes one on every list that has counters in use. So:
+//   short launches (up to kStaticRounds tiles per workgroup; by_rank) use no counters. A workgroup has `rounds` places on
+//     its home list, rank, rank + homes, rank + 2 homes, ... Where the list is shorter than its places, the spare ones,
+//     counted over all lists, take the tiles that the longer lists have too many, counted the same way (tile_by_rank).
+//     There are always enough: rounds * grid >= all tiles.
+//   longer ones let workgroups drift apart: the first three quarters of a workgroup's share of its home list go by rank,
+//     or one tile where the lists are uneven, and the rest is drawn (tile_walk_next).
+// By rank instead of by draws, even lists: M 2048, K 1024, N 4096 45.7 -> 34.6 us, M 9600, K 512, N 256 17.0 -> 13.7; uneven
+// ones: M 2654, K 640, N 3008 40.4 -> 18.0, M 7397, K 320, N 3088 58.0 -> 28.6. The line between the two, launches of 9 to 16
+// tiles a workgroup by rank against by draws: M 19089, K 128, N 4144 54.9 : 94.5, M 16384, K 1024, N 10240 333 : 346, M 20480,
+// K 2048, N 9216 643 : 633, M 12288, K 4096, N 16384 and M 16384, K 8192, N 9728 the same.
+constexpr int kStaticRounds = 16;
+struct HandOut { int rounds, by_rank; };
+__host__ inline HandOut hand_out(int64_t row_tiles, int64_t tiles_n, int col_lists, int grid)
 {
     int64_t most = 1, total = 0;
+    bool all_started = true;
     for (int x = 0; x < kTicketLists; ++x) {
         const int64_t t = resident_list_tiles(row_tiles, tiles_n, x, col_lists), h = resident_list_homes(grid, x);
         total += t;
-        if (t > 0 && h == 0) return 1;                      // a list nobody starts on
+        if (t > 0 && h == 0) all_started = false;           // a list nobody starts on
         if (h > 0 && (t + h - 1) / h > most) most = (t + h - 1) / h;
     }
     const int64_t even = (total + grid - 1) / grid;
-    if (most > even) return 1;
-    return (int)(even <= kStaticRounds ? even : even * 3 / 4);
+    if (even <= kStaticRounds) return {(int)even, 1};
+    return {(int)(all_started && most <= even ? even * 3 / 4 : 1), 0};
 }
 
-// Atomic draws one resident launch makes on list x's counter: none if the ranks of its own workgroups cover the list;
-// otherwise every later tile is drawn and every workgroup draws exactly one ticket past the end of the list. The host
-// advances its copy of each counter by this much per launch, so counters are never reset.
-__host__ __device__ inline uint32_t resident_list_draws(int64_t list_tiles, int grid, int x, int rounds)
+// by_rank: the tile of place `taken` of the workgroup of this rank on list `home`; false: none, nor any further on.
+template <class TotalFn>
+__host__ __device__ inline bool tile_by_rank(int home, int rank, int taken, int grid, int rounds, TotalFn total_of, int &x, int &t)
 {
-    const int64_t by_rank = (int64_t)rounds * resident_list_homes(grid, x);
-    return list_tiles > by_rank ? (uint32_t)(list_tiles - by_rank + grid) : 0u;
+    const int place = rank + taken * resident_list_homes(grid, home), total = total_of(home);
+    if (place < total) { x = home; t = place; return true; }
+    int spare = place - total;
+    for (int k = 0; k < home; ++k) {
+        const int left = rounds * resident_list_homes(grid, k) - total_of(k);
+        if (left > 0) spare += left;
+    }
+    for (int k = 0; k < kTicketLists; ++k) {
+        const int places = rounds * resident_list_homes(grid, k), over = total_of(k) - places;
+        if (over <= 0) continue;
+        if (spare < over) { x = k; t = places + spare; return true; }
+        spare -= over;
+    }
+    return false;
+}
+
+// Atomic draws one resident launch makes on list x's counter: none by rank, nor if the ranks of its own workgroups cover
+// the list; otherwise every later tile is drawn and every workgroup draws exactly one ticket past the end of the list. The
+// host advances its copy of each counter by this much per launch, so counters are never reset.
+__host__ __device__ inline uint32_t resident_list_draws(int64_t list_tiles, int grid, int x, HandOut h)
+{
+    const int64_t taken = (int64_t)h.rounds * resident_list_homes(grid, x);
+    return !h.by_rank && list_tiles > taken ? (uint32_t)(list_tiles - taken + grid) : 0u;
 }
 
 // How a kernel learns that piece `chunk` has landed:
@@ -163,7 +190,8 @@ struct ResidentLaunch {
     int32_t n_chunks;
     uint32_t *ticket;             // device, kTicketLists counters kFlagStrideWords apart, monotonically increasing across runs
     uint32_t ticket_base[8];      // value of each counter when this run starts
-    int32_t grid, rounds;         // workgroups; tiles each takes by rank (static_rounds)
+    int32_t grid;                 // workgroups
+    HandOut out;
     int32_t group;                // row tiles per group of a list's tile order (1..8)
     int32_t col_lists;            // column blocks the lists are split into (1, 2, 4 or 8; see resident_list_tiles)
     int32_t local_chunk_begin, local_chunk_end;   // chunk ids that need no flag (already resident), or empty
@@ -186,7 +214,8 @@ struct Resident2DLaunch {
     const int32_t *k0;            // device, slices + 1 entries: first column of each slice, then K (multiples of the k-tile)
     uint32_t *ticket;
     uint32_t ticket_base[8];
-    int32_t grid, rounds;
+    int32_t grid;
+    HandOut out;
     int32_t gated;                // 0: operands resident, no waiting
     int32_t group, col_lists;     // tile order, as in ResidentLaunch
     RunExit leave;
@@ -218,7 +247,8 @@ struct GroupedLaunch {
     int32_t n_row_tiles;
     uint32_t *ticket;
     uint32_t ticket_base[8];
-    int32_t grid, rounds;
+    int32_t grid;
+    HandOut out;
     int32_t gated;
     int32_t group, col_lists;     // tile order, as in ResidentLaunch
 };

@@ -213,10 +213,10 @@ inline void book_tickets(ficco_plan_t *p, Launch &r, const ListGeometry &lg, int
     r.grid = grid;
     r.group = lg.group;
     r.col_lists = lg.col_lists;
-    r.rounds = static_rounds(row_tiles, tn, lg.col_lists, grid);
+    r.out = hand_out(row_tiles, tn, lg.col_lists, grid);
     for (int x = 0; x < kTicketLists; ++x) {
         r.ticket_base[x] = p->ticket_total[x];
-        p->ticket_total[x] += resident_list_draws(resident_list_tiles(row_tiles, tn, x, lg.col_lists), grid, x, r.rounds);
+        p->ticket_total[x] += resident_list_draws(resident_list_tiles(row_tiles, tn, x, lg.col_lists), grid, x, r.out);
     }
 }
 int launch_2d(ficco_plan_t *p, const Gate &gate, bool gated, int grid, const void *A_dev, void *C_dev, hipStream_t cs,
