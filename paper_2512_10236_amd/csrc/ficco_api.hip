@@ -229,7 +229,7 @@ int ficco_run(ficco_plan_t *p, const void *A_src, void *A_dev, const void *W_dev
                 else if (p->local_shard >= 0) { r.local_chunk_begin = p->local_shard * c; r.local_chunk_end = (p->local_shard + 1) * c; }
                 else { r.local_chunk_begin = 0; r.local_chunk_end = 0; }
                 TileShape ts = tile_shape(p->tile);
-                book_tickets(p, r, lg, (int64_t)n * ((p->m + ts.bm - 1) / ts.bm), (p->N + ts.bn - 1) / ts.bn, grid);
+                book_tickets(p, r, lg, (int64_t)n * ((p->m + ts.bm - 1) / ts.bm), (p->N + ts.bn - 1) / ts.bn, grid, dependent && do_copy);
                 HIP_TRY(launch_resident(p->tile, r, cs));
             }
             ++n_launches;

@@ -311,7 +311,7 @@ int run_grouped(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, hi
         const ListGeometry lg = pick_lists(p, ts, tn, p->n_row_tiles, std::max<int64_t>(1, p->n_row_tiles / std::max(p->c, 1)), p->resident_grid / kTicketLists,
                                            p->M * p->K * 2, (int64_t)p->E * p->N * p->K * 2);
         if (!lg.col_lists) return FICCO_ERR_ARG;
-        book_tickets(p, r, lg, p->n_row_tiles, tn, p->resident_grid);
+        book_tickets(p, r, lg, p->n_row_tiles, tn, p->resident_grid, r.gated != 0);
         HIP_TRY(launch_grouped(p->tile, r, cs));
         ++n_launches;
     }
@@ -678,7 +678,7 @@ int run_engines(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, vo
                 if (!dependent) { r.local_chunk_begin = 0; r.local_chunk_end = n; }
                 else if (p->local_shard >= 0) { r.local_chunk_begin = p->local_shard * c; r.local_chunk_end = (p->local_shard + 1) * c; }
                 TileShape ts = tile_shape(p->tile);
-                book_tickets(p, r, lg, (int64_t)n * ((p->m + ts.bm - 1) / ts.bm), (p->N + ts.bn - 1) / ts.bn, p->resident_grid);
+                book_tickets(p, r, lg, (int64_t)n * ((p->m + ts.bm - 1) / ts.bm), (p->N + ts.bn - 1) / ts.bn, p->resident_grid, dependent);
                 if (timing) HIP_TRY(hipEventRecord(p->ev_gemm_b[0], cs));
                 HIP_TRY(launch_resident(p->tile, r, cs));
                 if (release_in_kernel) p->exit_total += (uint32_t)p->resident_grid;
@@ -742,7 +742,7 @@ int run_engines(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, vo
             r.done_count = p->d_done_count;
             r.done_sig = p->d_done_value;
             r.tiles_per_chunk = (int32_t)(rt * tn);
-            book_tickets(p, r, lg, (int64_t)n * rt, tn, p->resident_grid);
+            book_tickets(p, r, lg, (int64_t)n * rt, tn, p->resident_grid, false);
             HIP_TRY(launch_resident(p->tile, r, cs));
             ++n_launches;
         }

@@ -82,19 +82,22 @@ __host__ __device__ inline int resident_list_homes(int grid, int x) { return gri
 
 // How a resident launch hands out its tiles. A draw from a list's counter is a round trip of 3-4 us to memory that all
 // XCDs share, and at the end of a launch every workgroup makes one on every list that has counters in use. So:
-//   short launches (up to kStaticRounds tiles per workgroup; by_rank) use no counters. A workgroup has `rounds` places on
-//     its home list, rank, rank + homes, rank + 2 homes, ... Where the list is shorter than its places, the spare ones,
-//     counted over all lists, take the tiles that the longer lists have too many, counted the same way (tile_by_rank).
-//     There are always enough: rounds * grid >= all tiles.
+//   short launches (by_rank) use no counters. A workgroup has `rounds` places on its home list, rank, rank + homes, rank +
+//     2 homes, ... Where the list is shorter than its places, the spare ones, counted over all lists, take the tiles that the
+//     longer lists have too many, counted the same way (tile_by_rank). There are always enough: rounds * grid >= all tiles.
 //   longer ones let workgroups drift apart: the first three quarters of a workgroup's share of its home list go by rank,
 //     or one tile where the lists are uneven, and the rest is drawn (tile_walk_next).
 // By rank instead of by draws, even lists: M 2048, K 1024, N 4096 45.7 -> 34.6 us, M 9600, K 512, N 256 17.0 -> 13.7; uneven
 // ones: M 2654, K 640, N 3008 40.4 -> 18.0, M 7397, K 320, N 3088 58.0 -> 28.6. The line between the two, launches of 9 to 16
 // tiles a workgroup by rank against by draws: M 19089, K 128, N 4144 54.9 : 94.5, M 16384, K 1024, N 10240 333 : 346, M 20480,
 // K 2048, N 9216 643 : 633, M 12288, K 4096, N 16384 and M 16384, K 8192, N 9728 the same.
-constexpr int kStaticRounds = 16;
+// Where tiles wait for pieces (waits), a workgroup that is held up by a late piece must not hold a second tile that another
+// one could take: uneven lists go by rank only where every workgroup has one place (pairs and experts of two to five rounds
+// by rank against by draws: M 7936, K 14080, N 6216 2264 : 2134, experts 5922x6400x2816 547 : 515, 22858x4928x1744 1080 : 1038),
+// even ones up to 8.
+constexpr int kStaticRounds = 16, kStaticRoundsWaiting = 8;
 struct HandOut { int rounds, by_rank; };
-__host__ inline HandOut hand_out(int64_t row_tiles, int64_t tiles_n, int col_lists, int grid)
+__host__ inline HandOut hand_out(int64_t row_tiles, int64_t tiles_n, int col_lists, int grid, bool waits)
 {
     int64_t most = 1, total = 0;
     bool all_started = true;
@@ -105,8 +108,9 @@ __host__ inline HandOut hand_out(int64_t row_tiles, int64_t tiles_n, int col_lis
         if (h > 0 && (t + h - 1) / h > most) most = (t + h - 1) / h;
     }
     const int64_t even = (total + grid - 1) / grid;
-    if (even <= kStaticRounds) return {(int)even, 1};
-    return {(int)(all_started && most <= even ? even * 3 / 4 : 1), 0};
+    const bool evenly = all_started && most <= even;
+    if (even <= (!waits ? kStaticRounds : evenly ? kStaticRoundsWaiting : 1)) return {(int)even, 1};
+    return {(int)(evenly ? even * 3 / 4 : 1), 0};
 }
 
 // by_rank: the tile of place `taken` of the workgroup of this rank on list `home`; false: none, nor any further on.

@@ -205,15 +205,16 @@ GemmLaunch make_launch(const ficco_plan_t *p, const Group &g, const void *A_dev,
 ListGeometry pick_lists(const ficco_plan_t *p, const TileShape &ts, int64_t tn, int64_t row_tiles, int64_t S, int64_t slots,
                         int64_t a_bytes, int64_t w_bytes);
 ListGeometry resident_lists(const ficco_plan_t *p);
-// Fills the tile order and ticket fields of a resident launch over row_tiles x tn tiles and books its draws.
+// Fills the tile order and ticket fields of a resident launch over row_tiles x tn tiles and books its draws. waits: its
+// tiles wait for pieces.
 template <class Launch>
-inline void book_tickets(ficco_plan_t *p, Launch &r, const ListGeometry &lg, int64_t row_tiles, int64_t tn, int grid)
+inline void book_tickets(ficco_plan_t *p, Launch &r, const ListGeometry &lg, int64_t row_tiles, int64_t tn, int grid, bool waits)
 {
     r.ticket = p->d_ticket;
     r.grid = grid;
     r.group = lg.group;
     r.col_lists = lg.col_lists;
-    r.out = hand_out(row_tiles, tn, lg.col_lists, grid);
+    r.out = hand_out(row_tiles, tn, lg.col_lists, grid, waits);
     for (int x = 0; x < kTicketLists; ++x) {
         r.ticket_base[x] = p->ticket_total[x];
         p->ticket_total[x] += resident_list_draws(resident_list_tiles(row_tiles, tn, x, lg.col_lists), grid, x, r.out);

@@ -470,7 +470,7 @@ int launch_2d(ficco_plan_t *p, const Gate &gate, bool gated, int grid, const voi
     // column pieces: every tile can start with the first step, so any group height goes
     const ListGeometry lg = pick_lists(p, ts, tn, row_tiles, row_tiles, grid / kTicketLists, p->M * p->K * 2, p->N * p->K * 2);
     if (!lg.col_lists) return FICCO_ERR_ARG;
-    book_tickets(p, r, lg, row_tiles, tn, grid);
+    book_tickets(p, r, lg, row_tiles, tn, grid, gated);
     HIP_TRY(launch_resident2d(p->tile, r, cs));
     if (release_addr) p->exit_total += (uint32_t)grid;      // counted only once the workgroups are on their way
     return FICCO_OK;

@@ -142,7 +142,7 @@ extern "C" int ficco_gemm_static(int64_t M, int64_t K, int64_t N, const void *A_
     r.grid = grid;
     r.group = lg.group;
     r.col_lists = lg.col_lists;
-    r.out = hand_out(row_tiles, tn, lg.col_lists, grid);
+    r.out = hand_out(row_tiles, tn, lg.col_lists, grid, false);
     r.local_chunk_begin = 0;
     r.local_chunk_end = 1;
     HIP_TRY(launch_resident(shape.tile, r, s));

@@ -1,6 +1,7 @@
 """How a short resident launch hands out its tiles, on the CPU: a small program built from the library's own header walks
 every workgroup's places over lists that are even, uneven, empty or started by nobody. Every tile is taken exactly once,
-by no workgroup more than its share, and no counter is booked; longer launches book the draws that their lists need."""
+by no workgroup more than its share, and no counter is booked; where tiles wait for pieces, nobody takes a tile of another
+list behind one of its own. Longer launches book the draws that their lists need."""
 import os
 import subprocess
 
@@ -20,16 +21,18 @@ static int bad(const char *what, int64_t rt, int64_t tn, int cl, int grid)
     return 1;
 }
 
-static int check(int64_t rt, int64_t tn, int cl, int grid)
+static int check(int64_t rt, int64_t tn, int cl, int grid, bool waits)
 {
-    const HandOut h = hand_out(rt, tn, cl, grid);
+    const HandOut h = hand_out(rt, tn, cl, grid, waits);
     auto total_of = [&](int x) { return (int)resident_list_tiles(rt, tn, x, cl); };
     int64_t draws = 0, all = 0;
     for (int x = 0; x < kTicketLists; ++x) { draws += resident_list_draws(total_of(x), grid, x, h); all += total_of(x); }
     if (all != rt * tn) return bad("lists", rt, tn, cl, grid);
-    if (h.by_rank != (all <= (int64_t)kStaticRounds * grid)) return bad("by rank", rt, tn, cl, grid);
+    if (all <= grid ? !h.by_rank : all > (int64_t)kStaticRounds * grid ? h.by_rank : !waits && !h.by_rank) return bad("by rank", rt, tn, cl, grid);
     if (!h.by_rank) return h.rounds >= 1 && draws > 0 ? 0 : bad("draws", rt, tn, cl, grid);
     if (draws) return bad("draws by rank", rt, tn, cl, grid);
+    for (int x = 0; x < kTicketLists; ++x)       // a tile that waits for its piece holds up no second one from another list
+        if (waits && h.rounds > 1 && total_of(x) > h.rounds * resident_list_homes(grid, x)) return bad("uneven", rt, tn, cl, grid);
     std::vector<std::vector<int>> seen(kTicketLists);
     for (int x = 0; x < kTicketLists; ++x) seen[x].assign(total_of(x), 0);
     int64_t n = 0;
@@ -55,8 +58,8 @@ int main()
                 if (cl > tn) continue;
                 for (int slots : {1, 5, 8, 248, 256, 512}) {
                     const int grid = (int)(rt * tn < slots ? rt * tn : slots);
-                    if (check(rt, tn, cl, grid)) return 1;
-                    ++n;
+                    if (check(rt, tn, cl, grid, false) || check(rt, tn, cl, grid, true)) return 1;
+                    n += 2;
                 }
             }
     printf("%d launches\n", n);
