@@ -76,3 +76,32 @@ def test_limit_counts_from_the_last_landing_across_batches(gpu):
     finally:
         ficco.ficco_destroy(plan)
     assert torch.equal(A_dev.view(torch.int16), A.view(torch.int16))
+
+
+@pytest.mark.parametrize("big", [0, 7, 15])
+def test_tile_that_waits_for_128_pieces(gpu, big):
+    """One row tile per expert over 16 peers x 8 steps of ragged pieces, one peer's far larger than the others: the pieces of a
+    tile's two batches land in another order than they are listed in."""
+    dev, K, N = gpu["dev"], 1024, 264
+    rows = [[13 if j == big else 1 + (j + e) % 3 for e in range(2)] for j in range(16)]
+    rows[big][1] = 6000
+    M = sum(map(sum, rows))
+    g = torch.Generator(device=dev).manual_seed(big)
+    A = torch.randn((M, K), generator=g, device=dev).bfloat16()
+    W = torch.randn((2 * K, N), generator=g, device=dev).bfloat16()
+    out = []
+    for c, schedule in ((8, ficco.FICCO_FINE_PERSISTENT), (1, ficco.FICCO_SERIAL)):
+        A_dev = torch.full((M, K), float("nan"), dtype=torch.bfloat16, device=dev)
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=dev)
+        torch.cuda.synchronize()
+        plan = ficco.ficco_plan_grouped(K, N, rows, c, schedule)
+        try:
+            print(f"experts, {c} pieces a peer, peer {big} the largest", flush=True)
+            for _ in range(2):
+                ficco.ficco_run(plan, A, A_dev, W, C, None, gpu["cs"], gpu["xs"])
+                ficco.ficco_query_stats(plan)
+        finally:
+            ficco.ficco_destroy(plan)
+        out.append(C)
+    assert not torch.isnan(out[1].float()).any()
+    assert torch.equal(out[0], out[1])
