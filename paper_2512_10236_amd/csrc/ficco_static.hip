@@ -86,6 +86,7 @@ extern "C" int ficco_gemm_static(int64_t M, int64_t K, int64_t N, const void *A_
     shape.M = M; shape.K = K; shape.N = N; shape.G = 1; shape.c = 1;
     shape.schedule = FICCO_FINE_PERSISTENT;
     shape.order = FICCO_ORDER_STEP_MAJOR;
+    shape.mode = FICCO_MODE_GEMM_ONLY;
     if ((rc = build_lists(&shape))) return rc;
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));

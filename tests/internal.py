@@ -23,6 +23,7 @@ def direct_row_blocks(M, K, N):
     f.argtypes, f.restype = [C.c_int64, C.c_int64, C.c_int64, C.c_int, C.c_double], C.c_int
     plan = ficco.ficco_plan(M, K, N, 1, 1, ficco.FICCO_FINE_PERSISTENT)
     try:
+        ficco.ficco_plan_set(plan, ficco.FICCO_OPT_MODE, ficco.FICCO_MODE_GEMM_ONLY)
         return f(M, K, N, CUS, choose_tile(plan)[1])
     finally:
         ficco.ficco_destroy(plan)

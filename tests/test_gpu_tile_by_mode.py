@@ -8,7 +8,7 @@ import paper_2512_10236_amd as ficco
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-M, K, N, G, C = 8192, 1024, 768, 8, 2
+M, K, N, G, C = 8192, 4096, 768, 8, 2
 PAIR, ALONE, BOTH = ficco.FICCO_MODE_PAIR, ficco.FICCO_MODE_GEMM_ONLY, ficco.FICCO_MODE_INDEPENDENT
 
 
@@ -71,7 +71,7 @@ def test_loss_profile_leaves_the_pair_its_tile(gpu, operands):
         ficco.ficco_destroy(plan)
 
 
-@pytest.mark.parametrize("m,k,n,c,lists", [(16384, 512, 256, 2, 2), (4096, 512, 1024, 4, 8), (8192, 512, 768, 4, 4)])
+@pytest.mark.parametrize("m,k,n,c,lists", [(1024, 512, 256, 1, 2), (32768, 512, 512, 1, 4), (1024, 1024, 1536, 4, 8)])
 def test_column_lists_are_taken_wherever_a_tile_fits_them(gpu, m, k, n, c, lists):
     """Shapes whose own tile is too wide for the lists: they are taken all the same, before the first run and after it, and
     more lists than columns of the narrowest tile are refused."""
