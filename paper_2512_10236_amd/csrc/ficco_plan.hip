@@ -121,25 +121,26 @@ static bool runs_pair(const ficco_plan_t *p) { return (p->losses_of >= 0 ? p->lo
 // k-step of that tile shape when a fraction f of the machine's workgroup slots is occupied. Fitted to resident launches
 // over M 64-16384, K 1024 and 4096, N 256-7168 (132 shapes x 10 tiles, 4-10 % rms): the tile picked is 0.9 % slower than
 // the fastest on average, where the constants of the kernels' earlier k loop, without the 64x128 tile, were 8 % slower.
-// Beside transfers the full-machine cost of 256x128 and 256x192 is 4-5 % above that (all-gather pairs, 256x256 / 256x192 /
-// 256x128 / 128x256: M 16384, K 8192, N 3584 830 / 947 / 995 / 852 us, M 8192, K 8192, N 4096 518 / 566 / 553 / 520, M 6144,
-// K 4096, N 4096 267 / 290 / 311 / 254); alone they are faster by 2.7 % on average at 26 shapes where the line lies.
+// The full-machine cost of 256x128 and 256x192 is set 4-5 % above the fit, which holds for its K of up to 4096. Longer
+// launches, and above all pairs, lose more (us, 256x256 / 256x192 / 256x128 / 128x256; alone: M 16384, K 8192, N 3584 675 / 700 /
+// 720 / 705, M 16384, K 16384, N 3584 1349 / 1467 / 1434 / 1423; pairs over eight shards: M 16384, K 8192, N 3584 830 / 947 / 995 /
+// 852, M 8192, K 8192, N 4096 518 / 566 / 553 / 520, M 6144, K 4096, N 4096 267 / 290 / 311 / 254). It costs short launches alone
+// 2.7 % on average where it decides (26 shapes, K 768-9280).
 // Padded (masked) rows and columns are paid in full.
 // Where tiles wait for pieces a round costs kWaitRound more (a draw from the lists' counters and a look at the piece's
 // signal, neither of which hides behind another tile of the same workgroup), and two workgroups per CU, which both draw and
 // look, another kWaitSecond. Over 520 all-gather pairs (2 to 8 shards, 1 to 32 pieces each, M 128-32768, K 512-8192, N 256-
-// 9400; every tile forced in turn) the tile picked is 1.1 % slower than the fastest, 95 % of them within 6 %; without these
+// 9400; every tile forced in turn) the tile picked is 1.1 % slower than the fastest, 95 % of them within 7 %; without these
 // two terms 2.7 % and 12-18 % (M 9744, K 1152, N 7416, 4 x 4 pieces: 128x128 317 us, 128x256 242), with them but
 // without the last-step term below 1.3 %.
 int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
 {
-    static const struct { int id; double base, slope, start, next; int occ; double beside; } cand[] = {
-        {TILE_256x256, 0.89, 0.39, 13, 8, 1, 0},  {TILE_128x256, 0.49, 0.22, 10, 6, 1, 0}, {TILE_256x128, 0.51, 0.18, 10, 7, 1, 0.03},
-        {TILE_128x128, 0.47, 0.39, 6, 3, 2, 0},   {TILE_128x128D, 0.31, 0.09, 8, 4, 1, 0}, {TILE_64x256, 0.32, 0.16, 8, 3, 1, 0},
-        {TILE_32x256, 0.31, 0.09, 6, 2, 1, 0},    {TILE_128x192, 0.40, 0.15, 9, 4, 1, 0},  {TILE_256x192, 0.71, 0.29, 11, 6, 1, 0.05},
-        {TILE_64x128, 0.23, 0.04, 7, 2, 1, 0},
+    static const struct { int id; double base, slope, start, next; int occ; } cand[] = {
+        {TILE_256x256, 0.89, 0.39, 13, 8, 1}, {TILE_128x256, 0.49, 0.22, 10, 6, 1}, {TILE_256x128, 0.51, 0.21, 10, 7, 1},
+        {TILE_128x128, 0.47, 0.39, 6, 3, 2},  {TILE_128x128D, 0.31, 0.09, 8, 4, 1}, {TILE_64x256, 0.32, 0.16, 8, 3, 1},
+        {TILE_32x256, 0.31, 0.09, 6, 2, 1},   {TILE_128x192, 0.40, 0.15, 9, 4, 1},  {TILE_256x192, 0.71, 0.34, 11, 6, 1},
+        {TILE_64x128, 0.23, 0.04, 7, 2, 1},
     };
-    const bool beside = p->grouped || runs_pair(p);      // (an expert-parallel plan has one tile for all modes)
     constexpr double kWaitRound = 5, kWaitSecond = 3;
     double best = 1e300;
     int best_id = TILE_128x128;
@@ -154,8 +155,7 @@ int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
         if (lists > tn && lists <= (p->N + 127) / 128) continue;
         auto cost = [&](int64_t tiles) {
             const double full = std::floor((double)tiles / cap), rem = (double)tiles - full * cap;
-            const double slope = cd.slope + (beside ? cd.beside : 0.0);
-            const double steps = full * (cd.base + slope) + (rem > 0 ? cd.base + slope * rem / cap : 0.0);
+            const double steps = full * (cd.base + cd.slope) + (rem > 0 ? cd.base + cd.slope * rem / cap : 0.0);
             return cd.start + cd.next * (std::ceil((double)tiles / cap) - 1.0) + k_steps * steps;
         };
         double total = 0;
