@@ -211,7 +211,7 @@ static __device__ __forceinline__ void mfma_16x16x32(f32x4_t &c, const bf16x8_t 
 // the same bits); its loads spread over the turn instead of one every four slots 1512 (a denser issue holds up the
 // MFMAs behind it); M0 written a slot ahead of its load 1552; this loop's row-segment stores 1556. The loop before it
 // (32x32x16, one barrier per turn, the loads of a k-tile within half a turn) 1244; the vendor library 1596-1650.
-// Of a turn's 2470 cycles 2048 are MFMAs; LDS reads cost 100, the loads 70 when they hit in L2, and what misses it 230.
+// Counters (M 16384, K 8192, N 3584): 2446 cycles a turn, epilogues included, of which 2048 are MFMAs.
 template <class T, class Hook = NoHook, class AddrA = PlainA<T>>
 static __device__ __forceinline__ void tile_accumulate_from(TileAcc<T> &ta, AddrA &pa,
                                                             const uint16_t *__restrict__ wt_tile, int cols_valid,
@@ -463,6 +463,8 @@ struct TileWalk {
     int looked;      // the other lists' counters have been read
     int spent;       // bit k: list (home + k) % kTicketLists was already used up at that look
     int x, t;        // the result: list and tile in the list, x < 0 when there is nothing left
+    int have_drawn;  // `drawn` holds a counter value drawn ahead of time (kept here and not in a register across the k
+    uint32_t drawn;  // loop, which leaves none: the compiler would spill it to memory)
 };
 
 // Issues, ahead of time, the draw that the next tile_walk_next() call would start with (if it would
@@ -483,11 +485,11 @@ static __device__ __forceinline__ int tile_walk_predraw(const TileWalk &w, uint3
 
 template <class TotalFn>
 static __device__ __forceinline__ void tile_walk_next(TileWalk &w, uint32_t *ticket, const uint32_t *base, int grid, HandOut out,
-                                                      TotalFn total_of, int have_drawn = 0, uint32_t drawn = 0)
+                                                      TotalFn total_of)
 {
     const int home = blockIdx.x % kTicketLists, rank = blockIdx.x / kTicketLists, rounds = out.rounds;
     w.x = -1;
-    if (out.by_rank) {
+    if (__builtin_expect(out.by_rank, 0)) {
         if (w.taken < rounds && !tile_by_rank(home, rank, w.taken, grid, rounds, total_of, w.x, w.t)) w.taken = rounds;
         ++w.taken;
         return;
@@ -528,8 +530,8 @@ static __device__ __forceinline__ void tile_walk_next(TileWalk &w, uint32_t *tic
             ++w.turn;
             continue;
         }
-        const uint32_t raw = have_drawn ? drawn : __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        have_drawn = 0;
+        const uint32_t raw = w.have_drawn ? w.drawn : __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        w.have_drawn = 0;
         const int cand = (int)(raw - base[y]) + rounds * homes;
         if (cand < total) { w.x = y; w.t = cand; return; }
         ++w.turn;                                  // that was this workgroup's one draw past the end of list y
@@ -595,9 +597,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
     const ListGrid lists(row_tiles, tiles_n, r.col_lists, r.group);
     auto total_of = [&](int x) { return lists.total(x); };
 
-    if (threadIdx.x == 0) s_walk = TileWalk{0, 0, 0, 0, -1, 0};
-    int have_drawn = 0;
-    uint32_t drawn = 0;
+    if (threadIdx.x == 0) s_walk = TileWalk{0, 0, 0, 0, -1, 0, 0, 0};
     // Output streaming: a copy engine reads a piece of C while the kernel runs on, so
     // the tiles are written through the caches, and a tile is counted for its piece once every thread's
     // stores have been performed; whoever completes a piece lets its copy go. Ordering is by hand
@@ -617,8 +617,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
     for (;;) {
         if (threadIdx.x == 0) {
             TileWalk w = s_walk;
-            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.out, total_of, have_drawn, drawn);
-            have_drawn = 0;
+            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.out, total_of);
             int ok = 1;
             if (w.x >= 0) {
                 int R, tn;
@@ -650,6 +649,8 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
             else
                 tile_accumulate<T>(ta, a.A + row0 * a.lda, rows_valid, a.Wt + (int64_t)col0 * a.K, cols_valid, a.lda, a.K, a.K, smem);
             // the next ticket's round trip runs under the epilogue
+            int have_drawn = 0;
+            uint32_t drawn = 0;
             if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.out, total_of, drawn);
             if constexpr (STREAM_OUT) {
                 tile_store<T, true>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
@@ -657,6 +658,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
             } else {
                 tile_store<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
             }
+            if (threadIdx.x == 0) { s_walk.have_drawn = have_drawn; s_walk.drawn = drawn; }
         }
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused
     }
@@ -683,14 +685,11 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
     const ListGrid lists(row_tiles, tiles_n, r.col_lists, r.group);
     auto total_of = [&](int x) { return lists.total(x); };
 
-    if (threadIdx.x == 0) s_walk = TileWalk{0, 0, 0, 0, -1, 0};
-    int have_drawn = 0;
-    uint32_t drawn = 0;
+    if (threadIdx.x == 0) s_walk = TileWalk{0, 0, 0, 0, -1, 0, 0, 0};
     for (;;) {
         if (threadIdx.x == 0) {
             TileWalk w = s_walk;
-            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.out, total_of, have_drawn, drawn);
-            have_drawn = 0;
+            tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.out, total_of);
             s_walk = w;
         }
         __syncthreads();
@@ -734,8 +733,11 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
                 sl = run_end;
             }
         }
+        int have_drawn = 0;
+        uint32_t drawn = 0;
         if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.out, total_of, drawn);
         if (ok) tile_store<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
+        if (threadIdx.x == 0) { s_walk.have_drawn = have_drawn; s_walk.drawn = drawn; }
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused
     }
     wait_vmem<0>();                        // no load may arrive in LDS that is not this workgroup's any more
@@ -757,16 +759,13 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
     const ListGrid lists(r.n_row_tiles, tiles_n, r.col_lists, r.group);
     auto total_of = [&](int x) { return lists.total(x); };
 
-    if (threadIdx.x == 0) s_walk = TileWalk{0, 0, 0, 0, -1, 0};
-    int have_drawn = 0;
-    uint32_t drawn = 0;
+    if (threadIdx.x == 0) s_walk = TileWalk{0, 0, 0, 0, -1, 0, 0, 0};
     for (;;) {
         if (threadIdx.x < 64) {
             TileWalk w{};
             if (threadIdx.x == 0) {
                 w = s_walk;
-                tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.out, total_of, have_drawn, drawn);
-                have_drawn = 0;
+                tile_walk_next(w, r.ticket, r.ticket_base, r.grid, r.out, total_of);
                 s_walk = w;
             }
             const int wx = __builtin_amdgcn_readfirstlane(w.x), wt = __builtin_amdgcn_readfirstlane(w.t);
@@ -796,8 +795,11 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
             tile_zero(ta);
             tile_accumulate<T>(ta, a.A + row0 * a.lda, rows_valid, a.Wt + (expert * a.N + col0) * (int64_t)a.K, cols_valid,
                                a.lda, a.K, a.K, smem);
+            int have_drawn = 0;
+            uint32_t drawn = 0;
             if (threadIdx.x == 0) have_drawn = tile_walk_predraw(s_walk, r.ticket, r.grid, r.out, total_of, drawn);
             tile_store<T>(ta, a.C + row0 * a.ldc + col0, rows_valid, cols_valid, a.ldc);
+            if (threadIdx.x == 0) { s_walk.have_drawn = have_drawn; s_walk.drawn = drawn; }
         }
         __syncthreads();                   // s_walk / s_ok / LDS stages are reused
     }

@@ -120,10 +120,12 @@ __host__ __device__ inline bool tile_by_rank(int home, int rank, int taken, int 
     const int place = rank + taken * resident_list_homes(grid, home), total = total_of(home);
     if (place < total) { x = home; t = place; return true; }
     int spare = place - total;
+#pragma unroll 1
     for (int k = 0; k < home; ++k) {
         const int left = rounds * resident_list_homes(grid, k) - total_of(k);
         if (left > 0) spare += left;
     }
+#pragma unroll 1
     for (int k = 0; k < kTicketLists; ++k) {
         const int places = rounds * resident_list_homes(grid, k), over = total_of(k) - places;
         if (over <= 0) continue;
