@@ -50,12 +50,12 @@ HBM_PEAK_GBPS = 8000.0
 # read, and the factors by which a 256 MiB device copy's true traffic exceeds what they read for it.
 PMC_SCALE = {"FETCH_SIZE": 262144.0 / 131086.7, "WRITE_SIZE": 262144.0 / 262144.0}
 PMC_KIB = {
-    ("cfg2_qkv8b", "gemm_resident_kernel<128x192>"): {"FETCH_SIZE": 57491.0, "WRITE_SIZE": 12288.0},
-    ("cfg2_qkv8b", "gemm_blocks_kernel<128x192>"): {"FETCH_SIZE": 57458.0, "WRITE_SIZE": 12288.0},
-    ("cfg3_ffn70b", "gemm_resident_kernel<256x256>"): {"FETCH_SIZE": 908479.1, "WRITE_SIZE": 115327.7},
-    ("cfg3_ffn70b", "gemm_blocks_kernel<256x256>"): {"FETCH_SIZE": 825994.4, "WRITE_SIZE": 115201.6},
-    ("cfg6_2d_proj", "gemm_resident2d_kernel<256x256>"): {"FETCH_SIZE": 394542.8, "WRITE_SIZE": 33777.8},
-    ("cfg6_2d_proj", "gemm_blocks_kernel<256x256>"): {"FETCH_SIZE": 395433.1, "WRITE_SIZE": 33006.5},
+    ("cfg2_qkv8b", "gemm_resident_kernel<128x192>"): {"FETCH_SIZE": 57449.3, "WRITE_SIZE": 12288.0},
+    ("cfg2_qkv8b", "gemm_blocks_kernel<128x192>"): {"FETCH_SIZE": 57412.0, "WRITE_SIZE": 12288.0},
+    ("cfg3_ffn70b", "gemm_resident_kernel<256x256>"): {"FETCH_SIZE": 806072.8, "WRITE_SIZE": 117031.5},
+    ("cfg3_ffn70b", "gemm_blocks_kernel<256x256>"): {"FETCH_SIZE": 799399.3, "WRITE_SIZE": 116235.3},
+    ("cfg6_2d_proj", "gemm_resident2d_kernel<256x256>"): {"FETCH_SIZE": 393557.3, "WRITE_SIZE": 33544.5},
+    ("cfg6_2d_proj", "gemm_blocks_kernel<256x256>"): {"FETCH_SIZE": 413574.9, "WRITE_SIZE": 34304.8},
     ("cfg4_gemm_rs", "rs_reduce_kernel"): {"FETCH_SIZE": 131151.5, "WRITE_SIZE": 32768.0},      # profiles/rs_reduce_cfg4_gemm_rs.md
 }
 
