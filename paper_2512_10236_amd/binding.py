@@ -78,7 +78,7 @@ _lib = None
 
 
 def library_path() -> str:
-    """The in-tree library, or the one FICCO_LIBRARY names (a build made by ``_build.build_variant``)."""
+    """The in-tree library, or the one FICCO_LIBRARY names (another build, to be measured beside it)."""
     return os.environ.get("FICCO_LIBRARY") or _build.LIB
 
 

@@ -494,7 +494,7 @@ def test_grouped_plan_rules(args, status):
 
 
 def test_library_path_can_be_overridden_for_measuring_builds(monkeypatch, tmp_path):
-    """FICCO_LIBRARY names a measuring build (see _build.build_variant); without it the in-tree library is used,
+    """FICCO_LIBRARY names another build of the library; without it the in-tree library is used,
     and a path that does not exist is an error, not a fallback."""
     from paper_2512_10236_amd import _build, binding
     monkeypatch.delenv("FICCO_LIBRARY", raising=False)
