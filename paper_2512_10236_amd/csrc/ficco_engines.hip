@@ -742,6 +742,10 @@ int run_engines(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, vo
             r.done_count = p->d_done_count;
             r.done_sig = p->d_done_value;
             r.tiles_per_chunk = (int32_t)(rt * tn);
+            // the kernel releases a piece at every multiple of its tiles: another tile starts the count again
+            if (p->done_tiles != r.tiles_per_chunk && p->done_tiles)
+                HIP_TRY(hipMemsetAsync(p->d_done_count, 0, sizeof(uint32_t) * (size_t)n, cs));
+            p->done_tiles = r.tiles_per_chunk;
             book_tickets(p, r, lg, (int64_t)n * rt, tn, p->resident_grid, false);
             HIP_TRY(launch_resident(p->tile, r, cs));
             ++n_launches;

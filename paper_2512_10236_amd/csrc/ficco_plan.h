@@ -133,7 +133,8 @@ struct ficco_plan_s {
     std::vector<hsa_signal_t> sig_gather, sig_scatter;   // packing: per chunk id
     std::vector<hsa_signal_t> sig_done;              // resident GEMM -> RS: per chunk id, released by the kernel
     uint64_t *d_done_value = nullptr;                // device table: value-word addresses of sig_done
-    uint32_t *d_done_count = nullptr;                // device: tiles of each piece stored so far (never reset)
+    uint32_t *d_done_count = nullptr;                // device: tiles of each piece stored so far (reset only when ...
+    int32_t done_tiles = 0;                          // ... the tiles of a piece, which they are counted by, change)
     uint64_t *d_sig_value = nullptr;                 // device table: address of each data signal's value word
     int sig_poll = -1;                               // -1 unknown, 0 flags by 4-byte copies, 1 kernels poll the signals
     bool last_engines = false;

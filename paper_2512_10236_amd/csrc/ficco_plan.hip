@@ -221,6 +221,7 @@ void release(ficco_plan_t *p)
     p->d_slice_src = nullptr; p->d_packed_value = nullptr; p->d_packed_count = nullptr;
     p->d_done_value = nullptr;
     p->d_done_count = nullptr;
+    p->done_tiles = 0;
     p->d_sig_value = nullptr;
     p->sig_poll = -1;
     p->d_ticket_mem = nullptr;

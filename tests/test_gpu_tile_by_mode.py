@@ -96,3 +96,34 @@ def test_column_lists_are_taken_wherever_a_tile_fits_them(gpu, m, k, n, c, lists
     finally:
         for plan in plans:
             ficco.ficco_destroy(plan)
+
+
+def test_streamed_output_when_the_tile_changes_between_runs(gpu):
+    """GEMM -> reduce-scatter: the kernel counts a piece's tiles to release its transfer, and the count starts again where a
+    run has another tile than the one before it. A block that left early would bring the poison its rows were filled with."""
+    m, k, n, shards = 8192, 8192, 1160, 2
+    g = torch.Generator(device=gpu["dev"]).manual_seed(11)
+    A = torch.randn((m, k), generator=g, device=gpu["dev"]).bfloat16()
+    W = torch.randn((k, n), generator=g, device=gpu["dev"]).bfloat16()
+    out = torch.empty((m, n), dtype=torch.bfloat16, device=gpu["dev"])
+    peers = [torch.empty((m // shards, n), dtype=torch.bfloat16, device=gpu["dev"]) for _ in range(shards)]
+    tiles = []
+    plan = ficco.ficco_plan(m, k, n, shards, 1, ficco.FICCO_FINE_PERSISTENT)
+    try:
+        ficco.ficco_plan_set(plan, ficco.FICCO_OPT_DIRECTION, ficco.FICCO_DIR_GEMM_RS)
+        for lists in (8, 0, 0, 8, 0):
+            ficco.ficco_plan_set(plan, ficco.FICCO_OPT_TILE_COLUMN_LISTS, lists)
+            for t in peers + [out]:
+                t.fill_(float("nan"))
+            torch.cuda.synchronize()
+            print(f"{lists} column lists", flush=True)
+            ficco.ficco_run(plan, None, A, W, out, peers, gpu["cs"], gpu["xs"])
+            ficco.ficco_query_stats(plan)
+            torch.cuda.synchronize()
+            info = ficco.ficco_plan_info(plan)
+            tiles.append((info.tile_m, info.tile_n))
+            assert not torch.isnan(out.float()).any()
+            assert torch.equal(torch.cat(peers).view(torch.int16), out.view(torch.int16)), tiles
+    finally:
+        ficco.ficco_destroy(plan)
+    assert tiles[0] != tiles[1], "the shape no longer tells the two apart: take another one"
