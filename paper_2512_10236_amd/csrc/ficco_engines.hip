@@ -285,7 +285,7 @@ int run_grouped(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, hi
     p->run_index += 1;
     const uint32_t epoch = 1u + (p->run_index - 1u) % (uint32_t)(kEpochSlots - 1);
     const uint64_t spin_ticks = (uint64_t)p->spin_limit_us * (uint64_t)p->wall_clock_khz / 1000u;
-    const Gate gate{p->d_flags, poll_signals ? p->d_sig_value : nullptr, epoch, p->d_status, (uint32_t *)p->h_status, spin_ticks};
+    const Gate gate{p->d_flags, poll_signals ? p->d_sig_value : nullptr, poll_signals ? kRunTag | p->run_index : epoch, p->d_status, (uint32_t *)p->h_status, spin_ticks};
     for (int i = 0; i < n; ++i) {
         hsa_signal_store_relaxed(p->sig_data[i], (do_copy && p->piece_nrows[i] > 0) ? 1 : 0);
         hsa_signal_store_relaxed(p->sig_flag[i], 0);
@@ -412,7 +412,7 @@ int run_engines(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, vo
     // transfers are chained one after the other (peer-to-peer pattern) or run side by side (all-to-all)
     const bool chained = p->schedule == FICCO_SHARD ||
                          (p->schedule != FICCO_SERIAL && p->order == FICCO_ORDER_SHARD_MAJOR);
-    const Gate gate{p->d_flags, poll_signals ? p->d_sig_value : nullptr, epoch, p->d_status, (uint32_t *)p->h_status, spin_ticks};
+    const Gate gate{p->d_flags, poll_signals ? p->d_sig_value : nullptr, poll_signals ? kRunTag | p->run_index : epoch, p->d_status, (uint32_t *)p->h_status, spin_ticks};
     // arm the signals before any kernel that watches them can start
     for (int i = 0; i < n; ++i) {
         hsa_signal_store_relaxed(p->sig_data[i], (do_copy && !is_local(i)) ? 1 : 0);
@@ -586,7 +586,8 @@ int run_engines(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, vo
         // The launches watch the Gather copies' completion signals, or, when the transfers cross the host
         // link (where polling host memory would compete with them), flags raised by a 4-byte copy
         // behind each Gather copy. The final wait for the Scatter copies is a single wavefront.
-        const Gate pgate{p->d_flags, p->d_sig_value, epoch, p->d_status, (uint32_t *)p->h_status, spin_ticks};
+        // (signals n ... 3n - 1 of the table, which have no flags to pass anything on in)
+        const Gate pgate{nullptr, p->d_sig_value, kRunTag | p->run_index, p->d_status, (uint32_t *)p->h_status, spin_ticks};
         const Gate ggate = poll_signals ? pgate : gate;
         const size_t piece_a = (size_t)p->m * row_bytes_a, piece_c = (size_t)p->m * row_bytes_c;
         for (size_t g = 0; g < p->groups.size(); ++g) {
@@ -830,7 +831,7 @@ int ficco_rs_reduce(ficco_plan_t *p, int block, const void *P_src, void *P_dev, 
     p->run_index += 1;
     const uint32_t epoch = 1u + (p->run_index - 1u) % (uint32_t)(kEpochSlots - 1);
     const uint64_t spin_ticks = (uint64_t)p->spin_limit_us * (uint64_t)p->wall_clock_khz / 1000u;
-    const Gate gate{p->d_flags, poll_signals ? p->d_sig_value : nullptr, epoch, p->d_status, (uint32_t *)p->h_status, spin_ticks};
+    const Gate gate{p->d_flags, poll_signals ? p->d_sig_value : nullptr, poll_signals ? kRunTag | p->run_index : epoch, p->d_status, (uint32_t *)p->h_status, spin_ticks};
     for (int i = 0; i < n; ++i) {
         hsa_signal_store_relaxed(p->sig_data[i], (i / c == block || !do_copy) ? 0 : 1);
         hsa_signal_store_relaxed(p->sig_flag[i], 0);

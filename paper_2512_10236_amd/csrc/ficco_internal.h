@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace ficco {
@@ -149,14 +150,29 @@ __host__ __device__ inline uint32_t resident_list_draws(int64_t list_tiles, int 
 //   sig_value - the 64-bit word at sig_value[chunk] has dropped to 0: the value field of the transfer's
 //               own completion signal, decremented by the copy engine itself
 // Both are read at system scope; the wait is bounded (status[0] = 1 when it expires).
+// The signals' words lie in host memory, and what reads them shares the host link with the engines' own writes to them. So
+// where many workgroups wait, each looks there on one of polls_per_look() polls only, passes on what it sees landed - the
+// run's epoch, into the piece's flag in device memory, which no transfer writes then - and watches that flag on all others.
+constexpr uint32_t kRunTag = 0x80000000u;
 struct Gate {
-    const uint32_t *flags;
+    uint32_t *flags;              // nullptr where only the signals are watched and nothing is passed on
     const uint64_t *sig_value;    // device table of addresses, or nullptr to use flags
-    uint32_t epoch;
+    uint32_t epoch;               // of the run; with signals kRunTag | its number, which no flag copy and no earlier run writes
     uint32_t *status;             // device word every waiting workgroup watches
     uint32_t *status_host;        // pinned host word set together with it, so that the host needs no copy to see it
     uint64_t spin_limit_ticks;    // in wall_clock64() ticks
 };
+// Of `workgroups` that wait, `same` of them for the same piece, each looks at the signals on one of this many polls: about
+// four of those look at a time, and about 32 of all. 1: on every poll, and nothing is passed on. With all of them looking
+// all the time each costs a launch about 0.1 us; four a piece see it land as soon as all would (us a pass, all / 8 / 4 / 2 of
+// those at a time: M 4096, K 2048, N 256 over eight shards, 256 workgroups of 64x64 tiles, 32 a piece 76.0 / - / 73.2 / 75.7;
+// M 512, K 1024, N 1024 over four shards, 256 workgroups of 32x64, 64 a piece 41.2 / 37.5 / 35.3 / -; one launch per step, M
+// 4096, K 8192, N 3584, 224 workgroups, all / 28 of them at eight signals 355.8 / 330.7).
+__device__ inline uint32_t polls_per_look(uint32_t workgroups, uint32_t same)
+{
+    const uint32_t n = same / 4 > workgroups / 32 ? same / 4 : workgroups / 32;
+    return n < 1 ? 1 : n > 16 ? 16 : n;
+}
 
 // One GEMM launch over a list of equal-height row blocks of A/C (one block for a monolithic or
 // per-piece launch, G blocks for a fused step).
