@@ -24,31 +24,37 @@ static __device__ __forceinline__ Gate gate_argument(size_t offset)
 // Every load of a wait is over, also by the compiler's book (its other way is a wait in each turn of the k loop that follows).
 static __device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// Bounded wait of one thread until a piece is ready (see Gate); `every`: polls_per_look(). Reads at system scope (past the
+// Between two polls, about 0.1 us for each nap.
+static __device__ __forceinline__ void nap(Pace pace)
+{
+    for (uint32_t i = 0; i < pace.naps; ++i) __builtin_amdgcn_s_sleep(4);
+}
+
+// Bounded wait of one thread until a piece is ready (see Gate); `pace`: pace_of(). Reads at system scope (past the
 // caches): the writer is a copy engine. Returns 0 when the limit expires or another workgroup has
 // already given up; the caller then skips its work, so every wave still reaches its exit.
-static __device__ __forceinline__ int wait_ready(const Gate &g, int chunk, uint32_t every)
+static __device__ __forceinline__ int wait_ready(const Gate &g, int chunk, Pace pace)
 {
     const uint64_t t0 = wall_clock64();
     uint32_t *f = g.flags + (size_t)chunk * kFlagStrideWords;
     const int64_t *sv = g.sig_value ? reinterpret_cast<const int64_t *>(g.sig_value[chunk]) : nullptr;
     int late = 0;
     for (uint32_t polls = blockIdx.x;; ++polls) {
-        if ((!sv || every > 1) && __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == g.epoch) return 1;
-        if (sv && (late || polls % every == 0)) {
-            if (__hip_atomic_load(sv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) <= 0) {
-                if (every > 1) __hip_atomic_store(f, g.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if ((!sv || pace.every > 1) && __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == g.epoch) return 1;
+        if (late || polls % pace.every == 0) {
+            if (sv && __hip_atomic_load(sv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) <= 0) {
+                if (pace.every > 1) __hip_atomic_store(f, g.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 return 1;
             }
-        }
-        if (__hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) return 0;
-        if (late) {                        // the look above was the last one
-            __hip_atomic_store(g.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            __hip_atomic_store(g.status_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            return 0;
+            if (__hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) return 0;
+            if (late) {                    // that look was the last one
+                __hip_atomic_store(g.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                __hip_atomic_store(g.status_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                return 0;
+            }
         }
         late = wall_clock64() - t0 > g.spin_limit_ticks;
-        __builtin_amdgcn_s_sleep(4);
+        nap(pace);
     }
 }
 
@@ -67,14 +73,14 @@ static __device__ __forceinline__ int peek_ready(const Gate &g, int chunk, int p
 // ... A look at a signal is a round trip to host memory of 1-2 us, and a wave that looked at its pieces one after the
 // other paid one for each of them, landed or not; this way it pays one for 64. But waves that look at all their pieces all
 // the time swamp the host link, which the transfers' own signals cross too. So on the polls on which a wave looks there
-// (polls_per_look) it looks at all of them first, then at the last one that is missing (pieces are listed in the order in
+// (pace_of) it looks at all of them first, then at the last one that is missing (pieces are listed in the order in
 // which they leave), and at all again when that one has landed, every kLookEvery polls, and before it gives up; kLookFew
 // pieces are few enough to be looked at all the time. M 1675, K 3264, N 7496, eight experts in four steps, 32 pieces a tile,
 // every workgroup looking on every poll: one after the other 590 us, all of them all the time 887-907, this way 579.
 // The limit counts from the last time that a piece was seen to land. Returns the same value in every lane.
 constexpr int kLookEvery = 8, kLookFew = 2;
 template <class PieceFn>
-static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, uint32_t every, PieceFn piece_of)
+static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, Pace pace, PieceFn piece_of)
 {
     const int lane = threadIdx.x & 63;
     uint64_t t0 = wall_clock64();
@@ -84,9 +90,9 @@ static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, uint3
         uint64_t missing = __ballot(waiting);
         int all = 1, late = 0;
         for (int polls = 1;; ++polls) {
-            const int look = late || (polls + blockIdx.x) % every == 0;
+            const int look = late || (polls + blockIdx.x) % pace.every == 0;
             const int mine = all || lane == 63 - __builtin_clzll(missing);
-            const int landed = waiting && (every > 1 || mine) && peek_ready(g, piece, every > 1, look && mine);
+            const int landed = waiting && mine && peek_ready(g, piece, pace.every > 1, look);
             if (landed) waiting = 0;
             missing = __ballot(waiting);
             if (!missing) {
@@ -98,7 +104,7 @@ static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, uint3
             const int last_look = late && !any;
             late = wall_clock64() - t0 > g.spin_limit_ticks;
             int give_up = 0;
-            if (lane == 0) {
+            if (lane == 0 && look) {
                 if (__hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) {
                     give_up = 1;
                 } else if (last_look) {
@@ -110,7 +116,7 @@ static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, uint3
             if (__any(give_up)) return 0;
             const int last_landed = any && !all;
             all = last_landed || late || polls % kLookEvery == 0 || __builtin_popcountll(missing) <= kLookFew;
-            if (!last_landed) __builtin_amdgcn_s_sleep(4);
+            if (!last_landed) nap(pace);
         }
     }
     loads_done();

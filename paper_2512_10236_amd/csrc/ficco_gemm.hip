@@ -406,7 +406,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_blocks_kernel(GemmLaunch a)
     if (a.n_wait > 0) {
         __shared__ int s_go;
         if (threadIdx.x < 64) {
-            const int ok = wait_ready_all(a.gate, a.n_wait, a.gate.flags ? polls_per_look(gridDim.x, gridDim.x) : 1, [&](int i) { return a.wait_chunks[i]; });
+            const int ok = wait_ready_all(a.gate, a.n_wait, a.gate.flags ? pace_of(gridDim.x, gridDim.x) : Pace{1, 1}, [&](int i) { return a.wait_chunks[i]; });
             if (threadIdx.x == 0) s_go = ok;
         }
         __syncthreads();                   // also orders the tile's loads after the flag reads
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident_kernel(ResidentLaunc
                 int R, tn;
                 lists.position(w.x, w.t, R, tn);
                 const int chunk = r.arrival[R / rt_per_chunk];
-                if (chunk < r.local_chunk_begin || chunk >= r.local_chunk_end) ok = wait_ready(gate_argument(offsetof(ResidentLaunch, g.gate)), chunk, polls_per_look(r.grid, rt_per_chunk * tiles_n));
+                if (chunk < r.local_chunk_begin || chunk >= r.local_chunk_end) ok = wait_ready(gate_argument(offsetof(ResidentLaunch, g.gate)), chunk, pace_of(r.grid, rt_per_chunk * tiles_n));
                 s_chunk = chunk;           // the others take it from here instead of the table in memory
             }
             s_walk = w;
@@ -713,12 +713,12 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
             if (r.gated) {
                 if (threadIdx.x < 64) {
                     const Gate gate = gate_argument(offsetof(Resident2DLaunch, g.gate));
-                    const uint32_t every = polls_per_look(r.grid, r.grid / r.shards);
-                    const int o = wait_ready_all(gate, j1 - j0 + 1, every, [&](int i) { return sl * r.shards + j0 + i; });
+                    const Pace pace = pace_of(r.grid, r.grid / r.shards);
+                    const int o = wait_ready_all(gate, j1 - j0 + 1, pace, [&](int i) { return sl * r.shards + j0 + i; });
                     // one look at up to 64 following slices, a lane each
                     const int mine = sl + 1 + (int)threadIdx.x;
                     int landed = o && mine < r.slices;
-                    for (int j = j0; j <= j1; ++j) landed = landed && peek_ready(gate, mine * r.shards + j, every > 1, (blockIdx.x + sl) % every == 0);
+                    for (int j = j0; j <= j1; ++j) landed = landed && peek_ready(gate, mine * r.shards + j, pace.every > 1, (blockIdx.x + sl) % pace.every == 0);
                     const uint64_t not_landed = ~__ballot(landed);
                     const int run = not_landed ? __builtin_ctzll(not_landed) : 64;
                     if (threadIdx.x == 0) s_ok = o ? sl + 1 + run : 0;      // 0: gave up; else the slice after the run
@@ -777,7 +777,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
                 lists.position(wx, wt, R, tn);
                 const int32_t *rt = r.row_tiles + (size_t)R * kRowTileWords;
                 const int first = rt[3];
-                ok = wait_ready_all(gate_argument(offsetof(GroupedLaunch, g.gate)), rt[4] - first + 1, polls_per_look(r.grid, tiles_n), [&](int i) { return first + i; });
+                ok = wait_ready_all(gate_argument(offsetof(GroupedLaunch, g.gate)), rt[4] - first + 1, pace_of(r.grid, tiles_n), [&](int i) { return first + i; });
             }
             if (threadIdx.x == 0) s_ok = ok;
         }
@@ -810,7 +810,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_grouped_kernel(GroupedLaunch 
 
 __global__ __launch_bounds__(64) void wait_ready_kernel(Gate gate, const int32_t *chunks, int n)
 {
-    (void)wait_ready_all(gate, n, 1, [&](int i) { return chunks[i]; });
+    (void)wait_ready_all(gate, n, Pace{1, 1}, [&](int i) { return chunks[i]; });
 }
 
 // Nothing is published through the signal: what it orders is that the kernels before this one on the

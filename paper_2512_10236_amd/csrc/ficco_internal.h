@@ -151,7 +151,7 @@ __host__ __device__ inline uint32_t resident_list_draws(int64_t list_tiles, int 
 //               own completion signal, decremented by the copy engine itself
 // Both are read at system scope; the wait is bounded (status[0] = 1 when it expires).
 // The signals' words lie in host memory, and what reads them shares the host link with the engines' own writes to them. So
-// where many workgroups wait, each looks there on one of polls_per_look() polls only, passes on what it sees landed - the
+// where many workgroups wait, each looks there on some of its polls only (pace_of), passes on what it sees landed - the
 // run's epoch, into the piece's flag in device memory, which no transfer writes then - and watches that flag on all others.
 constexpr uint32_t kRunTag = 0x80000000u;
 struct Gate {
@@ -162,16 +162,21 @@ struct Gate {
     uint32_t *status_host;        // pinned host word set together with it, so that the host needs no copy to see it
     uint64_t spin_limit_ticks;    // in wall_clock64() ticks
 };
-// Of `workgroups` that wait, `same` of them for the same piece, each looks at the signals on one of this many polls: about
-// four of those look at a time, and about 32 of all. 1: on every poll, and nothing is passed on. With all of them looking
-// all the time each costs a launch about 0.1 us; four a piece see it land as soon as all would (us a pass, all / 8 / 4 / 2 of
-// those at a time: M 4096, K 2048, N 256 over eight shards, 256 workgroups of 64x64 tiles, 32 a piece 76.0 / - / 73.2 / 75.7;
-// M 512, K 1024, N 1024 over four shards, 256 workgroups of 32x64, 64 a piece 41.2 / 37.5 / 35.3 / -; one launch per step, M
-// 4096, K 8192, N 3584, 224 workgroups, all / 28 of them at eight signals 355.8 / 330.7).
-__device__ inline uint32_t polls_per_look(uint32_t workgroups, uint32_t same)
+// How a workgroup waits, of `workgroups` that wait and `same` of them for the same piece. It looks at the signals on one of
+// `every` polls: about four of those that wait for a piece look at a time, and about 32 of all (1: on every poll, and nothing
+// is passed on). With all of them looking all the time each costs a launch about 0.1 us; four a piece see it land as soon as
+// all would (us a pass, all / 8 / 4 / 2 of those at a time: M 4096, K 2048, N 256 over eight shards, 256 workgroups of 64x64
+// tiles, 32 a piece 76.0 / - / 73.2 / 75.7; M 512, K 1024, N 1024 over four shards, 256 workgroups of 32x64, 64 a piece 41.2 /
+// 37.5 / 35.3 / -; one launch per step, M 4096, K 8192, N 3584, 224 workgroups, all / 28 of them at eight signals 355.8 / 330.7).
+// A flag that hundreds of workgroups read as fast as they can holds up what else goes to that place in memory: from about
+// a hundred on a piece, polls are `naps` times as far apart (the same launches per step at 1 / 4 / 12 naps 315 / 308 / 303, M
+// 4096, K 2048, N 2048 122 / 116 / 108; with 64 a piece they only see it later, 44.5 / 47.2 / 47.1 at M 512).
+struct Pace { uint32_t every, naps; };
+__device__ inline Pace pace_of(uint32_t workgroups, uint32_t same)
 {
+    if (same > workgroups) same = workgroups;
     const uint32_t n = same / 4 > workgroups / 32 ? same / 4 : workgroups / 32;
-    return n < 1 ? 1 : n > 16 ? 16 : n;
+    return {n < 1 ? 1 : n > 16 ? 16 : n, same < 96 ? 1 : same / 24};
 }
 
 // One GEMM launch over a list of equal-height row blocks of A/C (one block for a monolithic or

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void rs_reduce_kernel(ReduceLaunch r)
                     watch = __builtin_amdgcn_readfirstlane(watch);
                 }
                 if (watch && ok) {
-                    ok = wait_ready_all(r.gate, r.G - 1, 1, [&](int i) { return (i < r.block ? i : i + 1) * r.pieces + s; });
+                    ok = wait_ready_all(r.gate, r.G - 1, Pace{1, 1}, [&](int i) { return (i < r.block ? i : i + 1) * r.pieces + s; });
                     if (ok && threadIdx.x == 0) __hip_atomic_store(word, r.gate.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
                 }
                 if (threadIdx.x == 0) s_ok = ok;
