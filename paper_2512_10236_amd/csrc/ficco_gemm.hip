@@ -79,14 +79,17 @@ struct TileCfg {
         }
         return true;
     }
-    static_assert(fragments_hold(), "a fragment is read too early or too late");
-    static_assert(NSTAGE >= 2 && NSTAGE <= 6 && (NSTAGE - 1) * LOADS < 64, "ring of 2 to 6 stages, vmcnt has 6 bits");
+    // Stages go in pairs (tile_accumulate_burst).
+    static constexpr bool BURST = NM <= 4;
+    static_assert(BURST || fragments_hold(), "a fragment is read too early or too late");
+    static_assert(BURST ? NSTAGE % 2 == 0 && NSTAGE >= 6 && (NSTAGE - 2) * LOADS < 64 : NSTAGE >= 2 && NSTAGE <= 6 && (NSTAGE - 1) * LOADS < 64,
+                  "ring of 2 to 6 stages, or pairs of them, vmcnt has 6 bits");
     static_assert(LDS_BYTES <= 160 * 1024 - 64, "LDS ring plus the kernels' few static words must fit one CU");
     static_assert(THREADS == 256, "4 wavefronts");
     static_assert(BM % (RPL * NW) == 0 && BN % (RPL * NW) == 0, "every wavefront loads the same number of blocks");
     static_assert(WTM % 16 == 0 && WTN % 32 == 0, "wavefront tile is made of 16x16 blocks, stored in pairs along a row");
     static_assert(AB >= 1 && BB >= 1, "tile too small for the loader");
-    static_assert(R0 + (NR - 1) * RSTEP - TT < (FM - 1) * FN && R0 + (NR - 1) * RSTEP - TT < FREE && load_slot(LOADS - 1) - TT < LS && load_slot(LOADS - 1) < LAND + (NSTAGE - 1) * TT,
+    static_assert(BURST || (R0 + (NR - 1) * RSTEP - TT < (FM - 1) * FN && R0 + (NR - 1) * RSTEP - TT < FREE && load_slot(LOADS - 1) - TT < LS && load_slot(LOADS - 1) < LAND + (NSTAGE - 1) * TT),
                   "what a turn leaves to the next one is done before it is needed");
 };
 
@@ -194,6 +197,105 @@ static __device__ __forceinline__ void mfma_16x16x32(f32x4_t &c, const bf16x8_t 
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(n), "v"(m));
 }
 
+// The k loop of tiles whose turn has too few MFMAs to put anything behind. A turn is two stages (128 k values): one wait and
+// one barrier, behind which its k-tiles have landed for everyone and everyone has read the two before; then all of its
+// fragments out of LDS; then the loads that refill the two stages before it, with the MFMAs between them, as their fragments
+// arrive (a wavefront's loads take 64 cycles each while all four issue theirs, and what is behind a load waits for that).
+//
+// What bounds it: the CU draws 64 bytes a cycle from L2 and 45-52 from beyond, whatever is in flight. 32x64 tiles draw 24 KiB
+// a turn, 64x64 32 KiB, where 64x128 draws 48: 0.26 / 0.35 / 0.45 us, of which the loads alone are 0.22 / 0.31 / 0.45. MFMAs
+// behind all loads 0.275 / 0.41; touching the lines a few turns ahead with a fifth wavefront 0.42 / 0.52, because a touched
+// line takes the same way.
+template <class T, class Hook, class AddrA>
+static __device__ __forceinline__ void tile_accumulate_burst(TileAcc<T> &ta, AddrA &pa, const uint16_t *__restrict__ wt_tile, int cols_valid,
+                                                             int64_t ldw, int K, unsigned char *smem, Hook after_first_wait)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = scalar(threadIdx.x >> 6);
+    const int wm = wave / T::WGN, wn = wave % T::WGN;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const uint16_t *const wt = scalar_base(wt_tile);
+    constexpr int TURNS = T::NSTAGE / 2, PAIR = 2 * T::STAGE, LOADS = 2 * T::LOADS;
+    const int KT = scalar(K) / T::BK, KP = (KT + 1) / 2;
+    uint32_t offb[T::BB];
+#pragma unroll
+    for (int i = 0; i < T::BB; ++i) offb[i] = lane_offset<T>(wave * T::BB + i, lane, cols_valid, ldw);
+    // load l of a turn's: those of its first k-tile, then those of its second (which may not exist at the end of K: the first
+    // again, and not used)
+    auto load = [&](int t, uint32_t pair, auto l_c) __attribute__((always_inline)) {
+        constexpr int u = decltype(l_c)::value / T::LOADS, l = decltype(l_c)::value % T::LOADS;
+        const int kt = min(2 * t + u, KT - 1);
+        if constexpr (l == 0) pa.seek(kt);
+        if constexpr (l < T::AB) set_lds_target<u * T::STAGE + l * 1024>(lds0 + pair + wave * T::AB * 1024);
+        else set_lds_target<u * T::STAGE + T::A_STAGE + (l - T::AB) * 1024>(lds0 + pair + wave * T::BB * 1024);
+        asm volatile("s_nop 0" ::: "memory");
+        if constexpr (l < T::AB) load_to_lds_16(pa.at(kt), pa.off[l]);
+        else load_to_lds_16(wt + (int64_t)kt * T::BK, offb[l - T::AB]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto issue = [&](int t, uint32_t pair) __attribute__((always_inline)) {
+        static_for<LOADS>([&](auto l) __attribute__((always_inline)) { load(t, pair, l); });
+    };
+    const int frow = lane & 15, fh = lane >> 4, fs = (frow >> 1) & 7;
+    const int a_base = (wm * T::WTM + frow) * T::ROWB, b_base = T::A_STAGE + (wn * T::WTN + frow) * T::ROWB;
+    bf16x8_t fa[4][T::FM], fb[4][T::FN];
+    auto read = [&](uint32_t pair) __attribute__((always_inline)) {
+        static_for<4>([&](auto h_c) __attribute__((always_inline)) {
+            constexpr int h = decltype(h_c)::value;
+            const unsigned char *base = smem + pair + h / 2 * T::STAGE + (((4 * (h % 2) + fh) ^ fs) << 4);
+#pragma unroll
+            for (int i = 0; i < T::FM; ++i) fa[h][i] = *reinterpret_cast<const bf16x8_t *>(base + a_base + i * 16 * T::ROWB);
+#pragma unroll
+            for (int j = 0; j < T::FN; ++j) fb[h][j] = *reinterpret_cast<const bf16x8_t *>(base + b_base + j * 16 * T::ROWB);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int NMF = 4 * T::NM;         // MFMAs of a turn
+    auto product = [&](auto m_c) __attribute__((always_inline)) {
+        constexpr int m = decltype(m_c)::value, h = m / T::NM, i = m % T::NM / T::FN, j = m % T::FN;
+        mfma_16x16x32(ta.acc[j][i], fb[h][j], fa[h][i]);
+    };
+    auto meet = [&](auto in_flight) __attribute__((always_inline)) {
+        wait_vmem<decltype(in_flight)::value>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        wg_barrier();
+    };
+    const int ahead = min(KP, TURNS - 1);
+    for (int t = 0; t < ahead; ++t) issue(t, t * PAIR);
+    uint32_t cur = 0, next = (TURNS - 1) * PAIR;
+    int k = 0;
+#pragma clang loop unroll(disable)
+    for (; k + TURNS - 1 < KP; ++k) {
+        meet(std::integral_constant<int, (TURNS - 2) * LOADS>{});
+        if (k == 0) after_first_wait();
+        read(cur);
+        static_for<LOADS>([&](auto l) __attribute__((always_inline)) {
+            load(k + TURNS - 1, next, l);
+            static_for<NMF>([&](auto m) __attribute__((always_inline)) {
+                if constexpr (l.value == 1 + m.value * (LOADS - 1) / NMF) product(m);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        cur = cur == (TURNS - 1) * PAIR ? 0 : cur + PAIR;
+        next = next == (TURNS - 1) * PAIR ? 0 : next + PAIR;
+    }
+    static_for<TURNS - 1>([&](auto t) __attribute__((always_inline)) {
+        constexpr int left = TURNS - 1 - decltype(t)::value;
+        if (left <= ahead) {
+            meet(std::integral_constant<int, (left - 1) * LOADS>{});
+            if (k == 0) after_first_wait();
+            read(cur);
+            static_for<NMF / 2>([&](auto m) __attribute__((always_inline)) { product(m); });
+            if (2 * k + 1 < KT) static_for<NMF / 2>([&](auto m) __attribute__((always_inline)) { product(std::integral_constant<int, NMF / 2 + m.value>{}); });
+            ++k;
+            cur = cur == (TURNS - 1) * PAIR ? 0 : cur + PAIR;
+        }
+    });
+    // accumulators may be read after the last MFMA's passes
+    asm volatile("s_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // The k loop. Turn k multiplies k-tile k out of registers: slots [0, NM) its first half (k values 0..31 of the stage),
 // whose fragments were read during the turn before, slots [NM, TT) its second half, whose fragments are read during
 // the first (from slot R1 on). Behind the MFMAs go, at fixed slots (TileCfg),
@@ -218,6 +320,10 @@ static __device__ __forceinline__ void tile_accumulate_from(TileAcc<T> &ta, Addr
                                                             int64_t ldw, int K, unsigned char *smem,
                                                             Hook after_first_wait = Hook())
 {
+    if constexpr (T::BURST) {
+        tile_accumulate_burst<T, Hook, AddrA>(ta, pa, wt_tile, cols_valid, ldw, K, smem, after_first_wait);
+        return;
+    } else {
     f32x4_t (&acc)[T::FN][T::FM] = ta.acc;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -323,6 +429,7 @@ static __device__ __forceinline__ void tile_accumulate_from(TileAcc<T> &ta, Addr
     // accumulators may be read after the last MFMA's 16 passes
     asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 template <class T, class Hook = NoHook>
@@ -932,12 +1039,15 @@ typedef TileCfg<256, 192, 2, 2, 2> T256x192;
 // the tile, so a k-tile's time is its bytes: 24 KiB in 0.27 us here, 32 KiB in 0.40 with 128x128, and a short launch gains
 // by spreading over more CUs. Six stages keep 120 KiB of loads in flight. M 1024, K 4096, N 768 30.6 -> 24.6 us.
 typedef TileCfg<64, 128, 2, 2, 6> T64x128;
+typedef TileCfg<64, 64, 2, 2, 8> T64x64;           // parts (is_part), rings of four and six pairs of stages
+typedef TileCfg<32, 64, 2, 2, 12> T32x64;
 
 // every tile shape, for the dispatch switches below
 #define FICCO_FOR_EACH_TILE(X) \
     X(TILE_256x256, T256x256) X(TILE_128x128, T128x128) X(TILE_256x128, T256x128) X(TILE_128x256, T128x256) \
     X(TILE_64x256, T64x256) X(TILE_32x256, T32x256) X(TILE_128x128D, T128x128D) X(TILE_128x192, T128x192) \
-    X(TILE_256x192, T256x192) X(TILE_64x128, T64x128)
+    X(TILE_256x192, T256x192) X(TILE_64x128, T64x128) \
+    X(TILE_64x64, T64x64) X(TILE_32x64, T32x64)
 
 TileShape tile_shape(int tile)
 {

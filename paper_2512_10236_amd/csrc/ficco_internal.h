@@ -11,7 +11,11 @@ namespace ficco {
 // same in all of them, so the output bits do not depend on the choice.
 enum TileId : int { TILE_256x256 = 1, TILE_128x128 = 2, TILE_256x128 = 3, TILE_128x256 = 4,
                     TILE_64x256 = 5, TILE_32x256 = 6, TILE_128x128D = 7, TILE_128x192 = 8, TILE_256x192 = 9,
-                    TILE_64x128 = 10, TILE_COUNT = 11 };
+                    TILE_64x128 = 10, TILE_64x64 = 11, TILE_32x64 = 12, TILE_COUNT = 13 };
+
+// The last two are parts that a launch's tiles are cut into, a workgroup each, where that is faster than whole ones (few
+// tiles, CUs idle). What a plan tells is the whole tile.
+inline bool is_part(int tile) { return tile == TILE_64x64 || tile == TILE_32x64; }
 
 struct TileShape { int bm, bn, lds_bytes, threads; };
 TileShape tile_shape(int tile);

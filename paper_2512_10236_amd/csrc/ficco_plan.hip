@@ -126,28 +126,34 @@ static bool runs_pair(const ficco_plan_t *p) { return (p->losses_of >= 0 ? p->lo
 // 720 / 705, M 16384, K 16384, N 3584 1349 / 1467 / 1434 / 1423; pairs over eight shards: M 16384, K 8192, N 3584 830 / 947 / 995 /
 // 852, M 8192, K 8192, N 4096 518 / 566 / 553 / 520, M 6144, K 4096, N 4096 267 / 290 / 311 / 254). It costs short launches alone
 // 2.7 % on average where it decides (26 shapes, K 768-9280).
+// The parts of a tile (is_part) compete with the whole ones: measured over 3400 launches of up to 300 64x128
+// tiles (M 16-8192, K 256-8192, N 64-4096; alone, pairs, one launch per step and per shard; every tile forced in turn) the
+// tile picked is 0.2-0.5 % slower than the fastest, and with them the fastest is 6-7 % faster than without in runs with
+// transfers, 28 % alone (us: M 512, K 4096, N 768 alone 64x128 19.4, 64x64 15.2, 32x64 12.3; the pair over four shards 66.1 /
+// 58.9 / 55.4; M 1024 of it over eight 69.5 / 61.6 / 69.2).
 // Padded (masked) rows and columns are paid in full.
-// Where tiles wait for pieces a round costs kWaitRound more (a draw from the lists' counters and a look at the piece's
+// Where tiles wait for pieces every workgroup that does costs kWaitEach, a round costs kWaitRound more (a draw from the lists' counters and a look at the piece's
 // signal, neither of which hides behind another tile of the same workgroup), and two workgroups per CU, which both draw and
 // look, another kWaitSecond. Over 520 all-gather pairs (2 to 8 shards, 1 to 32 pieces each, M 128-32768, K 512-8192, N 256-
 // 9400; every tile forced in turn) the tile picked is 1.1 % slower than the fastest, 95 % of them within 7 %; without these
 // two terms 2.7 % and 12-18 % (M 9744, K 1152, N 7416, 4 x 4 pieces: 128x128 317 us, 128x256 242), with them but
 // without the last-step term below 1.3 %.
-int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
+static int cheapest_tile(const ficco_plan_t *p, int cus, bool whole_rows, bool with_parts, double *us)
 {
     static const struct { int id; double base, slope, start, next; int occ; } cand[] = {
         {TILE_256x256, 0.89, 0.39, 13, 8, 1}, {TILE_128x256, 0.49, 0.22, 10, 6, 1}, {TILE_256x128, 0.51, 0.21, 10, 7, 1},
         {TILE_128x128, 0.47, 0.39, 6, 3, 2},  {TILE_128x128D, 0.31, 0.09, 8, 4, 1}, {TILE_64x256, 0.32, 0.16, 8, 3, 1},
         {TILE_32x256, 0.31, 0.09, 6, 2, 1},   {TILE_128x192, 0.40, 0.15, 9, 4, 1},  {TILE_256x192, 0.71, 0.34, 11, 6, 1},
-        {TILE_64x128, 0.23, 0.04, 7, 2, 1},
+        {TILE_64x128, 0.23, 0.04, 7, 2, 1},   {TILE_64x64, 0.17, 0.01, 5.5, 2, 1}, {TILE_32x64, 0.128, 0.006, 4.9, 2, 1},
     };
-    constexpr double kWaitRound = 5, kWaitSecond = 3;
+    constexpr double kWaitRound = 5, kWaitSecond = 3, kWaitEach = 0.01;
     double best = 1e300;
     int best_id = TILE_128x128;
     const double k_steps = (double)p->K / kBK;
     const int lists = (is_resident(p) || p->grouped) && !(whole_rows && p->N <= 256) ? p->tile_col_lists : 0;
     for (auto &cd : cand) {
         TileShape ts = tile_shape(cd.id);
+        if (!with_parts && is_part(cd.id)) continue;
         if (whole_rows && p->N <= 256 && ts.bn < p->N) continue;
         const double cap = (double)cus * cd.occ;
         const int64_t tn = (p->N + ts.bn - 1) / ts.bn;
@@ -178,7 +184,8 @@ int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
             }
             if (p->direction == FICCO_DIR_AG_GEMM && runs_pair(p)) {
                 const double rounds = std::ceil((double)p->n_chunks * (double)piece_tiles / cap);
-                total += kWaitRound * (rounds - 1.0) + (cd.occ > 1 ? kWaitSecond * rounds : 0.0);
+                total += kWaitRound * (rounds - 1.0) + (cd.occ > 1 ? kWaitSecond * rounds : 0.0) +
+                         kWaitEach * std::min(cap, (double)p->n_chunks * (double)piece_tiles);
             }
         } else {
             for (auto &g : p->groups) {
@@ -191,6 +198,14 @@ int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
     if (us) *us = best;
     return best_id;
 }
+
+int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
+{
+    if (us) (void)launch_tile(p, cus, whole_rows, us);
+    return cheapest_tile(p, cus, whole_rows, false, nullptr);
+}
+
+int launch_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us) { return cheapest_tile(p, cus, whole_rows, true, us); }
 
 void release(ficco_plan_t *p)
 {
@@ -260,7 +275,7 @@ int select_tile(ficco_plan_t *p, bool in_place)
     if (p->tile && (p->grouped || (pair == p->tile_for_pair && whole_rows == p->tile_whole_rows && p->tile_col_lists == p->tile_for_lists))) return FICCO_OK;
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-    const int tile = p->tile_opt ? p->tile_opt : choose_tile(p, cus, whole_rows);
+    const int tile = p->tile_opt ? p->tile_opt : launch_tile(p, cus, whole_rows, nullptr);
     const TileShape ts = tile_shape(tile);
     if (ts.bm == 0) return FICCO_ERR_ARG;
     int grid = 0;
@@ -272,6 +287,7 @@ int select_tile(ficco_plan_t *p, bool in_place)
         if (tiles < grid) grid = (int)tiles;
     }
     p->tile = tile;
+    p->tile_told = p->tile_opt ? p->tile_opt : choose_tile(p, cus, whole_rows);
     p->resident_grid = grid;
     p->tile_for_pair = pair;
     p->tile_whole_rows = whole_rows;
@@ -789,7 +805,7 @@ int ficco_plan_set(ficco_plan_t *p, int option, int64_t value)
         p->timing = (int)value;
         break;
     case FICCO_OPT_TILE:
-        if (value < 0 || value > FICCO_TILE_256x192) return FICCO_ERR_ARG;      // (64x128 is the library's own choice only)
+        if (value < 0 || value > FICCO_TILE_256x192) return FICCO_ERR_ARG;      // (64x128 and its parts are the library's own choice only)
         p->tile_opt = (int)value;
         break;
     case FICCO_OPT_FLAG_WRITE:
@@ -871,7 +887,7 @@ int ficco_plan_info(const ficco_plan_t *p, ficco_plan_info_t *out)
     o.n_chunks = p->n_chunks;
     o.n_groups = (int32_t)p->groups.size();
     o.chunk_rows = p->m;
-    TileShape ts = tile_shape(p->tile);
+    TileShape ts = tile_shape(p->tile_told);
     o.tile_m = ts.bm; o.tile_n = ts.bn; o.tile_k = p->tile ? kBK : 0;
     o.resident_grid = p->resident_grid;
     o.copy_backend = p->backend;

@@ -1,0 +1,89 @@
+"""The parts that tiles are cut into, 64x64 and 32x64, in each kernel that has them - row pieces, column pieces, one launch per step
+and per shard, output streaming, expert-parallel - at their edges (few rows, one column block, remainders of rows and columns),
+and over one to more than two rounds of their rings, odd and even k-tiles: bit for bit what a forced 256x256 tile gives. And
+what a plan tells of its tile stays the whole one."""
+import ctypes as C
+import os
+import sys
+
+import pytest
+
+import paper_2512_10236_amd as ficco
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import internal
+import test_gpu_small_tile as small
+
+torch = pytest.importorskip("torch")
+
+T64x64, T32x64 = 11, 12
+SHARD = dict(small.SCHEDULE, shard=ficco.FICCO_SHARD)
+CASES = [
+    ("rows", 512, 1024, 1024, 4, 1, T64x64), ("rows", 1024, 1024, 1000, 8, 1, T64x64), ("rows", 1000, 576, 1000, 8, 1, T64x64),
+    ("rows", 8, 64, 72, 8, 1, T32x64), ("rows", 132, 832, 136, 4, 1, T32x64), ("rows", 66, 4096, 520, 2, 1, T32x64),
+    ("columns", 280, 1088, 776, 2, 2, T32x64), ("columns", 1000, 1088, 1000, 2, 3, T64x64),
+    ("fused", 520, 1088, 1032, 4, 1, T64x64), ("fused", 264, 704, 264, 8, 1, T32x64),
+    ("shard", 264, 1088, 520, 8, 1, T32x64), ("shard", 8000, 704, 1000, 8, 1, T64x64),
+    ("scatter", 264, 704, 200, 8, 1, T32x64), ("scatter", 1024, 704, 1000, 8, 1, T64x64),
+    ("experts", 665, 1024, 520, 4, 2, T32x64), ("experts", 1000, 704, 1000, 4, 1, T64x64)]
+
+
+def _pick(plan):
+    f = ficco.load()._ZN5ficco11launch_tileEPK12ficco_plan_sibPd
+    f.argtypes, f.restype = [C.c_void_p, C.c_int, C.c_bool, C.POINTER(C.c_double)], C.c_int
+    return f(plan, internal.CUS, False, None)
+
+
+def _tiles(case):
+    plan = small._plan(*case[:6])
+    try:
+        return _pick(plan), internal.choose_tile(plan)[0]
+    finally:
+        ficco.ficco_destroy(plan)
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-%dx%dx%d-%dx%d-%d" % c)
+def test_rule_picks_the_part(case, monkeypatch):
+    monkeypatch.setattr(small, "SCHEDULE", SHARD)
+    assert _tiles(case)[0] == case[6]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-%dx%dx%d-%dx%d-%d" % c)
+def test_parts_have_the_bits_of_the_large_tile(gpu, case, monkeypatch):
+    monkeypatch.setattr(small, "SCHEDULE", SHARD)
+    kind, M, K, N = case[:4]
+    g = torch.Generator(device=gpu["dev"]).manual_seed(M + K + N)
+    A = torch.randn((M, K), generator=g, device=gpu["dev"]).bfloat16()
+    W = torch.randn((2 * K if kind == "experts" else K, N), generator=g, device=gpu["dev"]).bfloat16()
+    print(f"tile part {case}", flush=True)
+    got, tile = small._run(gpu, case[:6], ficco.FICCO_TILE_AUTO, A, W)
+    want, _ = small._run(gpu, case[:6], ficco.FICCO_TILE_256x256, A, W)
+    assert not torch.isnan(want.float()).any()
+    assert torch.equal(got, want)
+    assert tile == _tiles(case)[1]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,part,ring", [(40, 72, T32x64, 12), (1000, 1000, T64x64, 8)])
+def test_parts_over_their_rings(gpu, M, N, part, ring):
+    g = torch.Generator(device=gpu["dev"]).manual_seed(M)
+    for k_tiles in range(1, 2 * ring + 4):
+        K = 64 * k_tiles
+        A = torch.randn((M, K), generator=g, device=gpu["dev"]).bfloat16()
+        W = torch.randn((K, N), generator=g, device=gpu["dev"]).bfloat16()
+        out = []
+        for tile in (ficco.FICCO_TILE_AUTO, ficco.FICCO_TILE_256x256):
+            out.append(torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=gpu["dev"]))
+            print(f"ring {M}x{K}x{N} tile {tile}", flush=True)
+            torch.cuda.synchronize()
+            plan = ficco.ficco_plan(M, K, N, 1, 1, ficco.FICCO_FINE_PERSISTENT)
+            try:
+                ficco.ficco_plan_set(plan, ficco.FICCO_OPT_MODE, ficco.FICCO_MODE_GEMM_ONLY)
+                ficco.ficco_plan_set(plan, ficco.FICCO_OPT_TILE, tile)
+                assert tile or _pick(plan) == part
+                ficco.ficco_run(plan, None, A, W, out[-1], None, gpu["cs"], gpu["xs"])
+                ficco.ficco_query_stats(plan)
+            finally:
+                ficco.ficco_destroy(plan)
+        assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16)), K
