@@ -9,11 +9,12 @@
 // not hold next to each other: ds_read_b64_tr_b16 transposes on the way out of LDS (16 lanes read 4 rows x 16
 // columns, lane i gets column i).
 //
-// With FM = 1 a stage takes 0.16-0.25 us and M 64, K 4096, N 768 9.7 us, where packing the weight 2 bytes at a time and
-// running the resident kernel on it took 43. With the
-// stage's reads behind its loads instead of in front of them 11.7 us. Neither fewer bytes a stage (16 x 32 tiles, twice the
-// CUs, 9.7), nor reads a stage ahead in a second register buffer (11.1), nor wavefronts of their own for the loads (10.2)
-// made it faster; the last took 64-row tiles from 18.2 to 15.4 us (M 1024, K 4096, N 768).
+// With FM = 1 a stage of 20 KiB takes 0.19 us and M 64, K 4096, N 768 8.6 us: 46-50 bytes a cycle, which is what a CU draws
+// from beyond its L2 however much is in flight (64 from L2). Packing the weight first takes a
+// launch of 4 us more. With the stage's reads behind its loads instead of in front of them 11.7 us. Neither fewer bytes a stage (16 x 32
+// tiles, twice the CUs, 9.7: half of a weight line is drawn as a whole one), nor reads a stage ahead in a second register
+// buffer (11.1), nor wavefronts of their own for the loads (10.2), nor idle CUs that pull the XCD's lines into its L2 a few
+// stages ahead (8.6) made it faster.
 #include "ficco_internal.h"
 #include "ficco_mfma.h"
 
@@ -36,6 +37,9 @@ struct DirectCfg {
     static constexpr int LDS_BYTES = S * STAGE;
     static constexpr int THREADS = 256;
     static constexpr int LOADS = FM + 4;               // load instructions per wavefront per stage: 4 FM KiB of A and 16 KiB of W
+    // With 16 MFMAs a stage they go between its loads, which take 64 cycles each while all four wavefronts issue theirs: M 64,
+    // K 4096, N 768 17.9 -> 16.0 us, M 900, K 2048, N 1024 10.4 -> 9.8. With 4 or 8 nothing is gained (8.6 : 8.8, 11.6 : 11.4).
+    static constexpr bool BETWEEN = FM == 4;
     static_assert(FM == 1 || FM == 2 || FM == 4, "whole blocks of A per wavefront");
     static_assert(S >= 3 && (S - 2) * LOADS < 64, "vmcnt has 6 bits");
     static_assert(LDS_BYTES <= 160 * 1024 - 64, "ring must fit one CU");
@@ -79,7 +83,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_direct_kernel(DirectLaunch a)
 #pragma unroll
     for (int i = 0; i < 2; ++i) off_w[i] = (uint32_t)((i * 32 + wave * 8 + lane / 8) * a.N + w_slot * 8) * 2u;
 
-    auto issue = [&](int k, uint32_t stage) __attribute__((always_inline)) {
+    auto issue = [&](int k, uint32_t stage, auto behind) __attribute__((always_inline)) {
         // k values from here to the second half (which is the first again where K ends with it; it is then not used)
         const int up = half_tail && k == KS - 1 ? 0 : 64;
         const uint16_t *const ak = A + (int64_t)k * T::BK, *const wk = W + (int64_t)k * T::BK * a.N;
@@ -89,12 +93,14 @@ __global__ __launch_bounds__(T::THREADS) void gemm_direct_kernel(DirectLaunch a)
             set_lds_target<0>(lds0 + stage + half_a[i] * T::HALF + b % (2 * T::FM) * 1024);
             asm volatile("s_nop 0" ::: "memory");
             load_to_lds_16(ak + (half_a[i] ? up : 0), off_a[i]);
+            behind(i_c);
         });
         static_for<4>([&](auto i_c) __attribute__((always_inline)) {
             constexpr int i = decltype(i_c)::value, half = i / 2;
             set_lds_target<half * T::HALF + T::A_HALF + i % 2 * 4096>(lds0 + stage + wave * 1024);
             asm volatile("s_nop 0" ::: "memory");
             load_to_lds_16(wk + (half ? (int64_t)up * a.N : 0), off_w[i % 2]);
+            behind(std::integral_constant<int, T::FM + i>{});
         });
     };
 
@@ -121,14 +127,25 @@ __global__ __launch_bounds__(T::THREADS) void gemm_direct_kernel(DirectLaunch a)
         }
         __builtin_amdgcn_sched_barrier(0);
     };
+    constexpr int NMF = 4 * T::FM;         // MFMAs of a stage
+    auto product = [&](auto m_c) __attribute__((always_inline)) {
+        constexpr int q = decltype(m_c)::value / T::FM, i = decltype(m_c)::value % T::FM;
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fn[q], fm[q][i], acc[i], 0, 0, 0);
+    };
     auto multiply = [&](bool whole) __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (q < 2 || whole)
-#pragma unroll
-                for (int i = 0; i < T::FM; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fn[q], fm[q][i], acc[i], 0, 0, 0);
+        static_for<NMF / 2>([&](auto m) __attribute__((always_inline)) { product(m); });
+        if (whole) static_for<NMF / 2>([&](auto m) __attribute__((always_inline)) { product(std::integral_constant<int, NMF / 2 + m.value>{}); });
     };
+    // Behind load l of a stage's, where products go between the loads: products [l - 1, l) / (LOADS - 1) of them all.
+    auto products_behind = [&](auto l_c) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<NMF>([&](auto m) __attribute__((always_inline)) {
+            if constexpr (decltype(l_c)::value == 1 + m.value * (T::LOADS - 1) / NMF) product(m);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const auto nothing = [](auto) {};
     // One barrier per stage: behind it stage k has landed for everyone, and everyone has read stage k - 1, whose place
     // the next loads take.
     auto meet = [&](auto in_flight) __attribute__((always_inline)) {
@@ -138,14 +155,18 @@ __global__ __launch_bounds__(T::THREADS) void gemm_direct_kernel(DirectLaunch a)
     };
 
     const int ahead = min(KS, T::S - 1);
-    for (int k = 0; k < ahead; ++k) issue(k, k * T::STAGE);
+    for (int k = 0; k < ahead; ++k) issue(k, k * T::STAGE, nothing);
     uint32_t cur = 0, next = (T::S - 1) * T::STAGE;    // places in the ring of stage k and of stage k + S - 1
     int k = 0;
     for (; k + T::S - 1 < KS; ++k) {
         meet(std::integral_constant<int, (T::S - 2) * T::LOADS>{});
         read(cur);
-        issue(k + T::S - 1, next);
-        multiply(true);
+        if constexpr (T::BETWEEN) {
+            issue(k + T::S - 1, next, products_behind);
+        } else {
+            issue(k + T::S - 1, next, nothing);
+            multiply(true);
+        }
         cur = cur == (T::S - 1) * T::STAGE ? 0 : cur + T::STAGE;
         next = next == (T::S - 1) * T::STAGE ? 0 : next + T::STAGE;
     }

@@ -41,18 +41,19 @@ int scratch_of(int dev, unsigned char **out)
 // 16 * row_blocks rows x 64 columns. The direct kernel needs no packed weight but fetches every operand row once per
 // narrow tile, so it wins where a launch is a round or two of its tiles and loses where the resident kernel's big tiles
 // fill the chip. Estimates in us, from timings over M 1-8192, K 64-8192, N 8-4096: a stage of 128 k values takes 0.25 /
-// 0.31 / 0.55 us with 1 / 2 / 4 row blocks, a round starts in 1.5 us; the packed way takes choose_tile's
-// estimate and 4 us for the packing launch. Measured on either side, direct against packed: M 64, K 4096, N 768 9.7 : 37.6
-// and M 512, K 4096, N 1024 12.7 : 33.8 (packed without the 64x128 tile); M 1024, K 2048, N 2048 20.0 : 22.9 (packed by
-// the estimate); M 2048, K 4096, N 1024 41.7 : 30.1; M 4096, K 1024, N 1024 26.7 : 19.6.
+// 0.31 / 0.46 us with 1 / 2 / 4 row blocks, a round starts in 2 us; the packed way takes the tile rule's estimate and 6 us
+// for the packing launch. Over 600 random products (M 1-8192, K 512-8192, N 64-4096) the way taken is 0.1 % slower than the
+// fastest (0.4 with 0.55, 1.5 and 4 in the place of 0.46, 2 and 6; calls under 4.6 us, which the host takes, count as that).
+// Measured, direct against packed: M 576, K 4224, N 992 16.2 : 22.7, M 1225, K 2496, N 904 22.1 : 21.3, M 1596, K 1600, N
+// 1880 27.4 : 22.5, M 2594, K 4096, N 680 39.6 : 28.4.
 int direct_row_blocks(int64_t M, int64_t K, int64_t N, int cus, double packed_us)
 {
-    static const struct { int row_blocks; double stage; } cand[] = {{1, 0.25}, {2, 0.31}, {4, 0.55}};
-    double best = packed_us + 4.0;
+    static const struct { int row_blocks; double stage; } cand[] = {{1, 0.25}, {2, 0.31}, {4, 0.46}};
+    double best = packed_us + 6.0;
     int best_id = 0;
     for (auto &cd : cand) {
         const int64_t tiles = ((M + 16 * cd.row_blocks - 1) / (16 * cd.row_blocks)) * ((N + 63) / 64);
-        const double t = (double)((tiles + cus - 1) / cus) * (1.5 + cd.stage * (double)((K + 127) / 128)) + 2.0;
+        const double t = (double)((tiles + cus - 1) / cus) * (2.0 + cd.stage * (double)((K + 127) / 128)) + 2.0;
         if (t < best) { best = t; best_id = cd.row_blocks; }
     }
     return best_id;
