@@ -10,11 +10,11 @@
 // columns, lane i gets column i).
 //
 // With FM = 1 a stage of 20 KiB takes 0.19 us and M 64, K 4096, N 768 8.6 us: 46-50 bytes a cycle, which is what a CU draws
-// from beyond its L2 however much is in flight (64 from L2). Packing the weight first takes a
-// launch of 4 us more. With the stage's reads behind its loads instead of in front of them 11.7 us. Neither fewer bytes a stage (16 x 32
-// tiles, twice the CUs, 9.7: half of a weight line is drawn as a whole one), nor reads a stage ahead in a second register
-// buffer (11.1), nor wavefronts of their own for the loads (10.2), nor idle CUs that pull the XCD's lines into its L2 a few
-// stages ahead (8.6) made it faster.
+// from beyond its L2 however much is in flight (64 from L2). Packing the weight first takes a launch of 4 us more. With the
+// stage's reads behind its loads instead of in front of them 11.7 us. Neither fewer bytes a stage (16 x 32 tiles, twice the
+// CUs, 9.7: half of a weight line is drawn as a whole one), nor reads a stage ahead in a second register buffer (11.1), nor
+// wavefronts of their own for the loads (10.2), nor idle CUs that pull the XCD's lines into its L2 a few stages ahead (no
+// change) made it faster.
 #include "ficco_internal.h"
 #include "ficco_mfma.h"
 
