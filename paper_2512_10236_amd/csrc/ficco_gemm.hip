@@ -1035,9 +1035,10 @@ typedef TileCfg<64, 256, 1, 4, 3> T64x256;
 typedef TileCfg<32, 256, 1, 4, 4> T32x256;
 typedef TileCfg<128, 192, 2, 2, 3> T128x192;       // column counts that are multiples of 192 but not of 256
 typedef TileCfg<256, 192, 2, 2, 2> T256x192;
-// For launches that leave CUs idle with every larger tile. A CU draws about 32 bytes a cycle from L2 and beyond, whatever
-// the tile, so a k-tile's time is its bytes: 24 KiB in 0.27 us here, 32 KiB in 0.40 with 128x128, and a short launch gains
-// by spreading over more CUs. Six stages keep 120 KiB of loads in flight. M 1024, K 4096, N 768 30.6 -> 24.6 us.
+// For launches that leave CUs idle with every larger tile. A CU draws 45-52 bytes a cycle from beyond its L2, about 32 when
+// all of them do, whatever the tile, so a k-tile's time is its bytes: 24 KiB in 0.24-0.27 us here, 32 KiB in 0.31-0.40 with
+// 128x128, and a short launch gains by spreading over more CUs. Six stages keep 120 KiB of loads in flight. M 1024, K 4096,
+// N 768 30.6 -> 24.6 us.
 typedef TileCfg<64, 128, 2, 2, 6> T64x128;
 typedef TileCfg<64, 64, 2, 2, 8> T64x64;           // parts (is_part), rings of four and six pairs of stages
 typedef TileCfg<32, 64, 2, 2, 12> T32x64;
