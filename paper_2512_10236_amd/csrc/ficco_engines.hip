@@ -216,8 +216,7 @@ int engines_prepare(ficco_plan_t *p, bool touches_host, std::vector<int> &eng, i
     // for (FICCO_OPT_FLAG_WRITE = 2), every transfer is followed by a 4-byte flag copy instead.
     if (p->sig_poll < 0) {
         p->sig_poll = 0;
-        // table entries: [0, n) transfers; with packing also [n, 2n) Gather and [2n, 3n) Scatter copies
-        const int n_tab = p->packing ? 3 * n : n;
+        const int n_tab = signals_of(p);
         std::vector<uint64_t> addr(n_tab, 0);
         bool ok = p->flag_write == 0;
         for (int i = 0; i < n_tab && ok; ++i) {
@@ -602,8 +601,7 @@ int run_engines(ficco_plan_t *p, const void *A_src, void *A_dev, void *C_dev, vo
         // The launches watch the Gather copies' completion signals, or, when the transfers cross the host
         // link (where polling host memory would compete with them), flags raised by a 4-byte copy
         // behind each Gather copy. The final wait for the Scatter copies is a single wavefront.
-        // (signals n ... 3n - 1 of the table, which have no flags to pass anything on in)
-        const Gate pgate{nullptr, p->d_sig_value, kRunTag | p->run_index, p->d_status, (uint32_t *)p->h_status, spin_ticks};
+        const Gate pgate{p->d_flags, p->d_sig_value, kRunTag | p->run_index, p->d_status, (uint32_t *)p->h_status, spin_ticks};
         const Gate ggate = poll_signals ? pgate : gate;
         const size_t piece_a = (size_t)p->m * row_bytes_a, piece_c = (size_t)p->m * row_bytes_c;
         for (size_t g = 0; g < p->groups.size(); ++g) {

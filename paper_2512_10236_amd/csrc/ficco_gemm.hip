@@ -513,7 +513,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_blocks_kernel(GemmLaunch a)
     if (a.n_wait > 0) {
         __shared__ int s_go;
         if (threadIdx.x < 64) {
-            const int ok = wait_ready_all(a.gate, a.n_wait, a.gate.flags ? pace_of(gridDim.x, gridDim.x) : Pace{1, 1}, [&](int i) { return a.wait_chunks[i]; });
+            const int ok = wait_ready_all(a.gate, a.n_wait, pace_of(gridDim.x, gridDim.x), [&](int i) { return a.wait_chunks[i]; });
             if (threadIdx.x == 0) s_go = ok;
         }
         __syncthreads();                   // also orders the tile's loads after the flag reads

@@ -159,7 +159,7 @@ __host__ __device__ inline uint32_t resident_list_draws(int64_t list_tiles, int 
 // run's epoch, into the piece's flag in device memory, which no transfer writes then - and watches that flag on all others.
 constexpr uint32_t kRunTag = 0x80000000u;
 struct Gate {
-    uint32_t *flags;              // nullptr where only the signals are watched and nothing is passed on
+    uint32_t *flags;              // one for each signal of the table
     const uint64_t *sig_value;    // device table of addresses, or nullptr to use flags
     uint32_t epoch;               // of the run; with signals kRunTag | its number, which no flag copy and no earlier run writes
     uint32_t *status;             // device word every waiting workgroup watches

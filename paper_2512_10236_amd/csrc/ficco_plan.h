@@ -161,6 +161,10 @@ inline bool is_resident(const ficco_plan_t *p) { return p->schedule == FICCO_FIN
 // shard a piece belongs to: row pieces are numbered shard-major (j*c + s), column pieces slice-major (s*G + j)
 inline int shard_of(const ficco_plan_t *p, int chunk) { return is_2d(p) ? chunk % p->G : chunk / p->c; }
 
+// Signals that kernels watch, each with a flag of its own: [0, n) the transfers', with packing also [n, 2n) the Gather and
+// [2n, 3n) the Scatter copies'.
+inline int signals_of(const ficco_plan_t *p) { return p->packing ? 3 * p->n_chunks : p->n_chunks; }
+
 // Rows one launch covers as equal-height blocks: contiguous runs of chunks are merged so that a
 // monolithic launch is one block of M rows and a shard-major fused step is one block too.
 struct LaunchShape { int n_blocks; int64_t rows_per_block; bool contiguous; int64_t row0; };

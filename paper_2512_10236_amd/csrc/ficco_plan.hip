@@ -311,7 +311,8 @@ int finalize(ficco_plan_t *p)
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0) p->wall_clock_khz = khz;
 
     const int n = p->n_chunks;
-    const size_t words = (size_t)n * kFlagStrideWords + 2 * kFlagStrideWords + 32;   // flags | ticket | status | 128 B scratch
+    const size_t flag_words = (size_t)signals_of(p) * kFlagStrideWords;
+    const size_t words = flag_words + 2 * kFlagStrideWords + 32;   // flags | ticket | status | 128 B scratch
     // Flags and the status word are read by running kernels at system scope while a copy engine or
     // another queue writes them: that is only coherent for fine-grained memory (ordinary device
     // memory is coherent at kernel boundaries only).
@@ -323,7 +324,7 @@ int finalize(ficco_plan_t *p)
     HIP_TRY(hipDeviceSynchronize());
     p->d_flags = p->d_words;
     p->d_ticket = p->d_ticket_mem;
-    p->d_status = p->d_words + (size_t)n * kFlagStrideWords + kFlagStrideWords;
+    p->d_status = p->d_words + flag_words + kFlagStrideWords;
     const size_t n_k0 = is_2d(p) ? p->slice_k0.size() : 0;
     if (hipMalloc((void **)&p->d_tables, sizeof(int32_t) * (4 * (size_t)n + n_k0)) != hipSuccess) { release(p); return FICCO_ERR_ALLOC; }
     p->d_arrival = p->d_tables;

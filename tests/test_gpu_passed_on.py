@@ -1,6 +1,6 @@
 """Waits of launches with many workgroups, most of which learn that a piece has landed from the workgroup that saw it: row
-pieces of one and of several tiles, column pieces, one launch per step, expert-parallel, and the packed fused schedule, whose
-signals have no flags. Every run of a plan gets another activation over a poisoned landing buffer, with runs that wait for
+pieces of one and of several tiles, column pieces, one launch per step, expert-parallel, and the packed fused schedule, where it is
+the copies into the packed input that they wait for. Every run of a plan gets another activation over a poisoned landing buffer, with runs that wait for
 flags and runs that wait for nothing in between, and each result is that of the product alone, bit for bit."""
 import pytest
 
