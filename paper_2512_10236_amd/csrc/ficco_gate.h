@@ -72,13 +72,10 @@ static __device__ __forceinline__ int peek_ready(const Gate &g, int chunk, int p
 // The same for several pieces, piece_of(0) ... piece_of(n - 1), by one whole wavefront: lane l watches pieces l, l + 64,
 // ... A look at a signal is a round trip to host memory of 1-2 us, and a wave that looked at its pieces one after the
 // other paid one for each of them, landed or not; this way it pays one for 64. But waves that look at all their pieces all
-// the time swamp the host link, which the transfers' own signals cross too. So on the polls on which a wave looks there
-// (pace_of) it looks at all of them first, then at the last one that is missing (pieces are listed in the order in
-// which they leave), and at all again when that one has landed, every kLookEvery polls, and before it gives up; kLookFew
-// pieces are few enough to be looked at all the time. M 1675, K 3264, N 7496, eight experts in four steps, 32 pieces a tile,
-// every workgroup looking on every poll: one after the other 590 us, all of them all the time 887-907, this way 579.
+// the time swamp the host link, which the transfers' own signals cross too: PollPlan. M 1675, K 3264, N 7496, eight experts
+// in four steps, 32 pieces a tile, every workgroup at the signals on every poll: one after the other 590 us, all of them all
+// the time 887-907, this way 579.
 // The limit counts from the last time that a piece was seen to land. Returns the same value in every lane.
-constexpr int kLookEvery = 8, kLookFew = 2;
 template <class PieceFn>
 static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, Pace pace, PieceFn piece_of)
 {
@@ -88,11 +85,12 @@ static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, Pace 
         int waiting = base + lane < n;
         const int piece = piece_of(waiting ? base + lane : base);
         uint64_t missing = __ballot(waiting);
-        int all = 1, late = 0;
-        for (int polls = 1;; ++polls) {
-            const int look = late || (polls + blockIdx.x) % pace.every == 0;
-            const int mine = all || lane == 63 - __builtin_clzll(missing);
-            const int landed = waiting && mine && peek_ready(g, piece, pace.every > 1, look);
+        int late = 0;
+        for (PollPlan poll(pace.every, blockIdx.x);;) {
+            const int last = lane == 63 - __builtin_clzll(missing);
+            const int landed = waiting && (poll.flags || last) &&
+                               peek_ready(g, piece, pace.every > 1, (uint32_t)__builtin_popcountll(missing >> lane) <= poll.signals);
+            const int last_landed = __any(landed && last);
             if (landed) waiting = 0;
             missing = __ballot(waiting);
             if (!missing) {
@@ -104,7 +102,7 @@ static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, Pace 
             const int last_look = late && !any;
             late = wall_clock64() - t0 > g.spin_limit_ticks;
             int give_up = 0;
-            if (lane == 0 && look) {
+            if (lane == 0 && poll.signals) {
                 if (__hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) {
                     give_up = 1;
                 } else if (last_look) {
@@ -114,8 +112,7 @@ static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, Pace 
                 }
             }
             if (__any(give_up)) return 0;
-            const int last_landed = any && !all;
-            all = last_landed || late || polls % kLookEvery == 0 || __builtin_popcountll(missing) <= kLookFew;
+            poll.next(last_landed, late, (uint32_t)__builtin_popcountll(missing));
             if (!last_landed) nap(pace);
         }
     }

@@ -182,6 +182,35 @@ __device__ inline Pace pace_of(uint32_t workgroups, uint32_t same)
     const uint32_t n = same / 4 > workgroups / 32 ? same / 4 : workgroups / 32;
     return {n < 1 ? 1 : n > 16 ? 16 : n, same < 96 ? 1 : same / 24};
 }
+// What a wavefront that waits for several pieces looks at on each of its polls: on one of `every` at the signal of the last
+// one that is missing (pieces are listed in the order in which they leave), on all others at its flag alone. When it has
+// landed the poll behind it is at all flags, and the next look at the signals is a wide one, at those of the kLookWide last missing
+// pieces (of all, where few workgroups wait and `every` is 1); so is every kLookEvery-th, and each where no more than kLookFew
+// pieces are missing. Before it gives up it looks at everything. Pieces that have landed before a wait thus cost it one interval for each kLookWide of them and one more, also where
+// nobody else passes them on.
+// Wide looks are dear where hundreds of workgroups have them at the same time (us a pass; on the first poll of every wait / on
+// the poll behind a landing / this way: launches per step, M 8192, K 1024, N 1024 over eight shards of four pieces 222 / 124 /
+// 116; all of M 2048, K 192, N 2048 behind eight shards 69 / 42 / 41), and so are wider ones (at all missing pieces: eight
+// experts, four steps, 32 pieces a tile, M 1675, K 3264, N 7496 514 against 508).
+constexpr uint32_t kLookEvery = 8, kLookFew = 2, kLookWide = 8;
+struct PollPlan {
+    uint32_t every, polls, looks, wide;
+    uint32_t signals;              // this poll: at the signals of that many of the missing pieces, from the last one down ...
+    int flags = 1;                 // ... and at the flags of all of them, or of the last one
+    int again = 0;                 // the next look is a wide one
+    __host__ __device__ PollPlan(uint32_t every_, uint32_t phase)
+        : every(every_), polls(phase), looks(0), wide(every_ == 1 ? 64 : kLookWide), signals(phase % every_ == 0 ? wide : 0) {}
+    // last_landed: the last one that was missing has; late: the limit is over; missing: pieces
+    __host__ __device__ void next(int last_landed, int late, uint32_t missing)
+    {
+        const int turn = ++polls % every == 0, few = missing <= kLookFew;
+        looks += (uint32_t)turn;
+        again |= last_landed;
+        signals = late ? 64 : !turn ? 0 : few || again || looks % kLookEvery == 0 ? wide : 1;
+        if (turn) again = 0;
+        flags = last_landed || late || few || signals > 1;
+    }
+};
 
 // One GEMM launch over a list of equal-height row blocks of A/C (one block for a monolithic or
 // per-piece launch, G blocks for a fused step).
