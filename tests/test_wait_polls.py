@@ -2,7 +2,7 @@
 replays its waits, alone (nobody passes landings on), for every interval between looks at the signals and every phase.
 Pieces that have landed, before a wait or together during it, in whichever order they are listed, are seen within one interval for the last one
 and one for each wide look that the others take (at once where every poll is a look); a wait whose limit is over looks at everything;
-and in between it looks no more often than it may."""
+and in between it looks no more often than it may. And those that wait for the same piece take turns."""
 import os
 import subprocess
 
@@ -12,7 +12,9 @@ from paper_2512_10236_amd import _build
 
 PROGRAM = r"""
 #include "ficco_internal.h"
+#include <algorithm>
 #include <cstdio>
+#include <vector>
 using namespace ficco;
 
 // polls until n pieces are seen; those with bit i of `first` land before the wait, the others before poll `when`
@@ -40,9 +42,24 @@ static int bad(const char *what, int n, int every, int phase, int got)
     return 1;
 }
 
+// workgroups first, first + step, ... of a launch: on every poll as many of them look at the signals as on any other, give or take `slack`
+static int turns(int first, int step, int grid, int every, int slack)
+{
+    std::vector<int> look(every);
+    for (int b = first; b < grid; b += step) ++look[poll_phase((uint32_t)b) % (uint32_t)every];
+    const auto mm = std::minmax_element(look.begin(), look.end());
+    return *mm.second - *mm.first <= slack ? 0 : bad("turns", step, every, first, *mm.second);
+}
+
 int main()
 {
     int waits = 0;
+    for (int every = 1; every <= 16; ++every)
+        for (int grid : {64, 96, 224, 256, 512}) {
+            for (int x = 0; x < kTicketLists; ++x)
+                if (turns(x, kTicketLists, grid, every, 1)) return 1;
+            if (turns(0, 1, grid, every, kTicketLists)) return 1;
+        }
     for (int every = 1; every <= 16; ++every)
         for (int phase = 0; phase < 256; ++phase)
             for (int n : {1, 2, 3, 4, 8, 16, 63, 64}) {
