@@ -6,12 +6,20 @@ import paper_2512_10236_amd as ficco
 from paper_2512_10236_amd.binding import _ptr
 
 CUS = 256
-TILES = {1: (256, 256), 2: (128, 128), 3: (256, 128), 4: (128, 256), 5: (64, 256), 6: (32, 256), 7: (128, 128), 8: (128, 192), 9: (256, 192), 10: (64, 128)}
+TILES = {1: (256, 256), 2: (128, 128), 3: (256, 128), 4: (128, 256), 5: (64, 256), 6: (32, 256), 7: (128, 128), 8: (128, 192), 9: (256, 192), 10: (64, 128), 11: (64, 64), 12: (32, 64)}
 
 
 def choose_tile(plan, whole_rows=False):
     """(tile rows, tile columns), estimated microseconds: the tile rule's answer for a plan on a whole MI355X."""
     f = ficco.load()._ZN5ficco11choose_tileEPK12ficco_plan_sibPd
+    f.argtypes, f.restype = [C.c_void_p, C.c_int, C.c_bool, C.POINTER(C.c_double)], C.c_int
+    us = C.c_double()
+    return TILES[f(plan, CUS, whole_rows, C.byref(us))], us.value
+
+
+def launch_tile(plan, whole_rows=False):
+    """The same for the tile that is launched, which may be a part of one."""
+    f = ficco.load()._ZN5ficco11launch_tileEPK12ficco_plan_sibPd
     f.argtypes, f.restype = [C.c_void_p, C.c_int, C.c_bool, C.POINTER(C.c_double)], C.c_int
     us = C.c_double()
     return TILES[f(plan, CUS, whole_rows, C.byref(us))], us.value

@@ -1,7 +1,7 @@
 """The 64x128 tile, which the library picks for launches that leave CUs idle with every larger one, in each kernel that has
 it - row pieces, column pieces, one launch per step, output streaming and expert-parallel - at the edges of the tile (one
-row, one column block, remainders) and with fewer k-tiles than its ring of six stages, as many and more: bit for bit what
-a forced 256x256 tile gives. And that it stays the library's own choice: the option refuses it as before."""
+row, one column block, remainders of eight columns) and with fewer k-tiles than its ring of six stages, as many and more: bit for
+bit what a forced 256x256 tile gives. And that it stays the library's own choice: the option refuses it as before."""
 import os
 import sys
 
@@ -15,13 +15,13 @@ import internal
 torch = pytest.importorskip("torch")
 
 CASES = [
-    ("rows", 512, 1024, 1024, 4, 1), ("rows", 8, 1024, 136, 8, 1), ("rows", 8 * 65, 1088, 264, 8, 1), ("rows", 2 * 64 * 4, 4096, 128, 2, 4),
-    ("rows", 1024, 1024, 2040, 8, 2), ("rows", 16384, 256, 64, 1, 1), ("rows", 624, 256, 3088, 1, 1), ("rows", 624, 320, 3088, 1, 1),
+    ("rows", 504, 768, 2056, 8, 1), ("rows", 4112, 128, 264, 4, 4), ("rows", 8224, 64, 120, 8, 4), ("rows", 8224, 384, 120, 8, 4), ("rows", 10240, 1088, 72, 8, 4),
+    ("rows", 1024, 1024, 2040, 8, 2), ("rows", 624, 256, 3088, 1, 1), ("rows", 624, 320, 3088, 1, 1),
     ("rows", 624, 384, 3088, 1, 1), ("rows", 624, 448, 3088, 1, 1),
-    ("columns", 512, 1024, 1024, 4, 3), ("columns", 130, 1088, 776, 2, 2), ("columns", 624, 320, 3088, 2, 5),
-    ("fused", 520, 1088, 1032, 4, 1), ("fused", 624, 320, 3088, 2, 1),
+    ("columns", 504, 1024, 2056, 8, 3), ("columns", 2056, 384, 776, 8, 3), ("columns", 624, 320, 3088, 2, 5),
+    ("fused", 16, 1088, 2056, 8, 2), ("fused", 624, 320, 3088, 2, 1),
     ("scatter", 520, 1088, 1032, 8, 1), ("scatter", 624, 256, 3088, 2, 1),
-    ("experts", 700, 1024, 520, 4, 2)]
+    ("experts", 1000, 1024, 1032, 4, 2), ("experts", 3000, 320, 520, 4, 4), ("experts", 300, 768, 3088, 8, 4)]
 SCHEDULE = dict(rows=ficco.FICCO_FINE_PERSISTENT, columns=ficco.FICCO_FINE_2D, fused=ficco.FICCO_FINE_FUSED, scatter=ficco.FICCO_FINE_PERSISTENT)
 
 
@@ -50,7 +50,7 @@ def test_option_refuses_the_tile():
 def test_rule_picks_the_tile(kind, M, K, N, G, c):
     plan = _plan(kind, M, K, N, G, c)
     try:
-        assert internal.choose_tile(plan)[0] == (64, 128)
+        assert internal.launch_tile(plan)[0] == (64, 128)
     finally:
         ficco.ficco_destroy(plan)
 
