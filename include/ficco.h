@@ -230,7 +230,7 @@ typedef struct ficco_plan_info {
     int32_t n_groups;                /* GEMM launches per run                                    */
     int64_t chunk_rows;              /* rows of one piece (M / n_chunks; M / shards for FICCO_FINE_2D; 0 for
                                         grouped plans, whose pieces differ: see ficco_plan_pieces)   */
-    int32_t tile_m, tile_n, tile_k;  /* chosen tile; small launches may cut it into parts, a workgroup each */
+    int32_t tile_m, tile_n, tile_k;  /* chosen workgroup tile (of the latest run; small launches may get tiles that FICCO_OPT_TILE does not name) */
     int32_t resident_grid;           /* workgroups of the resident kernel (0 if not used)        */
     int32_t copy_backend, links;     /* as resolved by the last run (0 before the first run)     */
     double  otb;                     /* static op-to-byte of one launch's GEMM (Sec. IV-B)       */

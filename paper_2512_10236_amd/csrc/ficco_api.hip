@@ -36,8 +36,8 @@ int ficco_run(ficco_plan_t *p, const void *A_src, void *A_dev, const void *W_dev
     if (rc) return rc;
     if ((rc = select_tile(p, do_gemm && overlap(C_dev, 2 * p->M * p->N, A_dev, 2 * p->M * p->K)))) return rc;
     if (p->tile_col_lists > 1 && (is_resident(p) || p->grouped)) {     // refuse before anything is enqueued
-        const TileShape ts = tile_shape(p->tile_told);
-        if (p->tile_col_lists > (p->N + ts.bn - 1) / ts.bn) return FICCO_ERR_ARG;
+        const TileShape ts = tile_shape(p->tile);
+        if (p->tile_col_lists > std::min((p->N + ts.bn - 1) / ts.bn, widest_lists(p->N))) return FICCO_ERR_ARG;
     }
 
     bool dev = false;

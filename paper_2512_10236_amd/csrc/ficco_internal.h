@@ -14,7 +14,7 @@ enum TileId : int { TILE_256x256 = 1, TILE_128x128 = 2, TILE_256x128 = 3, TILE_1
                     TILE_64x128 = 10, TILE_64x64 = 11, TILE_32x64 = 12, TILE_COUNT = 13 };
 
 // The last two are parts that a launch's tiles are cut into, a workgroup each, where that is faster than whole ones (few
-// tiles, CUs idle). What a plan tells is the whole tile.
+// tiles, CUs idle).
 inline bool is_part(int tile) { return tile == TILE_64x64 || tile == TILE_32x64; }
 
 struct TileShape { int bm, bn, lds_bytes, threads; };

@@ -97,8 +97,7 @@ struct ficco_plan_s {
 
     // resources (allocated by finalize())
     bool finalized = false;
-    int tile = 0;                        // of the latest run's launches (select_tile); 0: none chosen yet
-    int tile_told = 0;                   // the whole tile where `tile` is a part of one
+    int tile = 0;                        // of the latest run (select_tile); 0: none chosen yet
     int resident_grid = 0;
     bool tile_for_pair = false, tile_whole_rows = false;   // what `tile` was chosen for ...
     int tile_for_lists = 0;                                // ... and tile_col_lists at the time
@@ -193,8 +192,10 @@ inline Extent piece_extent(const ficco_plan_t *p, int chunk)
 int build_lists(ficco_plan_t *p);
 // whole_rows: only tiles as wide as the output, where one is (N <= 256), so that a workgroup has read all it will read of
 // its rows of A before it stores them; us: the estimate for the tile chosen
-int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows = false, double *us = nullptr);   // the whole tile
-int launch_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us);                     // what the launch is made of: that or parts
+int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows = false, double *us = nullptr);
+// Column lists that N columns can have: as many as they fill of the narrowest whole tile. (Parts would fill more, but whether
+// a caller's lists are taken must not depend on whether a launch is cut into them.)
+inline int64_t widest_lists(int64_t N) { return (N + 127) / 128; }
 // ficco_gemm_static: row blocks (1, 2 or 4) of the direct kernel, 0 = pack the weight first, which takes packed_us
 int direct_row_blocks(int64_t M, int64_t K, int64_t N, int cus, double packed_us);
 inline bool overlap(const void *a, int64_t a_bytes, const void *b, int64_t b_bytes)

@@ -138,7 +138,7 @@ static bool runs_pair(const ficco_plan_t *p) { return (p->losses_of >= 0 ? p->lo
 // 9400; every tile forced in turn) the tile picked is 1.1 % slower than the fastest, 95 % of them within 7 %; without these
 // two terms 2.7 % and 12-18 % (M 9744, K 1152, N 7416, 4 x 4 pieces: 128x128 317 us, 128x256 242), with them but
 // without the last-step term below 1.3 %.
-static int cheapest_tile(const ficco_plan_t *p, int cus, bool whole_rows, bool with_parts, double *us)
+int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
 {
     static const struct { int id; double base, slope, start, next; int occ; } cand[] = {
         {TILE_256x256, 0.89, 0.39, 13, 8, 1}, {TILE_128x256, 0.49, 0.22, 10, 6, 1}, {TILE_256x128, 0.51, 0.21, 10, 7, 1},
@@ -153,12 +153,11 @@ static int cheapest_tile(const ficco_plan_t *p, int cus, bool whole_rows, bool w
     const int lists = (is_resident(p) || p->grouped) && !(whole_rows && p->N <= 256) ? p->tile_col_lists : 0;
     for (auto &cd : cand) {
         TileShape ts = tile_shape(cd.id);
-        if (!with_parts && is_part(cd.id)) continue;
         if (whole_rows && p->N <= 256 && ts.bn < p->N) continue;
         const double cap = (double)cus * cd.occ;
         const int64_t tn = (p->N + ts.bn - 1) / ts.bn;
         // column lists that the caller asks for must not depend on how wide a tile this rule happens to like
-        if (lists > tn && lists <= (p->N + 127) / 128) continue;
+        if (lists > tn && lists <= widest_lists(p->N)) continue;
         auto cost = [&](int64_t tiles) {
             const double full = std::floor((double)tiles / cap), rem = (double)tiles - full * cap;
             const double steps = full * (cd.base + cd.slope) + (rem > 0 ? cd.base + cd.slope * rem / cap : 0.0);
@@ -198,14 +197,6 @@ static int cheapest_tile(const ficco_plan_t *p, int cus, bool whole_rows, bool w
     if (us) *us = best;
     return best_id;
 }
-
-int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
-{
-    if (us) (void)launch_tile(p, cus, whole_rows, us);
-    return cheapest_tile(p, cus, whole_rows, false, nullptr);
-}
-
-int launch_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us) { return cheapest_tile(p, cus, whole_rows, true, us); }
 
 void release(ficco_plan_t *p)
 {
@@ -275,7 +266,7 @@ int select_tile(ficco_plan_t *p, bool in_place)
     if (p->tile && (p->grouped || (pair == p->tile_for_pair && whole_rows == p->tile_whole_rows && p->tile_col_lists == p->tile_for_lists))) return FICCO_OK;
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-    const int tile = p->tile_opt ? p->tile_opt : launch_tile(p, cus, whole_rows, nullptr);
+    const int tile = p->tile_opt ? p->tile_opt : choose_tile(p, cus, whole_rows);
     const TileShape ts = tile_shape(tile);
     if (ts.bm == 0) return FICCO_ERR_ARG;
     int grid = 0;
@@ -287,7 +278,6 @@ int select_tile(ficco_plan_t *p, bool in_place)
         if (tiles < grid) grid = (int)tiles;
     }
     p->tile = tile;
-    p->tile_told = p->tile_opt ? p->tile_opt : choose_tile(p, cus, whole_rows);
     p->resident_grid = grid;
     p->tile_for_pair = pair;
     p->tile_whole_rows = whole_rows;
@@ -888,7 +878,7 @@ int ficco_plan_info(const ficco_plan_t *p, ficco_plan_info_t *out)
     o.n_chunks = p->n_chunks;
     o.n_groups = (int32_t)p->groups.size();
     o.chunk_rows = p->m;
-    TileShape ts = tile_shape(p->tile_told);
+    TileShape ts = tile_shape(p->tile);
     o.tile_m = ts.bm; o.tile_n = ts.bn; o.tile_k = p->tile ? kBK : 0;
     o.resident_grid = p->resident_grid;
     o.copy_backend = p->backend;

@@ -96,7 +96,7 @@ extern "C" int ficco_gemm_static(int64_t M, int64_t K, int64_t N, const void *A_
     // needs it too: the direct kernel's tiles are narrower than most outputs, and while one stores, another still reads
     // the same rows of A. The packed way then takes a tile as wide as the output.
     const bool over_a = overlap(C_dev, 2 * M * N, A_dev, 2 * M * K);
-    shape.tile = launch_tile(&shape, cus, over_a, &packed_us);
+    shape.tile = choose_tile(&shape, cus, over_a, &packed_us);
     const bool packed_only = over_a || (uintptr_t)W_dev % 16 || overlap(C_dev, 2 * M * N, W_dev, 2 * K * N);
     const int row_blocks = packed_only ? 0 : direct_row_blocks(M, K, N, cus, packed_us);
     if (row_blocks) {

@@ -17,14 +17,6 @@ def choose_tile(plan, whole_rows=False):
     return TILES[f(plan, CUS, whole_rows, C.byref(us))], us.value
 
 
-def launch_tile(plan, whole_rows=False):
-    """The same for the tile that is launched, which may be a part of one."""
-    f = ficco.load()._ZN5ficco11launch_tileEPK12ficco_plan_sibPd
-    f.argtypes, f.restype = [C.c_void_p, C.c_int, C.c_bool, C.POINTER(C.c_double)], C.c_int
-    us = C.c_double()
-    return TILES[f(plan, CUS, whole_rows, C.byref(us))], us.value
-
-
 def direct_row_blocks(M, K, N):
     """How ficco_gemm_static goes about a product: row blocks of the direct kernel, or 0 where it packs the weight."""
     f = ficco.load()._ZN5ficco17direct_row_blocksElllid

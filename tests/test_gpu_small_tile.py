@@ -50,7 +50,7 @@ def test_option_refuses_the_tile():
 def test_rule_picks_the_tile(kind, M, K, N, G, c):
     plan = _plan(kind, M, K, N, G, c)
     try:
-        assert internal.launch_tile(plan)[0] == (64, 128)
+        assert internal.choose_tile(plan)[0] == (64, 128)
     finally:
         ficco.ficco_destroy(plan)
 

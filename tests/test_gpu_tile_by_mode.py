@@ -71,10 +71,10 @@ def test_loss_profile_leaves_the_pair_its_tile(gpu, operands):
         ficco.ficco_destroy(plan)
 
 
-@pytest.mark.parametrize("m,k,n,c,lists", [(1024, 512, 256, 1, 2), (32768, 512, 512, 1, 4), (1024, 1024, 1536, 4, 8)])
+@pytest.mark.parametrize("m,k,n,c,lists", [(4096, 256, 256, 1, 2), (32768, 512, 512, 1, 4), (1024, 1024, 1536, 4, 8)])
 def test_column_lists_are_taken_wherever_a_tile_fits_them(gpu, m, k, n, c, lists):
     """Shapes whose own tile is too wide for the lists: they are taken all the same, before the first run and after it, and
-    more lists than columns of the narrowest tile are refused."""
+    more lists than columns of the narrowest whole tile are refused, also where the rule would cut the launch into parts."""
     g = torch.Generator(device=gpu["dev"]).manual_seed(7)
     ops = (torch.randn((m, k), generator=g, device=gpu["dev"]).bfloat16(), torch.randn((k, n), generator=g, device=gpu["dev"]).bfloat16())
     ops += (torch.empty_like(ops[0]), torch.empty((m, n), dtype=torch.bfloat16, device=gpu["dev"]))

@@ -1,8 +1,7 @@
 """The parts that tiles are cut into, 64x64 and 32x64, in each kernel that has them - row pieces, column pieces, one launch per step
 and per shard, output streaming, expert-parallel - at their edges (few rows, one column block, remainders of rows and columns),
-and over one to more than two rounds of their rings, odd and even k-tiles: bit for bit what a forced 256x256 tile gives. And
-what a plan tells of its tile stays the whole one."""
-import ctypes as C
+and over one to more than two rounds of their rings, odd and even k-tiles: bit for bit what a forced 256x256 tile gives. And a
+plan tells the tile that was launched."""
 import os
 import sys
 
@@ -16,7 +15,7 @@ import test_gpu_small_tile as small
 
 torch = pytest.importorskip("torch")
 
-T64x64, T32x64 = 11, 12
+T64x64, T32x64 = (64, 64), (32, 64)
 SHARD = dict(small.SCHEDULE, shard=ficco.FICCO_SHARD)
 CASES = [
     ("rows", 512, 1024, 1024, 4, 1, T64x64), ("rows", 1024, 1024, 1000, 8, 1, T64x64), ("rows", 1000, 576, 1000, 8, 1, T64x64),
@@ -28,28 +27,22 @@ CASES = [
     ("experts", 665, 1024, 520, 4, 2, T32x64), ("experts", 1000, 704, 1000, 4, 1, T64x64)]
 
 
-def _pick(plan):
-    f = ficco.load()._ZN5ficco11launch_tileEPK12ficco_plan_sibPd
-    f.argtypes, f.restype = [C.c_void_p, C.c_int, C.c_bool, C.POINTER(C.c_double)], C.c_int
-    return f(plan, internal.CUS, False, None)
-
-
-def _tiles(case):
+def _tile(case):
     plan = small._plan(*case[:6])
     try:
-        return _pick(plan), internal.choose_tile(plan)[0]
+        return internal.choose_tile(plan)[0]
     finally:
         ficco.ficco_destroy(plan)
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-%dx%dx%d-%dx%d-%d" % c)
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-%dx%dx%d-%dx%d" % c[:6])
 def test_rule_picks_the_part(case, monkeypatch):
     monkeypatch.setattr(small, "SCHEDULE", SHARD)
-    assert _tiles(case)[0] == case[6]
+    assert _tile(case) == case[6]
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-%dx%dx%d-%dx%d-%d" % c)
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-%dx%dx%d-%dx%d" % c[:6])
 def test_parts_have_the_bits_of_the_large_tile(gpu, case, monkeypatch):
     monkeypatch.setattr(small, "SCHEDULE", SHARD)
     kind, M, K, N = case[:4]
@@ -61,7 +54,7 @@ def test_parts_have_the_bits_of_the_large_tile(gpu, case, monkeypatch):
     want, _ = small._run(gpu, case[:6], ficco.FICCO_TILE_256x256, A, W)
     assert not torch.isnan(want.float()).any()
     assert torch.equal(got, want)
-    assert tile == _tiles(case)[1]
+    assert tile == case[6]
 
 
 @pytest.mark.gpu
@@ -81,7 +74,7 @@ def test_parts_over_their_rings(gpu, M, N, part, ring):
             try:
                 ficco.ficco_plan_set(plan, ficco.FICCO_OPT_MODE, ficco.FICCO_MODE_GEMM_ONLY)
                 ficco.ficco_plan_set(plan, ficco.FICCO_OPT_TILE, tile)
-                assert tile or _pick(plan) == part
+                assert tile or internal.choose_tile(plan)[0] == part
                 ficco.ficco_run(plan, None, A, W, out[-1], None, gpu["cs"], gpu["xs"])
                 ficco.ficco_query_stats(plan)
             finally:
