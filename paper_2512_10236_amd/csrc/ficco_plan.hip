@@ -130,14 +130,20 @@ static bool runs_pair(const ficco_plan_t *p) { return (p->losses_of >= 0 ? p->lo
 // tiles (M 16-8192, K 256-8192, N 64-4096; alone, pairs, one launch per step and per shard; every tile forced in turn) the
 // tile picked is 0.2-0.5 % slower than the fastest, and with them the fastest is 6-7 % faster than without in runs with
 // transfers, 28 % alone (us: M 512, K 4096, N 768 alone 64x128 19.4, 64x64 15.2, 32x64 12.3; the pair over four shards 66.1 /
-// 58.9 / 55.4; M 1024 of it over eight 69.5 / 61.6 / 69.2).
+// 58.9 / 55.4; M 1024 of it over eight 69.5 / 61.6 / 69.2). Over 2900 launches of K 8256-32704 the fastest whole tile is
+// 14-31 % slower than the one picked in runs with transfers, 67 % alone. In launches of more 64x128 tiles than CUs, which whole
+// tiles fill the chip with, parts stay where tiles follow row pieces as these land (with / without parts: 187 pairs of two
+// and four steps 1 : 1.018, 581 expert-parallel ones 1 : 1.012). In the others they are never the fastest by more than a little, and
+// the fits of 64x64 and 128x128 are not good enough to tell them apart there (alone 1 : 0.88 over 540, column pieces 0.965 over
+// 460, streamed output 0.982 over 450, launches per step 0.989 over 440; alone, 64x64 / the fastest whole tile: M 10240, K 1600,
+// N 192 17.6 / 14.5, M 20224, K 1472, N 64 16.7 / 14.1, M 25600, K 448, N 64 8.7 / 7.7): no parts there.
 // Padded (masked) rows and columns are paid in full.
-// Where tiles wait for pieces every workgroup that does costs kWaitEach, a round costs kWaitRound more (a draw from the lists' counters and a look at the piece's
-// signal, neither of which hides behind another tile of the same workgroup), and two workgroups per CU, which both draw and
-// look, another kWaitSecond. Over 520 all-gather pairs (2 to 8 shards, 1 to 32 pieces each, M 128-32768, K 512-8192, N 256-
-// 9400; every tile forced in turn) the tile picked is 1.1 % slower than the fastest, 95 % of them within 7 %; without these
-// two terms 2.7 % and 12-18 % (M 9744, K 1152, N 7416, 4 x 4 pieces: 128x128 317 us, 128x256 242), with them but
-// without the last-step term below 1.3 %.
+// Where tiles wait for pieces every workgroup that does costs kWaitEach, a round costs kWaitRound more (a draw from the
+// lists' counters and a look at the piece's signal, neither of which hides behind another tile of the same workgroup), and
+// two workgroups per CU, which both draw and look, another kWaitSecond. Over 520 all-gather pairs (2 to 8 shards, 1 to 32
+// pieces each, M 128-32768, K 512-8192, N 256-9400; every tile forced in turn) the tile picked is 1.1 % slower than the
+// fastest, 95 % of them within 7 %; without these two terms 2.7 % and 12-18 % (M 9744, K 1152, N 7416, 4 x 4 pieces: 128x128
+// 317 us, 128x256 242), with them but without the last-step term below 1.3 %.
 int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
 {
     static const struct { int id; double base, slope, start, next; int occ; } cand[] = {
@@ -151,8 +157,19 @@ int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
     int best_id = TILE_128x128;
     const double k_steps = (double)p->K / kBK;
     const int lists = (is_resident(p) || p->grouped) && !(whole_rows && p->N <= 256) ? p->tile_col_lists : 0;
+    bool parts = p->grouped || (p->schedule == FICCO_FINE_PERSISTENT && p->direction == FICCO_DIR_AG_GEMM && runs_pair(p));
+    if (!parts) {
+        int64_t rows = p->M;               // of the largest launch
+        if (!is_resident(p)) {
+            int pieces = 0;
+            for (auto &g : p->groups) pieces = std::max(pieces, g.pos_end - g.pos_begin);
+            rows = pieces * p->m;
+        }
+        parts = ((rows + 63) / 64) * ((p->N + 127) / 128) <= cus;
+    }
     for (auto &cd : cand) {
         TileShape ts = tile_shape(cd.id);
+        if (is_part(cd.id) && !parts) continue;
         if (whole_rows && p->N <= 256 && ts.bn < p->N) continue;
         const double cap = (double)cus * cd.occ;
         const int64_t tn = (p->N + ts.bn - 1) / ts.bn;

@@ -41,6 +41,27 @@ def test_rule_picks_the_part(case, monkeypatch):
     assert _tile(case) == case[6]
 
 
+@pytest.mark.parametrize("kind,M,K,N,G,c", [
+    ("alone", 10240, 1600, 192, 1, 1), ("alone", 20224, 1472, 64, 1, 1), ("alone", 25600, 448, 64, 4, 2), ("columns", 8560, 12032, 168, 4, 2),
+    ("scatter", 10344, 1024, 136, 4, 1), ("scatter", 23040, 2432, 64, 8, 1), ("fused", 9680, 5760, 184, 8, 1)])
+def test_rule_picks_whole_tiles_where_they_fill_the_chip(kind, M, K, N, G, c):
+    """Launches of more 64x128 tiles than CUs, each of which some whole tile does 2-18 % faster than 64x64."""
+    assert -(-M // 64) * -(-N // 128) > internal.CUS
+    plan = small._plan("rows" if kind == "alone" else kind, M, K, N, G, c)
+    try:
+        if kind == "alone":
+            ficco.ficco_plan_set(plan, ficco.FICCO_OPT_MODE, ficco.FICCO_MODE_GEMM_ONLY)
+        assert internal.choose_tile(plan)[0] not in (T64x64, T32x64)
+    finally:
+        ficco.ficco_destroy(plan)
+
+
+@pytest.mark.parametrize("case", [("rows", 6144, 2816, 320, 8, 4), ("experts", 6144, 2240, 320, 8, 1)], ids=lambda c: c[0])
+def test_rule_picks_parts_where_tiles_follow_their_pieces(case):
+    """As many tiles, but those of the last step count, and they are few: 150 us against 161, 140 against 148 (sixteen peers)."""
+    assert _tile(case) == T64x64
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-%dx%dx%d-%dx%d" % c[:6])
 def test_parts_have_the_bits_of_the_large_tile(gpu, case, monkeypatch):
