@@ -413,8 +413,11 @@ int ficco_query_stats(ficco_plan_t *p, ficco_stats_t *out)
     float ms = 0;
     // Copy-engine timestamps (system clock ticks) of every transfer of the run, read as the transfers complete, while the
     // run's kernels are still at work: behind the end of the run 64 of them held the host up for 10-15 us (M 16384, K 8192,
-    // N 3584 842 -> 831 us a pass). A transfer that is still out after a second is waited for behind the end of the run.
+    // N 3584 842 -> 831 us a pass). The host looks at the signals all the time, as the runtime does in hipEventSynchronize (the
+    // thread is on the processor for the whole of a call, either way and also with hipDeviceScheduleBlockingSync). Transfers
+    // that are still out a second from here are waited for behind the end of the run.
     const bool engines = p->last_had_copies && p->last_engines && !p->last_graph;
+    const auto spin_until = std::chrono::steady_clock::now() + std::chrono::seconds(1);
     uint64_t t_min = ~0ull, t_max = 0;
     double busy = 0;
     int q_done = 0;
@@ -429,7 +432,7 @@ int ficco_query_stats(ficco_plan_t *p, ficco_stats_t *out)
     for (; engines && q_done < p->n_chunks; ++q_done) {
         const int chunk = p->arrival[q_done];
         if (!travels(chunk)) continue;
-        if (!spin_on_signal(p->sig_data[chunk], 1.0) || !spin_on_signal(p->sig_flag[chunk], 1.0)) break;
+        if (!spin_on_signal(p->sig_data[chunk], spin_until) || !spin_on_signal(p->sig_flag[chunk], spin_until)) break;
         read_stamps(chunk);
     }
     HIP_TRY(hipEventSynchronize(p->ev_end));

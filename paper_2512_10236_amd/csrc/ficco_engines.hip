@@ -144,17 +144,16 @@ bool wait_signal(hsa_signal_t sgn, double limit_s)
 
 // The same, looking at the signal all the time: the runtime's wait gives the processor up for tens of microseconds after a
 // while, which is long beside what follows the last transfer of a run.
-bool spin_on_signal(hsa_signal_t sgn, double limit_s)
+bool spin_on_signal(hsa_signal_t sgn, std::chrono::steady_clock::time_point until)
 {
     hsa_signal_value_t v = hsa_signal_load_scacquire(sgn);
     if (v < 1) return v >= 0;
-    const auto t0 = std::chrono::steady_clock::now();
     for (;;) {
         for (int i = 0; i < 64; ++i) {
             if ((v = hsa_signal_load_scacquire(sgn)) < 1) return v >= 0;
             __builtin_ia32_pause();
         }
-        if (std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > limit_s) return false;
+        if (std::chrono::steady_clock::now() > until) return false;
     }
 }
 

@@ -234,7 +234,7 @@ int launch_2d(ficco_plan_t *p, const Gate &gate, bool gated, int grid, const voi
 // ---- copy-engine backend (ficco_engines.hip)
 hsa_status_t make_signal(hsa_signal_t *out);
 bool wait_signal(hsa_signal_t sgn, double limit_s);
-bool spin_on_signal(hsa_signal_t sgn, double limit_s);
+bool spin_on_signal(hsa_signal_t sgn, std::chrono::steady_clock::time_point until);
 uint64_t signal_value_address(hsa_signal_t sg);
 double engine_ticks_per_us();
 int engines_prepare(ficco_plan_t *p, bool touches_host, std::vector<int> &eng, int &links);
