@@ -10,11 +10,11 @@
 // columns, lane i gets column i).
 //
 // With FM = 1 a stage of 20 KiB takes 0.19 us and M 64, K 4096, N 768 8.6 us: 46-50 bytes a cycle, which is what a CU draws
-// from beyond its L2 however much is in flight (64 from L2). Packing the weight first takes a launch of 4 us more. With the
-// stage's reads behind its loads instead of in front of them 11.7 us. Neither fewer bytes a stage (16 x 32 tiles, twice the
-// CUs, 9.7: half of a weight line is drawn as a whole one), nor reads a stage ahead in a second register buffer (11.1), nor
-// wavefronts of their own for the loads (10.2), nor idle CUs that pull the XCD's lines into its L2 a few stages ahead (no
-// change) made it faster.
+// from beyond its L2 however much is in flight (64 from L2). Packing the weight first takes 3.9 us and, with the gap to the
+// second launch, 6-7 of a call. With the stage's reads behind its loads instead of in front of them 11.7 us. Neither fewer
+// bytes a stage (16 x 32 tiles, twice the CUs, 9.7: half of a weight line is drawn as a whole one), nor reads a stage ahead
+// in a second register buffer (11.1), nor wavefronts of their own for the loads (10.2), nor idle CUs that pull the XCD's
+// lines into its L2 a few stages ahead (no change) made it faster.
 #include "ficco_internal.h"
 #include "ficco_mfma.h"
 
@@ -38,7 +38,7 @@ struct DirectCfg {
     static constexpr int THREADS = 256;
     static constexpr int LOADS = FM + 4;               // load instructions per wavefront per stage: 4 FM KiB of A and 16 KiB of W
     // With 16 MFMAs a stage they go between its loads, which take 64 cycles each while all four wavefronts issue theirs: M 64,
-    // K 4096, N 768 17.9 -> 16.0 us, M 900, K 2048, N 1024 10.4 -> 9.8. With 4 or 8 nothing is gained (8.6 : 8.8, 11.6 : 11.4).
+    // K 4096, N 768 17.9 -> 15.5 us, M 900, K 2048, N 1024 10.4 -> 9.5. With 4 or 8 nothing is gained (8.6 : 8.8, 11.6 : 11.4).
     static constexpr bool BETWEEN = FM == 4;
     static_assert(FM == 1 || FM == 2 || FM == 4, "whole blocks of A per wavefront");
     static_assert(S >= 3 && (S - 2) * LOADS < 64, "vmcnt has 6 bits");

@@ -42,10 +42,10 @@ int scratch_of(int dev, unsigned char **out)
 // narrow tile, so it wins where a launch is a round or two of its tiles and loses where the resident kernel's big tiles
 // fill the chip. Estimates in us, from timings over M 1-8192, K 64-8192, N 8-4096: a stage of 128 k values takes 0.25 /
 // 0.31 / 0.46 us with 1 / 2 / 4 row blocks, a round starts in 2 us; the packed way takes the tile rule's estimate and 6 us
-// for the packing launch. Over 600 random products (M 1-8192, K 512-8192, N 64-4096) the way taken is 0.1 % slower than the
-// fastest (0.4 with 0.55, 1.5 and 4 in the place of 0.46, 2 and 6; calls under 4.6 us, which the host takes, count as that).
-// Measured, direct against packed: M 576, K 4224, N 992 16.2 : 22.7, M 1225, K 2496, N 904 22.1 : 21.3, M 1596, K 1600, N
-// 1880 27.4 : 22.5, M 2594, K 4096, N 680 39.6 : 28.4.
+// for the packing launch (3.9) and the gap behind it. Over 600 random products (M 1-8192, K 512-8192, N 64-4096) the way
+// taken is 0.1 % slower than the fastest (0.4 with 0.55, 1.5 and 4 in the place of 0.46, 2 and 6; calls under 4.6 us, which
+// the host takes, count as that). Measured, direct against packed: M 576, K 4224, N 992 16.3 : 22.7, M 1225, K 2496, N 904
+// 22.0 : 20.9, M 1596, K 1600, N 1880 27.3 : 21.5, M 2594, K 4096, N 680 39.6 : 27.4.
 int direct_row_blocks(int64_t M, int64_t K, int64_t N, int cus, double packed_us)
 {
     static const struct { int row_blocks; double stage; } cand[] = {{1, 0.25}, {2, 0.31}, {4, 0.46}};
