@@ -131,12 +131,14 @@ static bool runs_pair(const ficco_plan_t *p) { return (p->losses_of >= 0 ? p->lo
 // tile picked is 0.2-0.5 % slower than the fastest, and with them the fastest is 6-7 % faster than without in runs with
 // transfers, 28 % alone (us: M 512, K 4096, N 768 alone 64x128 19.4, 64x64 15.2, 32x64 12.3; the pair over four shards 66.1 /
 // 58.9 / 55.4; M 1024 of it over eight 69.5 / 61.6 / 69.2). Over 2900 launches of K 8256-32704 the fastest whole tile is
-// 14-31 % slower than the one picked in runs with transfers, 67 % alone. In launches of more 64x128 tiles than CUs, which whole
-// tiles fill the chip with, parts stay where tiles follow row pieces as these land (with / without parts: 187 pairs of two
-// and four steps 1 : 1.018, 581 expert-parallel ones 1 : 1.012). In the others they are never the fastest by more than a little, and
-// the fits of 64x64 and 128x128 are not good enough to tell them apart there (alone 1 : 0.88 over 540, column pieces 0.965 over
-// 460, streamed output 0.982 over 450, launches per step 0.989 over 440; alone, 64x64 / the fastest whole tile: M 10240, K 1600,
-// N 192 17.6 / 14.5, M 20224, K 1472, N 64 16.7 / 14.1, M 25600, K 448, N 64 8.7 / 7.7): no parts there.
+// 14-31 % slower than the one picked in runs with transfers, 67 % alone. Launches of more 64x128 tiles
+// than CUs, but not of 128x128 tiles, have parts only where tiles follow row pieces as these land (with / without parts: 182
+// pairs of two and four steps 1 : 1.02, 581 expert-parallel ones 1 : 1.01). In the others whole tiles fill the chip in one
+// round, no part is the fastest by more than a little, and the fits of 64x64 and 128x128 are not good enough to tell them
+// apart (alone 1 : 0.88 over 540, column pieces 0.96 over 400, streamed output 0.975 over 390, launches per step 0.986 over 400;
+// alone, 64x64 / the fastest whole tile: M 10240, K 1600, N 192 17.6 / 14.5, M 20224, K 1472, N 64 16.7 / 14.1, M 25600, K 448, N
+// 64 8.7 / 7.7). With more 128x128 tiles than CUs, a second round of them, it is 1.03-1.08 for streamed output, 1.01 for
+// launches per step, and 0.97 for column pieces, which have no parts then either.
 // Padded (masked) rows and columns are paid in full.
 // Where tiles wait for pieces every workgroup that does costs kWaitEach, a round costs kWaitRound more (a draw from the
 // lists' counters and a look at the piece's signal, neither of which hides behind another tile of the same workgroup), and
@@ -159,13 +161,19 @@ int choose_tile(const ficco_plan_t *p, int cus, bool whole_rows, double *us)
     const int lists = (is_resident(p) || p->grouped) && !(whole_rows && p->N <= 256) ? p->tile_col_lists : 0;
     bool parts = p->grouped || (p->schedule == FICCO_FINE_PERSISTENT && p->direction == FICCO_DIR_AG_GEMM && runs_pair(p));
     if (!parts) {
-        int64_t rows = p->M;               // of the largest launch
-        if (!is_resident(p)) {
-            int pieces = 0;
-            for (auto &g : p->groups) pieces = std::max(pieces, g.pos_end - g.pos_begin);
-            rows = pieces * p->m;
+        int64_t rows = p->M, tiles = 0;    // of the largest launch: rows, and 128-row tiles of row pieces
+        if (p->schedule == FICCO_FINE_PERSISTENT) {
+            tiles = (int64_t)p->n_chunks * ((p->m + 127) / 128);
+        } else if (!is_2d(p)) {
+            rows = 0;
+            for (auto &g : p->groups) {
+                const LaunchShape ls = launch_shape(p, g);
+                rows = std::max(rows, (int64_t)ls.n_blocks * ls.rows_per_block);
+                tiles = std::max(tiles, (int64_t)ls.n_blocks * ((ls.rows_per_block + 127) / 128));
+            }
         }
-        parts = ((rows + 63) / 64) * ((p->N + 127) / 128) <= cus;
+        const int64_t tn = (p->N + 127) / 128;
+        parts = ((rows + 63) / 64) * tn <= cus || tiles * tn > cus;
     }
     for (auto &cd : cand) {
         TileShape ts = tile_shape(cd.id);
