@@ -39,7 +39,7 @@ static __device__ __forceinline__ int wait_ready(const Gate &g, int chunk, Pace 
     uint32_t *f = g.flags + (size_t)chunk * kFlagStrideWords;
     const int64_t *sv = g.sig_value ? reinterpret_cast<const int64_t *>(g.sig_value[chunk]) : nullptr;
     int late = 0;
-    for (uint32_t polls = poll_phase(blockIdx.x);; ++polls) {
+    for (uint32_t polls = poll_phase(blockIdx.x, pace.every);; ++polls) {
         if ((!sv || pace.every > 1) && __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == g.epoch) return 1;
         if (late || polls % pace.every == 0) {
             if (sv && __hip_atomic_load(sv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) <= 0) {
@@ -86,7 +86,7 @@ static __device__ __forceinline__ int wait_ready_all(const Gate &g, int n, Pace 
         const int piece = piece_of(waiting ? base + lane : base);
         uint64_t missing = __ballot(waiting);
         int late = 0;
-        for (PollPlan poll(pace.every, poll_phase(blockIdx.x));;) {
+        for (PollPlan poll(pace.every, poll_phase(blockIdx.x, pace.every));;) {
             const int last = lane == 63 - __builtin_clzll(missing);
             const int landed = waiting && (poll.flags || last) &&
                                peek_ready(g, piece, pace.every > 1, (uint32_t)__builtin_popcountll(missing >> lane) <= poll.signals);

@@ -825,7 +825,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_resident2d_kernel(Resident2DL
                     // one look at up to 64 following slices, a lane each
                     const int mine = sl + 1 + (int)threadIdx.x;
                     int landed = o && mine < r.slices;
-                    for (int j = j0; j <= j1; ++j) landed = landed && peek_ready(gate, mine * r.shards + j, pace.every > 1, (poll_phase(blockIdx.x) + sl) % pace.every == 0);
+                    for (int j = j0; j <= j1; ++j) landed = landed && peek_ready(gate, mine * r.shards + j, pace.every > 1, (poll_phase(blockIdx.x, pace.every) + sl) % pace.every == 0);
                     const uint64_t not_landed = ~__ballot(landed);
                     const int run = not_landed ? __builtin_ctzll(not_landed) : 64;
                     if (threadIdx.x == 0) s_ok = o ? sl + 1 + run : 0;      // 0: gave up; else the slice after the run

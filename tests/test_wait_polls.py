@@ -46,7 +46,7 @@ static int bad(const char *what, int n, int every, int phase, int got)
 static int turns(int first, int step, int grid, int every, int slack)
 {
     std::vector<int> look(every);
-    for (int b = first; b < grid; b += step) ++look[poll_phase((uint32_t)b) % (uint32_t)every];
+    for (int b = first; b < grid; b += step) ++look[poll_phase((uint32_t)b, (uint32_t)every) % (uint32_t)every];
     const auto mm = std::minmax_element(look.begin(), look.end());
     return *mm.second - *mm.first <= slack ? 0 : bad("turns", step, every, first, *mm.second);
 }
@@ -55,10 +55,10 @@ int main()
 {
     int waits = 0;
     for (int every = 1; every <= 16; ++every)
-        for (int grid : {64, 96, 224, 256, 512}) {
+        for (int grid : {8, 24, 40, 64, 76, 96, 224, 256, 512}) {
             for (int x = 0; x < kTicketLists; ++x)
                 if (turns(x, kTicketLists, grid, every, 1)) return 1;
-            if (turns(0, 1, grid, every, kTicketLists)) return 1;
+            if (turns(0, 1, grid, every, 4)) return 1;
         }
     for (int every = 1; every <= 16; ++every)
         for (int phase = 0; phase < 256; ++phase)
